@@ -445,8 +445,10 @@ typedef struct gfs_serve_summary {
 /* Run a whole request stream and return when every request has completed (blocking).
  * reqs: host array of n requests (1 <= n <= 2^20); out: host array of n records, in the
  * order of reqs; summary may be NULL. Times are replayed on the host clock from the moment
- * the kernel is seen running. The call allocates its own device and pinned buffers and frees
- * them before returning; the kernel runs on hip_stream, which must not carry other work that
+ * the kernel is seen running. The call's device and pinned buffers (a chunk buffer per block,
+ * 64 B per request) are allocated by the first call and stay with the context for the next,
+ * grown when a call needs more; after a call that failed or needed more than 1 GiB, and by
+ * gfs_shutdown, they are freed. The kernel runs on hip_stream, which must not carry other work that
  * waits on it. Errors: -EINVAL (bad arguments), -EBADF (a file not registered), -ENOMEM,
  * -EIO (HIP error), -ETIMEDOUT (the kernel stopped serving); per-request failures are
  * reported in out[i].result with the call returning 0. */

@@ -423,6 +423,7 @@ int serve_core(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n, const gf
   uint32_t ninflight = 0;
   uint64_t reserved = 0, peak_reserved = 0, delivered = 0, last_query = 0;
   uint32_t next = 0, admitted = 0, completed = 0, peak_pending = 0;
+  uint64_t last_event = 0;   /* the last admission or completion */
   int err = 0;
   for (uint32_t i = 0; i < n; ++i) out[i] = gfs_serve_record{};
   while (completed < n) {
@@ -445,6 +446,7 @@ int serve_core(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n, const gf
       peak_reserved = std::max(peak_reserved, reserved);
       inflight[ninflight++] = q;
       ++qhead;
+      last_event = now;
     }
     bool progress = false;
     for (uint32_t j = 0; j < ninflight;) {
@@ -465,8 +467,11 @@ int serve_core(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n, const gf
       inflight[j] = inflight[--ninflight];
       progress = true;
     }
-    if (progress) continue;
     now = host_ns() - t0;
+    if (progress) {
+      last_event = now;
+      continue;
+    }
     if (now - last_query > 1000000ull) {   // the kernel must still be running
       last_query = now;
       if (hipStreamQuery(s) != hipErrorNotReady) {
@@ -476,6 +481,8 @@ int serve_core(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n, const gf
     }
     if (qhead == qtail && next < n && reqs[next].arrival_ns > now + 100000ull)
       nap_ns(std::min<uint64_t>(reqs[next].arrival_ns - now - 50000ull, 200000ull));
+    else if (ninflight && now - last_event < 200000ull)
+      __builtin_ia32_pause();   // the next completion is near; the shortest sleep takes 55 us
     else
       nap_ns(2000);
   }
@@ -496,16 +503,48 @@ int serve_core(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n, const gf
   return err;
 }
 
-/* buffers of one gfs_serve_run; freed on every exit path */
+/* Buffers of gfs_serve_run. A context keeps its last run's, so that a program that serves in
+   many short runs does not pay for the memory each time: 512 blocks x 1 MiB cost 0.5 ms a run
+   to allocate and free while the driver still had cleared memory, and 9-15 ms once it had to
+   clear what earlier runs gave back. A run that needs more than kKeepBytes gives it back. */
 struct ServeBuffers {
-  uint8_t* dev = nullptr;    /* table, control, block status */
-  uint8_t* bufs = nullptr;   /* one chunk buffer per block */
+  uint8_t* dev = nullptr;    /* table, control, block status; then one chunk buffer per block */
   uint8_t* pin = nullptr;    /* submissions, host control, completion records (pinned) */
-  ~ServeBuffers() {
-    if (dev) (void)hipFree(dev);
-    if (bufs) (void)hipFree(bufs);
-    if (pin) (void)hipHostFree(pin);
+  uint8_t* dpin = nullptr;   /* its device address */
+  uint64_t dev_bytes = 0, pin_bytes = 0;
+  int device = -1;
+  static constexpr uint64_t kKeepBytes = 1ull << 30;
+  /* hold at least that much, on device `dev_id` (current); the buffers are not in use. 0, -ENOMEM, -EIO */
+  int reserve(int dev_id, uint64_t dev_need, uint64_t pin_need) {
+    if (device == dev_id && dev && dev_bytes >= dev_need && pin && pin_bytes >= pin_need) return 0;
+    clear();
+    device = dev_id;
+    if (hipMalloc((void**)&dev, dev_need) != hipSuccess) {
+      dev = nullptr;
+      return -ENOMEM;
+    }
+    dev_bytes = dev_need;
+    if (hipHostMalloc((void**)&pin, pin_need, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+      pin = nullptr;
+      clear();
+      return -ENOMEM;
+    }
+    pin_bytes = pin_need;
+    void* p = nullptr;
+    if (hipHostGetDevicePointer(&p, pin, 0) != hipSuccess) {
+      clear();
+      return -EIO;
+    }
+    dpin = (uint8_t*)p;
+    return 0;
   }
+  void clear() {
+    if (dev) (void)hipFree(dev);
+    if (pin) (void)hipHostFree(pin);
+    dev = pin = dpin = nullptr;
+    dev_bytes = pin_bytes = 0;
+  }
+  ~ServeBuffers() { clear(); }
 };
 
 /* ---- the entry point that allocates nothing ----
@@ -533,6 +572,7 @@ struct gfs_serve_area {
   uint8_t* done_seen = nullptr;
   uint32_t* queue = nullptr;
   uint32_t* inflight = nullptr;
+  ServeBuffers kept;         /* gfs_serve_run's, freed with the context */
 };
 
 extern "C" void gfs_internal_serve_teardown(gfs_serve_area* a) {
@@ -597,13 +637,12 @@ extern "C" int gfs_serve_run(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32
   int rc = serve_check(ctx, reqs, n, p, out, &grid, &khz, &page);
   if (rc) return rc;
   const ServeSizes z = serve_sizes(n, grid, p->chunk_bytes);
-  ServeBuffers B;
-  if (hipMalloc((void**)&B.dev, z.tab + z.ctl + z.st) != hipSuccess) return -ENOMEM;
-  if (hipMalloc((void**)&B.bufs, z.bufs) != hipSuccess) return -ENOMEM;
-  if (hipHostMalloc((void**)&B.pin, z.sub + z.hc + z.dn, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
-    return -ENOMEM;
-  void* dpin = nullptr;
-  if (hipHostGetDevicePointer(&dpin, B.pin, 0) != hipSuccess) return -EIO;
+  gfs_serve_area* a = gfs_internal_ctx_serve_area(ctx);
+  int dev = -1;
+  if (!a || hipGetDevice(&dev) != hipSuccess) return -EIO;
+  ServeBuffers& B = a->kept;
+  rc = B.reserve(dev, z.tab + z.ctl + z.st + z.bufs, z.sub + z.hc + z.dn);
+  if (rc) return rc;
   std::vector<uint64_t> size(n), resv(n);
   std::vector<uint32_t> seq_req(n), queue(n), inflight(n);
   std::vector<uint8_t> done_seen(n);
@@ -611,11 +650,11 @@ extern "C" int gfs_serve_run(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32
   m.tab = (SrvEntry*)B.dev;
   m.ctl = (SrvCtrl*)(B.dev + z.tab);
   m.status = (int64_t*)(B.dev + z.tab + z.ctl);
-  m.bufs = B.bufs;
+  m.bufs = B.dev + z.tab + z.ctl + z.st;
   m.dev_clear = B.dev;
   m.dev_clear_bytes = z.tab + z.ctl + z.st;
   m.pin = B.pin;
-  m.dpin = (uint8_t*)dpin;
+  m.dpin = B.dpin;
   m.sub_bytes = z.sub;
   m.hc_bytes = z.hc;
   m.dn_bytes = z.dn;
@@ -625,7 +664,10 @@ extern "C" int gfs_serve_run(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32
   m.done_seen = done_seen.data();
   m.queue = queue.data();
   m.inflight = inflight.data();
-  return serve_core(ctx, reqs, n, p, out, summary, (hipStream_t)hip_stream, grid, khz, page, m);
+  rc = serve_core(ctx, reqs, n, p, out, summary, (hipStream_t)hip_stream, grid, khz, page, m);
+  /* after a failure the kernel may not have ended in order */
+  if (rc || B.dev_bytes + B.pin_bytes > ServeBuffers::kKeepBytes) B.clear();
+  return rc;
 }
 
 extern "C" int gfs_serve_run_noalloc(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n,
