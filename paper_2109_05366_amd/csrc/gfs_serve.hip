@@ -3,13 +3,19 @@
 // The host replays request arrivals on its own clock and admits them in arrival order
 // while the cache bytes reserved by unfinished requests stay within a budget; each
 // admitted request is appended to a submission array in pinned memory. On the device, the
-// persistent blocks take (request, chunk) units oldest request first: a request's chunks
-// are handed out by one fetch-and-add counter, so every block that finds work on the
-// oldest request helps finish it, and new requests join between chunks. One block at a
-// time polls the pinned submissions (so the rest spin on HBM only), copies new requests
-// into the device table, and turns the host's close into the exit condition. The block
-// that finishes a request's last chunk writes its completion record to pinned memory,
-// where the host sees it.
+// persistent blocks take (request, chunk) units oldest request first: the chunks of all
+// requests form one sequence in admission order, and a free block takes the next number of
+// that sequence from one counter, then waits until a request that holds it is there. So every
+// block that finds work on the oldest request helps finish it, and new requests join between
+// chunks. One block at a time polls the pinned submissions (so the rest spin on HBM only),
+// copies new requests into the device table, 64 at once, and turns the host's close into the
+// exit condition. The block that finishes a request's last chunk writes its completion record
+// to pinned memory, where the host sees it.
+//
+// A burst of small requests is bound by this hand-out, not by the reads: with a counter in
+// every request, all free blocks went through every request's counter in turn (about 13 us a
+// request with 512 blocks), and one lane read the submissions over the host link one after the
+// other. 64 requests of 313 MiB in all, cached, 512 blocks x 1 MiB chunks: 1313 -> 483 us a run.
 #include <errno.h>
 #include <string.h>
 #include <time.h>
@@ -36,11 +42,11 @@ using gfs_consumers::checksum_part;
 
 /* one admitted request, device memory, indexed by admission order */
 struct SrvEntry {
-  uint32_t ready;      /* 1 once the poller filled the entry in (release) */
+  uint32_t pad;
   uint32_t file;
   uint64_t size;
-  uint64_t nchunks;
-  uint64_t next;       /* chunks handed out */
+  uint64_t nchunks;    /* 0 until the poller filled the entry in */
+  uint64_t start;      /* number of its first chunk in the sequence of all requests' chunks */
   uint64_t done;       /* chunks finished */
   uint64_t csum;       /* wrapping sum over finished chunks */
   uint64_t t_first;    /* wall_clock64 when the request's first page was delivered (0: not yet) */
@@ -48,15 +54,18 @@ struct SrvEntry {
 };
 static_assert(sizeof(SrvEntry) == 64, "entry is one 64-byte record");
 
-/* device control words, one 128-byte line each */
+/* device control words, one 128-byte line for each group that is written together */
 struct SrvCtrl {
-  uint64_t cursor;      uint64_t pad0[15];   /* entries below it have every chunk handed out */
-  uint64_t ingested;    uint64_t pad1[15];   /* entries filled in (written by the poller only) */
+  uint64_t taken;       uint64_t pad0[15];   /* unit numbers handed out to blocks */
+  uint64_t ingested;    uint64_t pad1[15];   /* entries filled in (read and written by the poller only) */
   uint64_t poller;      uint64_t pad2[15];   /* 1 while a block polls the host */
-  uint64_t final_n;     uint64_t pad3[15];   /* 0 until the host has closed; then requests + 1 */
-  uint64_t abort;       uint64_t pad4[15];   /* 1: stop taking work */
-  uint64_t progress;    uint64_t pad5[15];   /* wall_clock64 of the last chunk or submission seen */
+  /* the line that waiting blocks read */
+  uint64_t units;                            /* units of the entries filled in (release) */
+  uint64_t final_n;                          /* 0 until the host has closed; then units + 1 */
+  uint64_t abort;       uint64_t pad3[13];   /* 1: stop taking work */
+  uint64_t progress;    uint64_t pad4[31];   /* wall_clock64 of the last chunk or submission seen */
 };
+static_assert(sizeof(SrvCtrl) == 768, "a part of the scratch limit callers are told");
 
 /* pinned host memory */
 struct SrvSub {
@@ -83,10 +92,11 @@ static_assert(sizeof(SrvDone) == 64, "completion record is 64 bytes");
 
 constexpr int kWork = 0, kExit = 1;
 
-/* Idle blocks back off to about 30 us between looks, so that a thousand of them polling
-   the table stay a small load on the memory system next to the blocks at work. */
-__device__ __forceinline__ void idle_nap(uint32_t& n) {
-  const uint32_t reps = n < 4 ? 1 : (n < 16 ? 2 : 8);
+/* A block whose unit is among the next 64 looks every 3-7 us; the others back off to about
+   14 us, so that a thousand of them stay a small load on the memory system next to the blocks
+   at work. */
+__device__ __forceinline__ void idle_nap(uint32_t& n, bool next) {
+  const uint32_t reps = n < 4 ? 1 : (next || n < 16 ? 2 : 4);
   for (uint32_t j = 0; j < reps; ++j) __builtin_amdgcn_s_sleep(127);
   ++n;
 }
@@ -117,90 +127,130 @@ __device__ void complete_entry(SrvEntry* e, SrvDone* dn, uint64_t t_first) {
   st_sys_rel(&dn->flag, 1);
 }
 
-/* The polling block: copy newly submitted requests into the table, and turn the host's
-   close (or abort, or a silent host) into the device's exit condition. Thread 0 only. */
+/* The polling block, one wave: copy newly submitted requests into the table, 64 at a time (lane
+   i the i-th: one round trip over the host link for all of them), and turn the host's close
+   (or abort, or a silent host) into the device's exit condition. */
 __device__ bool poll_host(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub* subs, SrvHost* host,
                           SrvDone* done, uint64_t chunk, uint64_t idle_ticks) {
+  const uint32_t l = gfsd::lane();
   const uint64_t now = wall_clock64();
-  if (ld_sys(&host->abort)) {
-    gfsd::st_rel(&ctl->abort, 1);
+  /* the three host words in one load */
+  const uint64_t* const word = l == 0 ? &host->tail : l == 1 ? &host->closed : &host->abort;
+  const uint64_t v = l < 3 ? ld_sys_rlx(word) : 0;
+  gfsd::acquire_system();
+  if (__shfl(v, 2, 64)) {
+    if (l == 0) gfsd::st_rel(&ctl->abort, 1);
     return false;
   }
-  const uint64_t tail = std::min<uint64_t>(ld_sys(&host->tail), cap);
-  const uint64_t ing = gfsd::ld_acq(&ctl->ingested);
+  const uint64_t tail = std::min<uint64_t>(__shfl(v, 0, 64), cap);
+  const uint64_t ing = gfsd::ld_rlx(&ctl->ingested);
+  uint64_t units = gfsd::ld_rlx(&ctl->units);
   if (tail > ing) {
-    for (uint64_t k = ing; k < tail; ++k) {
-      SrvEntry* e = &tab[k];
-      const uint64_t size = ld_sys_rlx(&subs[k].size);
-      e->file = ld_sys_rlx32(&subs[k].file);
-      e->size = size;
-      e->nchunks = (size + chunk - 1) / chunk;
-      __hip_atomic_store(&e->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      if (size == 0) complete_entry(e, &done[k], now);
+    for (uint64_t k0 = ing; k0 < tail; k0 += 64) {
+      const uint64_t k = k0 + l;
+      uint64_t size = 0, nch = 0;
+      if (k < tail) {
+        size = ld_sys_rlx(&subs[k].size);
+        tab[k].file = ld_sys_rlx32(&subs[k].file);
+        nch = (size + chunk - 1) / chunk;
+      }
+      uint64_t sum = nch;   /* over this lane and those below it */
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t o = __shfl_up(sum, off, 64);
+        if ((int)l >= off) sum += o;
+      }
+      if (k < tail) {
+        tab[k].size = size;
+        tab[k].start = units + sum - nch;
+        tab[k].nchunks = nch;
+        if (size == 0) complete_entry(&tab[k], &done[k], now);
+      }
+      units += __shfl(sum, 63, 64);
     }
-    gfsd::st_rel(&ctl->ingested, tail);
-    gfsd::st_rlx(&ctl->progress, now);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   /* every lane's entries, before units */
+    if (l == 0) {
+      gfsd::st_rlx(&ctl->ingested, tail);
+      gfsd::st_rlx(&ctl->units, units);
+      gfsd::st_rlx(&ctl->progress, now);
+    }
     return true;
   }
-  if (ld_sys(&host->closed) && ld_sys(&host->tail) == ing) {
-    gfsd::st_rel(&ctl->final_n, ing + 1);
+  /* closed was read together with tail: look at tail again, after it */
+  if (__shfl(v, 1, 64) && ld_sys(&host->tail) == ing) {
+    if (l == 0) gfsd::st_rel(&ctl->final_n, units + 1);
     return false;
   }
-  // other blocks store newer clock values into progress at any time: read the clock after
-  // it, and compare signed, so that a value stored after `now` was read is not "idle"
-  const uint64_t last = gfsd::ld_rlx(&ctl->progress);
-  const uint64_t t = wall_clock64();
-  if (last == 0) {
-    gfsd::st_rlx(&ctl->progress, t);
-  } else if ((int64_t)(t - last) > (int64_t)idle_ticks) {
-    gfsd::st_rel(&ctl->abort, 1);
+  if (l == 0) {
+    // other blocks store newer clock values into progress at any time: read the clock after
+    // it, and compare signed, so that a value stored after `now` was read is not "idle"
+    const uint64_t last = gfsd::ld_rlx(&ctl->progress);
+    const uint64_t t = wall_clock64();
+    if (last == 0) {
+      gfsd::st_rlx(&ctl->progress, t);
+    } else if ((int64_t)(t - last) > (int64_t)idle_ticks) {
+      gfsd::st_rel(&ctl->abort, 1);
+    }
   }
   return false;
 }
 
-/* Thread 0: find the next unit, oldest request first, or decide to exit. The flags and
-   counters are read relaxed: every block without work runs this loop, and an agent-scope
-   acquire would invalidate its XCD's L2 each time; an entry's fields are read after one
-   acquire fence, once its ready flag is seen. */
+/* Wave 0: take the next unit and wait until its request is in the table, or decide to exit.
+   The words a waiting block reads are read relaxed: an agent-scope acquire would invalidate
+   its XCD's L2 each time; the table is read after one acquire fence, once the unit is there.
+   hint: an entry at or before the one that holds the unit (a block's units only grow, so its
+   last one's), from which 64 entries are looked at in one round. */
 __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub* subs, SrvHost* host,
-                         SrvDone* done, uint64_t chunk, uint64_t idle_ticks, uint64_t* oi, uint64_t* ok) {
+                         SrvDone* done, uint64_t chunk, uint64_t idle_ticks, uint64_t& hint, uint64_t* ok,
+                         uint32_t* file, uint64_t* size) {
+  const uint32_t l = gfsd::lane();
+  uint64_t t = 0;
+  if (l == 0) t = gfsd::fadd64(&ctl->taken, 1);
+  t = __shfl(t, 0, 64);
   uint32_t naps = 0;
   while (true) {
-    if (gfsd::ld_rlx(&ctl->abort)) return kExit;
-    uint64_t c = gfsd::ld_rlx(&ctl->cursor);
-    for (uint64_t i = c; i < cap; ++i) {
-      SrvEntry* e = &tab[i];
-      if (__hip_atomic_load(&e->ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) break;
-      gfsd::acquire_agent();   /* the entry's fields, written before ready */
-      const uint64_t nch = e->nchunks;
-      // look before taking, so that idle blocks only read exhausted entries
-      if (gfsd::ld_rlx(&e->next) < nch) {
-        const uint64_t k = gfsd::fadd64(&e->next, 1);
-        if (k < nch) {
-          *oi = i;
-          *ok = k;
-          return kWork;
-        }
-      }
-      if (i == c) {
-        uint64_t expected = c;
-        gfsd::cas64(&ctl->cursor, expected, c + 1);   // a failed swap means another block moved it
-        c = c + 1;
-      }
+    uint64_t v = 0;
+    if (l < 3) v = gfsd::ld_rlx(l == 0 ? &ctl->units : l == 1 ? &ctl->final_n : &ctl->abort);
+    const uint64_t units = __shfl(v, 0, 64), fin = __shfl(v, 1, 64);
+    if (__shfl(v, 2, 64)) return kExit;
+    if (t < units) break;
+    if (fin && t >= fin - 1) return kExit;
+    int mine = 0;
+    if (l == 0 && gfsd::ld_rlx(&ctl->poller) == 0) {
+      uint64_t free_ = 0;
+      mine = gfsd::cas64(&ctl->poller, free_, 1) ? 1 : 0;
     }
-    const uint64_t fin = gfsd::ld_rlx(&ctl->final_n);
-    if (fin && gfsd::ld_rlx(&ctl->cursor) >= fin - 1) return kExit;
-    uint64_t free_ = 0;
-    if (gfsd::ld_rlx(&ctl->poller) == 0 && gfsd::cas64(&ctl->poller, free_, 1)) {
+    if (__shfl(mine, 0, 64)) {
       const bool fresh = poll_host(ctl, tab, cap, subs, host, done, chunk, idle_ticks);
-      gfsd::st_rel(&ctl->poller, 0);
+      if (l == 0) gfsd::st_rel(&ctl->poller, 0);
       if (fresh) {
         naps = 0;
         continue;
       }
     }
-    idle_nap(naps);
+    idle_nap(naps, t - units < 64);
   }
+  gfsd::acquire_agent();   /* the entries, written before units */
+  for (uint64_t base = hint; base < cap; base += 64) {
+    const uint64_t i = base + l;
+    uint64_t start = 0, nch = 0, sz = 0;
+    uint32_t f = 0;
+    if (i < cap) {
+      start = tab[i].start;
+      nch = tab[i].nchunks;
+      sz = tab[i].size;
+      f = tab[i].file;
+    }
+    const uint64_t m = __ballot(start <= t && t - start < nch);
+    if (m) {
+      const int at = __ffsll((unsigned long long)m) - 1;
+      hint = base + (uint64_t)at;
+      *ok = t - __shfl(start, at, 64);
+      *file = (uint32_t)__shfl((int)f, at, 64);
+      *size = __shfl(sz, at, 64);
+      return kWork;
+    }
+  }
+  return kExit;   /* not reached: units counts the chunks of entries in the table */
 }
 
 __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const gfs_dev* d, SrvEntry* tab, uint32_t cap, SrvCtrl* ctl, const SrvSub* subs,
@@ -219,15 +269,18 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
   int fd = -1;
   uint32_t cur_file = 0xffffffffu;
   int64_t err = 0, total = 0;
+  uint64_t hint = 0;   /* wave 0: the entry of the block's last unit */
   while (true) {
-    if (tid == 0) {
-      uint64_t i = 0, k = 0;
-      s_cmd = pick_unit(ctl, tab, cap, subs, host, done, chunk, idle_ticks, &i, &k);
-      if (s_cmd == kWork) {
-        s_i = i;
+    if (tid < 64) {
+      uint64_t k = 0, size = 0;
+      uint32_t file = 0;
+      const int cmd = pick_unit(ctl, tab, cap, subs, host, done, chunk, idle_ticks, hint, &k, &file, &size);
+      if (tid == 0) {
+        s_cmd = cmd;
+        s_i = hint;
         s_k = k;
-        s_file = tab[i].file;
-        s_size = tab[i].size;
+        s_file = file;
+        s_size = size;
       }
     }
     __syncthreads();
@@ -244,21 +297,25 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
     }
     const uint64_t off = k * chunk;
     const uint64_t len = std::min<uint64_t>(chunk, size - off);
-    if (r == 0 && k == 0) {
+    if (r == 0) {
       // the request's first page on its own, so that its delivery time is the time to
       // first page; then the rest of the chunk
-      const uint64_t first = std::min<uint64_t>(len, d->page_size);
-      r = gread(d, fd, 0, first, mybuf);
-      if (r == (int64_t)first && tid == 0) {
-        uint64_t zero = 0;
-        gfsd::cas64(&tab[i].t_first, zero, wall_clock64());
-      }
-      if (r == (int64_t)first && first < len) {
-        const int64_t r2 = gread(d, fd, first, len - first, mybuf + first);
-        r = r2 < 0 ? r2 : r + r2;
-      }
-    } else if (r == 0) {
-      r = gread(d, fd, off, len, mybuf);
+      const uint64_t first = k == 0 ? std::min<uint64_t>(len, d->page_size) : len;
+      uint64_t at = 0, piece = first;
+      do {
+        const int64_t got = gread(d, fd, off + at, piece, mybuf + at);
+        if (got < 0) {
+          r = got;
+          break;
+        }
+        r += got;
+        if (k == 0 && at == 0 && got == (int64_t)first && tid == 0) {
+          uint64_t zero = 0;
+          gfsd::cas64(&tab[i].t_first, zero, wall_clock64());
+        }
+        at += piece;
+        piece = len - at;
+      } while (r == (int64_t)at && piece);
     }
     const uint64_t part = r > 0 ? checksum_part(mybuf, (uint64_t)r, tid, nt) : 0;
     const uint64_t s = block_sum_u64(part, red, tid, nt);
