@@ -53,6 +53,8 @@ constexpr uint32_t kMaxWindow = GFS_MAX_WINDOW_PAGES;
 constexpr uint64_t kFrameMask = (1ull << GFS_ENTRY_FRAME_BITS) - 1;
 /* page-table entry frame value of a page reserved by a miss that has no frame yet */
 constexpr uint32_t kReserved = (uint32_t)kFrameMask;
+/* group pass: no table entry; an entry whose frame is not ready to be copied from */
+constexpr int32_t kAbsent = -1, kNotReady = -2;
 
 /* Per-block state in LDS, shared by gopen/gread/gclose within one kernel. */
 struct BlockState {
@@ -79,17 +81,17 @@ struct BlockState {
   uint32_t nclaim;              /* entries of lslot[] claimed for pulling */
   uint32_t help_page;           /* page of the frame a helping block pulls */
   int32_t pslot;                /* private policy: the block's slot (-1: none) */
-  int32_t bframe[64];           /* batched hits: frame pinned for page base + i, or -1 */
+  int32_t bframe[2][64];        /* group pass: frame pinned for page base + i, kAbsent (no table
+                                   entry) or kNotReady; the two halves take turns (par) */
+  uint64_t bbad[2];             /* group pass: pages whose frame turned out to hold another page */
+  uint32_t par;                 /* the half the next group pass uses */
   uint32_t trig;                /* asynchronous readahead: this page access took a marker */
   uint32_t a_pending;           /* 1: this block has an asynchronous request outstanding, whose
                                    pages and frames are list[0..a_n) / lframe[0..a_n) */
   uint32_t a_slot, a_n, a_file;
   int32_t a_status;
   uint64_t a_gen, a_first;
-  uint64_t tagkey;              /* nonzero: frame is pinned VALID and its tag is still to be
-                                   compared with this key (the hit's copy carries the check) */
-  uint64_t pinw;                /* the frame word the pin returned (for the hit's bit updates) */
-  int32_t tag_ok;               /* the check's outcome, for every thread of the block */
+  uint32_t naps;                /* back-off of the page access in progress (lane 0) */
   uint64_t read_last;           /* last page of the gread in progress: a readahead window
                                    opened by a miss covers the read up to it */
 };
@@ -121,12 +123,33 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-/* ------------------------------------------------------------------ atomics (agent scope) */
+/* ------------------------------------------------------------------ the device handle
+ * Written by the host before any kernel and never changed while one runs, so its fields are
+ * read as constants: through the scalar cache, which no acquire empties, and kept in scalar
+ * registers across fences and barriers. As ordinary memory each field was a vector load that
+ * every acquire sent back to memory: about five dependent round trips a page on the hit path. */
+typedef const __attribute__((address_space(4))) gfs_dev hdev;
+__device__ __forceinline__ hdev* H(const gfs_dev* d) { return (hdev*)d; }
+/* A function that is not inlined gets the handle's address in vector registers; it is the same
+   in every lane. */
+__device__ __forceinline__ const gfs_dev* uniform(const gfs_dev* d) {
+  const uint64_t a = (uint64_t)d;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return (const gfs_dev*)(((uint64_t)hi << 32) | lo);
+}
+
+/* ------------------------------------------------------------------ atomics (agent scope)
+ * The library's atomics are all on global memory (metadata, pinned ring): said to the compiler,
+ * which otherwise emits flat accesses that also wait for LDS. */
+typedef __attribute__((address_space(1))) uint64_t gu64;
+typedef __attribute__((address_space(1))) uint32_t gu32;
+__device__ __forceinline__ gu64* G(uint64_t* p) { return (gu64*)p; }
+__device__ __forceinline__ gu32* G(uint32_t* p) { return (gu32*)p; }
 __device__ __forceinline__ uint64_t ld_rlx(uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(G(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t ld_acq(uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(G(p), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
 /* Spin loops poll with relaxed loads and take one acquire fence once the awaited value is
    seen: an agent-scope acquire invalidates the XCD's L2, and hundreds of waiting blocks
@@ -147,31 +170,31 @@ __device__ __forceinline__ void drain_atomics() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 __device__ __forceinline__ uint32_t ld_rlx32(uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(G(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_rlx(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(G(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_rel(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(G(p), v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_rlx32(uint32_t* p, uint32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(G(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool cas64(uint64_t* p, uint64_t& expected, uint64_t desired) {
-  return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_ACQ_REL,
+  return __hip_atomic_compare_exchange_strong(G(p), &expected, desired, __ATOMIC_ACQ_REL,
                                               __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool cas64_rlx(uint64_t* p, uint64_t& expected, uint64_t desired) {
-  return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
+  return __hip_atomic_compare_exchange_strong(G(p), &expected, desired, __ATOMIC_RELAXED,
                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool cas32(uint32_t* p, uint32_t& expected, uint32_t desired) {
-  return __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_ACQ_REL,
+  return __hip_atomic_compare_exchange_strong(G(p), &expected, desired, __ATOMIC_ACQ_REL,
                                               __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t fadd64(uint64_t* p, uint64_t v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_add(G(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 /* block-local statistics: only thread 0 of the block (lane 0 of wave 0) adds */
 __device__ __forceinline__ void bcount(BlockState* bs, int c, uint64_t v) { bs->ctr[c] += v; }
@@ -190,17 +213,16 @@ __device__ __forceinline__ void nap_short(uint32_t& n) {
   ++n;
 }
 __device__ __forceinline__ bool expired(const gfs_dev* d, uint64_t t0) {
-  return wall_clock64() - t0 > d->timeout_ticks;
+  return wall_clock64() - t0 > H(d)->timeout_ticks;
 }
 
 /* ------------------------------------------------------------------ trace */
-__device__ __forceinline__ void trace_ev(const gfs_dev* d, uint32_t level, uint32_t op,
-                                         uint32_t block, uint32_t file, uint32_t page,
-                                         uint32_t frame, uint32_t a, uint64_t b) {
-  if (d->trace_level < level) return;
-  const uint64_t i = fadd64(&d->g->trace_n, 1);
-  if (i >= d->trace_cap) return;
-  gfs_event* e = ((gfs_event*)d->trace) + i;
+__device__ __attribute__((noinline)) void trace_store(const gfs_dev* d, uint32_t op, uint32_t block,
+                                                      uint32_t file, uint32_t page, uint32_t frame, uint32_t a,
+                                                      uint64_t b) {
+  const uint64_t i = fadd64(&H(d)->g->trace_n, 1);
+  if (i >= H(d)->trace_cap) return;
+  gfs_event* e = ((gfs_event*)H(d)->trace) + i;
   e->op = op;
   e->block = block;
   e->file = file;
@@ -208,6 +230,10 @@ __device__ __forceinline__ void trace_ev(const gfs_dev* d, uint32_t level, uint3
   e->frame = frame;
   e->a = a;
   e->b = b;
+}
+__device__ __forceinline__ void trace_ev(const gfs_dev* d, uint32_t level, uint32_t op, uint32_t block,
+                                         uint32_t file, uint32_t page, uint32_t frame, uint32_t a, uint64_t b) {
+  if (H(d)->trace_level >= level) trace_store(d, op, block, file, page, frame, a, b);
 }
 
 /* ------------------------------------------------------------------ hashed page table
@@ -235,10 +261,10 @@ __device__ __forceinline__ void key_buckets_m(uint32_t mask, uint64_t key, uint3
 }
 __device__ __forceinline__ void key_buckets(const gfs_dev* d, uint64_t key, uint32_t& b1,
                                             uint32_t& b2) {
-  key_buckets_m(d->nbuckets_mask, key, b1, b2);
+  key_buckets_m(H(d)->nbuckets_mask, key, b1, b2);
 }
 __device__ __forceinline__ uint64_t* slot_ptr(const gfs_dev* d, uint32_t b1, uint32_t b2, int i) {
-  return d->pt + (uint64_t)(i < GFS_BUCKET_SLOTS ? b1 : b2) * GFS_BUCKET_SLOTS + (i & 15);
+  return H(d)->pt + (uint64_t)(i < GFS_BUCKET_SLOTS ? b1 : b2) * GFS_BUCKET_SLOTS + (i & 15);
 }
 
 /* wave-collective: lanes 0-15 read bucket 1, lanes 16-31 bucket 2; uniform result: the
@@ -255,7 +281,7 @@ __device__ __forceinline__ int32_t pt_lookup_at(uint64_t* pt, uint32_t mask, uin
   return (int32_t)(hit & kFrameMask);
 }
 __device__ int32_t pt_lookup_wave(const gfs_dev* d, uint64_t key) {
-  return pt_lookup_at(d->pt, d->nbuckets_mask, key);
+  return pt_lookup_at(H(d)->pt, H(d)->nbuckets_mask, key);
 }
 
 /* per lane: the 32 candidate entries of a key, loaded together (one round trip) */
@@ -266,7 +292,8 @@ __device__ __forceinline__ void pt_load_lane(const gfs_dev* d, uint32_t b1, uint
 }
 
 /* per lane: true if key has an entry (a frame or a reservation) */
-__device__ bool pt_present_lane(const gfs_dev* d, uint64_t key) {
+__device__ __attribute__((noinline)) bool pt_present_lane(const gfs_dev* d, uint64_t key) {
+  d = uniform(d);
   uint32_t b1, b2;
   key_buckets(d, key, b1, b2);
   uint64_t e[2 * GFS_BUCKET_SLOTS];
@@ -277,22 +304,10 @@ __device__ bool pt_present_lane(const gfs_dev* d, uint64_t key) {
   return hit;
 }
 
-/* per lane: the frame key maps to, kReserved, or -1 when absent */
-__device__ int32_t pt_find_lane(const gfs_dev* d, uint64_t key) {
-  uint32_t b1, b2;
-  key_buckets(d, key, b1, b2);
-  uint64_t e[2 * GFS_BUCKET_SLOTS];
-  pt_load_lane(d, b1, b2, e);
-  int32_t f = -1;
-#pragma unroll
-  for (int i = 0; i < 2 * GFS_BUCKET_SLOTS; ++i)
-    if ((e[i] >> GFS_ENTRY_FRAME_BITS) == key) f = (int32_t)(e[i] & kFrameMask);
-  return f;
-}
-
 /* per lane, under key's file lock: reserve key; returns the global slot index or -1 if
  * both buckets are full */
-__device__ int64_t pt_reserve_lane(const gfs_dev* d, uint64_t key) {
+__device__ __attribute__((noinline)) int64_t pt_reserve_lane(const gfs_dev* d, uint64_t key) {
+  d = uniform(d);
   const uint64_t ent = (key << GFS_ENTRY_FRAME_BITS) | kReserved;
   uint32_t b1, b2;
   key_buckets(d, key, b1, b2);
@@ -312,13 +327,14 @@ __device__ int64_t pt_reserve_lane(const gfs_dev* d, uint64_t key) {
     if (pick < 0) return -1;
     uint64_t expect = 0;
     uint64_t* sp = slot_ptr(d, b1, b2, pick);
-    if (cas64_rlx(sp, expect, ent)) return (int64_t)(sp - d->pt);
+    if (cas64_rlx(sp, expect, ent)) return (int64_t)(sp - H(d)->pt);
   }
   return -1;
 }
 
 /* per lane: clear the entry key -> frame (the caller owns it) */
-__device__ bool pt_delete_lane(const gfs_dev* d, uint64_t key, uint32_t frame) {
+__device__ __attribute__((noinline)) bool pt_delete_lane(const gfs_dev* d, uint64_t key, uint32_t frame) {
+  d = uniform(d);
   const uint64_t ent = (key << GFS_ENTRY_FRAME_BITS) | frame;
   uint32_t b1, b2;
   key_buckets(d, key, b1, b2);
@@ -334,7 +350,7 @@ __device__ bool pt_delete_lane(const gfs_dev* d, uint64_t key, uint32_t frame) {
 }
 
 /* ------------------------------------------------------------------ frame words */
-enum { PIN_RETRY = 0, PIN_VALID = 1, PIN_FILLING = 2, PIN_ERROR = 3, PIN_VALID_UNCHECKED = 4 };
+enum { PIN_RETRY = 0, PIN_VALID = 1, PIN_FILLING = 2, PIN_ERROR = 3 };
 
 /* Pins are counted with fetch-and-add and fetch-and-subtract, so a pin costs one atomic
  * round trip and dropping one costs none (the wave does not wait for it). Every other change
@@ -352,7 +368,7 @@ enum { PIN_RETRY = 0, PIN_VALID = 1, PIN_FILLING = 2, PIN_ERROR = 3, PIN_VALID_U
  * one of them: a page a reader consumed and the cache dropped lies behind that reader, and a
  * demanded one means the file is being read again. */
 __device__ __forceinline__ uint64_t* shadow_word(const gfs_dev* d, uint32_t file, uint64_t q) {
-  return d->shadow + (uint64_t)file * (GFS_SHADOW_PAGES / 64) + (q >> 6);
+  return H(d)->shadow + (uint64_t)file * (GFS_SHADOW_PAGES / 64) + (q >> 6);
 }
 __device__ __forceinline__ bool shadow_lane(const gfs_dev* d, uint32_t file, uint64_t q) {
   if (q >= GFS_SHADOW_PAGES) return false;
@@ -360,11 +376,21 @@ __device__ __forceinline__ bool shadow_lane(const gfs_dev* d, uint32_t file, uin
 }
 __device__ __forceinline__ void shadow_set_lane(const gfs_dev* d, uint32_t file, uint64_t q) {
   if (q < GFS_SHADOW_PAGES)
-    __hip_atomic_fetch_or(shadow_word(d, file, q), 1ull << (q & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_or(G(shadow_word(d, file, q)), 1ull << (q & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void frame_unpin(const gfs_dev* d, uint32_t f) {
-  __hip_atomic_fetch_sub(&d->fword[f], GFS_FW_PIN_ONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_fetch_sub(G(&H(d)->fword[f]), GFS_FW_PIN_ONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+/* The bit updates of a demand pin: set the reference bit, clear the prefetched mark (the page
+   has now been demanded). Idempotent; the wave does not wait for them. */
+__device__ __forceinline__ void frame_pin_bits(const gfs_dev* d, uint32_t f, uint64_t w) {
+  uint64_t* fw = &H(d)->fword[f];
+  if (!(w & GFS_FW_REF))
+    __hip_atomic_fetch_or(G(fw), GFS_FW_REF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (w & GFS_FW_RA)
+    __hip_atomic_fetch_and(G(fw), ~GFS_FW_RA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 /* Pin frame f if it is filling or valid and still holds key; sets the reference bit and
@@ -372,11 +398,11 @@ __device__ __forceinline__ void frame_unpin(const gfs_dev* d, uint32_t f) {
  * bytes, published with release by the block that filled it, are visible afterwards, and
  * the tag is read after the pin is in place (a frame cannot be claimed while pinned). */
 __device__ int frame_pin(const gfs_dev* d, uint32_t f, uint64_t key, uint64_t* w_out = nullptr) {
-  uint64_t* fw = &d->fword[f];
-  const uint64_t w = __hip_atomic_fetch_add(fw, GFS_FW_PIN_ONE, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+  uint64_t* fw = &H(d)->fword[f];
+  const uint64_t w = __hip_atomic_fetch_add(G(fw), GFS_FW_PIN_ONE, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
   if (w_out) *w_out = w;
   const uint64_t st = w & GFS_FW_STATE;
-  if ((st != GFS_FS_FILLING && st != GFS_FS_VALID) || ld_rlx(&d->ftag[f]) != key) {
+  if ((st != GFS_FS_FILLING && st != GFS_FS_VALID) || ld_rlx(&H(d)->ftag[f]) != key) {
     frame_unpin(d, f);
     return PIN_RETRY;
   }
@@ -384,52 +410,14 @@ __device__ int frame_pin(const gfs_dev* d, uint32_t f, uint64_t key, uint64_t* w
     frame_unpin(d, f);   /* the host read of this page failed */
     return PIN_ERROR;
   }
-  /* idempotent bit updates; the wave does not wait for them */
-  if (!(w & GFS_FW_REF))
-    __hip_atomic_fetch_or(fw, GFS_FW_REF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (w & GFS_FW_RA)
-    __hip_atomic_fetch_and(fw, ~GFS_FW_RA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return st == GFS_FS_VALID ? PIN_VALID : PIN_FILLING;
-}
-
-/* The bit updates of a demand pin: set the reference bit, clear the prefetched mark (the page
-   has now been demanded). Idempotent; the wave does not wait for them. */
-__device__ __forceinline__ void frame_pin_bits(const gfs_dev* d, uint32_t f, uint64_t w) {
-  uint64_t* fw = &d->fword[f];
-  if (!(w & GFS_FW_REF))
-    __hip_atomic_fetch_or(fw, GFS_FW_REF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (w & GFS_FW_RA)
-    __hip_atomic_fetch_and(fw, ~GFS_FW_RA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-/* Pin frame f for a hit whose tag comparison travels with the copy: a VALID frame without
- * the error bit is left pinned and reported PIN_VALID_UNCHECKED (w receives the word the pin
- * returned); the caller loads the frame's tag together with the first loads of its copy and
- * keeps the copy only if the tag is key (a pinned frame cannot be claimed, so the tag read
- * after the pin is the one the bytes belong to), then applies frame_pin_bits. Any other state
- * goes through frame_pin's checks. Saves frame_pin's dependent tag load on every hit. */
-__device__ int frame_pin_fast(const gfs_dev* d, uint32_t f, uint64_t key, uint64_t& w_out) {
-  uint64_t* fw = &d->fword[f];
-  const uint64_t w = __hip_atomic_fetch_add(fw, GFS_FW_PIN_ONE, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-  w_out = w;
-  const uint64_t st = w & GFS_FW_STATE;
-  if (st == GFS_FS_VALID && !(w & GFS_FW_ERR)) return PIN_VALID_UNCHECKED;
-  if ((st != GFS_FS_FILLING && st != GFS_FS_VALID) || ld_rlx(&d->ftag[f]) != key) {
-    frame_unpin(d, f);
-    return PIN_RETRY;
-  }
-  if (st == GFS_FS_VALID) {
-    frame_unpin(d, f);   /* the host read of this page failed */
-    return PIN_ERROR;
-  }
   frame_pin_bits(d, f, w);
-  return PIN_FILLING;
+  return st == GFS_FS_VALID ? PIN_VALID : PIN_FILLING;
 }
 
 /* Lane: the pinned frame's word showed the marker bit; clear it. True for the one block whose
    clearing took it (that block advances the stream). */
 __device__ __forceinline__ bool mark_take_lane(const gfs_dev* d, uint32_t f) {
-  const uint64_t old = __hip_atomic_fetch_and(&d->fword[f], ~GFS_FW_MARK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t old = __hip_atomic_fetch_and(G(&H(d)->fword[f]), ~GFS_FW_MARK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return (old & GFS_FW_MARK) != 0;
 }
 
@@ -438,9 +426,9 @@ __device__ __forceinline__ bool mark_take_lane(const gfs_dev* d, uint32_t f) {
  * decided on, for the trace: the reference bit << 1 | pinned << 2 | lost race << 3 |
  * state << 4 (the word was read, then a compare-and-swap against it failed: SKIP). */
 __device__ int hand_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t& vra, uint32_t& seen) {
-  uint64_t* fw = &d->fword[f];
+  uint64_t* fw = &H(d)->fword[f];
   uint64_t w = ld_rlx(fw);
-  const uint64_t tag = ld_rlx(&d->ftag[f]);   /* loaded with the word; used only on EVICT */
+  const uint64_t tag = ld_rlx(&H(d)->ftag[f]);   /* loaded with the word; used only on EVICT */
   const uint64_t st = w & GFS_FW_STATE;
   const uint64_t claimed = (((w >> GFS_FW_VER_SHIFT) + 1) << GFS_FW_VER_SHIFT) | GFS_FS_CLAIMED;
   seen = ((w & GFS_FW_REF) ? 2u : 0u) | ((w & GFS_FW_PINS) ? 4u : 0u) | ((uint32_t)st << 4);
@@ -472,7 +460,7 @@ __device__ int hand_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t
 __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
   uint32_t n = 0;
   while (true) {
-    const uint64_t w = ld_rlx(&d->fword[f]);
+    const uint64_t w = ld_rlx(&H(d)->fword[f]);
     if ((w & GFS_FW_STATE) == GFS_FS_VALID) {
       acquire_agent();   /* the frame's bytes, published before VALID */
       if (w & GFS_FW_ERR) {
@@ -513,7 +501,7 @@ __device__ __forceinline__ uint64_t lock_waiting(uint64_t n, uint64_t page) {
   return (1ull << 63) | (page << 32) | (uint64_t)((uint32_t)n << 2);
 }
 __device__ __forceinline__ uint64_t* lock_slot(const gfs_dev* d, uint32_t file, uint64_t n) {
-  return d->lockq + (uint64_t)file * GFS_LOCK_SLOTS + (n & (GFS_LOCK_SLOTS - 1));
+  return H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS + (n & (GFS_LOCK_SLOTS - 1));
 }
 
 /* Lane 0: leave the queue if ticket t is not granted yet; true if it is out of the queue
@@ -521,10 +509,10 @@ __device__ __forceinline__ uint64_t* lock_slot(const gfs_dev* d, uint32_t file, 
    the caller holds it). */
 __device__ bool lock_try_leave_lane(const gfs_dev* d, uint32_t file, uint64_t t) {
   uint64_t* sl = lock_slot(d, file, t);
-  uint64_t v = __hip_atomic_load(sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint64_t v = __hip_atomic_load(G(sl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   while (v != lock_granted(t)) {
     if (v == lock_covered(t)) return true;
-    if (__hip_atomic_compare_exchange_strong(sl, &v, lock_left(t), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    if (__hip_atomic_compare_exchange_strong(G(sl), &v, lock_left(t), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT))
       return true;
   }
@@ -533,34 +521,25 @@ __device__ bool lock_try_leave_lane(const gfs_dev* d, uint32_t file, uint64_t t)
 
 /* Wave-collective. Waits for the file's miss lock for page `page` (key `key`); while
  * waiting, looks up `key` in the table now and then and leaves the queue if it appeared.
- * Returns LOCK_OWN (ticket set), LOCK_LEFT, LOCK_COVERED (the holder's window covers the
- * page) or LOCK_TIMEOUT (left the queue after the wait timeout). */
-__device__ int lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key, uint64_t page, uint64_t t0,
-                              uint64_t& ticket, bool may_leave = true);
-/* Wave-collective: pass the lock on; [lo, hi) is the window the holder has just claimed
-   (lo == hi: none). has_pre: lane l's `pre` is the value of the slot of ticket + 1 + l, read
-   earlier under the lock, and the first look uses it instead of reading the slots again. */
-__device__ void unlock_file_wave(const gfs_dev* d, uint32_t file, uint64_t ticket, uint64_t lo, uint64_t hi,
-                                 bool has_pre = false, uint64_t pre = 0);
-
-__device__ int32_t pt_lookup_wave(const gfs_dev* d, uint64_t key);
-
-__device__ int lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key, uint64_t page, uint64_t t0,
-                              uint64_t& ticket, bool may_leave) {
+ * Returns the ticket << 2 | LOCK_OWN, LOCK_LEFT, LOCK_COVERED (the holder's window covers the
+ * page) or LOCK_TIMEOUT (left the queue after the wait timeout): in registers, as a result
+ * through memory would be loaded back with the lock held. */
+__device__ __attribute__((noinline)) uint64_t lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key,
+                                                             uint64_t page, uint64_t t0, bool may_leave = true) {
+  d = uniform(d);
   uint64_t t = 0;
   if (lane() == 0)
-    t = __hip_atomic_fetch_add(&d->locks[file].next, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t = __hip_atomic_fetch_add(G(&H(d)->locks[file].next), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   t = __shfl(t, 0, 64);
-  ticket = t;
   int res = LOCK_OWN;
   if (t != 0) {
     uint64_t* sl = lock_slot(d, file, t);
     /* announce the page, unless the grant is already there */
     int own = 0;
     if (lane() == 0) {
-      uint64_t v = __hip_atomic_load(sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint64_t v = __hip_atomic_load(G(sl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       while (v != lock_granted(t)) {
-        if (__hip_atomic_compare_exchange_strong(sl, &v, lock_waiting(t, page), __ATOMIC_RELAXED,
+        if (__hip_atomic_compare_exchange_strong(G(sl), &v, lock_waiting(t, page), __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
           break;
       }
@@ -570,7 +549,7 @@ __device__ int lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key, uin
     for (uint32_t n = 0; !own; ++n) {
       int st = -1;   /* -1: keep waiting */
       if (lane() == 0) {
-        const uint64_t v = __hip_atomic_load(sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t v = __hip_atomic_load(G(sl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (v == lock_granted(t)) st = LOCK_OWN;
         else if (v == lock_covered(t)) st = LOCK_COVERED;
       }
@@ -597,7 +576,7 @@ __device__ int lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key, uin
     }
   }
   drain_atomics();
-  return res;
+  return (t << 2) | (uint64_t)res;
 }
 
 /* Wave-collective: pass the lock to the first later ticket that is still waiting for it
@@ -610,7 +589,7 @@ __device__ int lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key, uin
  * waiter left just before the exchange, the scan goes on after it. A ticket that has not
  * announced its page yet is granted the lock like any other. */
 /* lq: the file's queue slots, ticket n in lq[n mod GFS_LOCK_SLOTS] */
-__device__ void unlock_slots_wave(uint64_t* lq, uint64_t ticket, uint64_t lo, uint64_t hi, bool has_pre,
+__device__ __attribute__((noinline)) void unlock_slots_wave(uint64_t* lq, uint64_t ticket, uint64_t lo, uint64_t hi, bool has_pre,
                                   uint64_t pre) {
   drain_atomics();
   const uint32_t l = lane();
@@ -628,7 +607,7 @@ __device__ void unlock_slots_wave(uint64_t* lq, uint64_t ticket, uint64_t lo, ui
       const uint32_t first = ~skip ? (uint32_t)__builtin_ctzll(~skip) : 64u;
       if (cov && l < first) {
         /* loses only to the waiter leaving, which takes it out of the queue as well */
-        (void)__hip_atomic_compare_exchange_strong(sl, &v, lock_covered(nl), __ATOMIC_RELAXED,
+        (void)__hip_atomic_compare_exchange_strong(G(sl), &v, lock_covered(nl), __ATOMIC_RELAXED,
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (first == 64) {
@@ -639,7 +618,7 @@ __device__ void unlock_slots_wave(uint64_t* lq, uint64_t ticket, uint64_t lo, ui
     }
     uint64_t old = 0;
     if (l == 0)
-      old = __hip_atomic_exchange(lq + (n & (GFS_LOCK_SLOTS - 1)), lock_granted(n), __ATOMIC_RELAXED,
+      old = __hip_atomic_exchange(G(lq + (n & (GFS_LOCK_SLOTS - 1))), lock_granted(n), __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_AGENT);
     old = __shfl(old, 0, 64);
     if (old != lock_left(n)) return;
@@ -647,10 +626,10 @@ __device__ void unlock_slots_wave(uint64_t* lq, uint64_t ticket, uint64_t lo, ui
     look = true;
   }
 }
-/* the same, given the file instead of its queue slots */
-__device__ void unlock_file_wave(const gfs_dev* d, uint32_t file, uint64_t ticket, uint64_t lo, uint64_t hi,
-                                 bool has_pre, uint64_t pre) {
-  unlock_slots_wave(d->lockq + (uint64_t)file * GFS_LOCK_SLOTS, ticket, lo, hi, has_pre, pre);
+/* the same, given the file instead of its queue slots, which have not been read */
+__device__ __forceinline__ void unlock_file_wave(const gfs_dev* d, uint32_t file, uint64_t ticket, uint64_t lo,
+                                                 uint64_t hi) {
+  unlock_slots_wave(H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS, ticket, lo, hi, false, 0);
 }
 
 /* ------------------------------------------------------------------ readahead detector
@@ -668,7 +647,9 @@ __device__ void unlock_file_wave(const gfs_dev* d, uint32_t file, uint64_t ticke
  * read next to cached pages), and a context or new window covers at least those req pages
  * (Sec. 2.3: the prefetcher reads at least what the caller asked for), up to the cap. */
 /* Per lane: the file's detector state, loaded together (lane i: recent miss i, stream
-   slot i); the decision below uses it after the caller's acquire fence. */
+   slot i, lanes past them a copy that is not used); the decision below uses it after the
+   caller waited for it. No load depends on the lane: loads under a lane condition were waited
+   for one group after the other, a round trip more with the miss lock held. */
 struct RaState {
   uint32_t advice, clk, rn;
   uint64_t r, s_next;
@@ -676,20 +657,26 @@ struct RaState {
 };
 __device__ __forceinline__ RaState ra_load_lane(gfs_file_dev* fe, uint32_t nrec, uint32_t nstreams) {
   const uint32_t l = lane();
-  RaState st{};
+  RaState st;
   st.advice = ld_rlx32(&fe->advice);
-  if (l == 0) st.clk = ld_rlx32(&fe->clock);
+  st.clk = ld_rlx32(&fe->clock);
   st.rn = ld_rlx32(&fe->recent_n);
-  if (l < nrec) st.r = ld_rlx(&fe->recent[l]);
-  if (l < nstreams) {
-    gfs_stream* sp = &fe->streams[l];
-    st.s_next = ld_rlx(&sp->next);
-    st.s_size = ld_rlx32(&sp->size);
-    st.s_last = ld_rlx32(&sp->last_use);
-    st.s_valid = ld_rlx32(&sp->valid);
-    st.s_marker = ld_rlx32(&sp->marker);
-  }
+  st.r = ld_rlx(&fe->recent[l < nrec ? l : 0]);
+  gfs_stream* sp = &fe->streams[l < nstreams ? l : 0];
+  st.s_next = ld_rlx(&sp->next);
+  st.s_size = ld_rlx32(&sp->size);
+  st.s_last = ld_rlx32(&sp->last_use);
+  st.s_valid = ld_rlx32(&sp->valid);
+  st.s_marker = ld_rlx32(&sp->marker);
   return st;
+}
+
+/* The values of a round of loads are used only from here on, after the caller's wait: without
+   this the compiler put work on the first of them between the loads, and so a wait for a round
+   trip before the last ones were issued. */
+__device__ __forceinline__ void ra_loaded(RaState& st, uint64_t& a, uint64_t& b) {
+  asm volatile("" : "+v"(st.advice), "+v"(st.clk), "+v"(st.rn), "+v"(st.r), "+v"(st.s_next), "+v"(st.s_size),
+               "+v"(st.s_last), "+v"(st.s_valid), "+v"(st.s_marker), "+v"(a), "+v"(b));
 }
 
 /* Which rule decided a window (GFS_RA_RULE_*, recorded in the trace with the detector's inputs). */
@@ -702,10 +689,10 @@ enum { RA_RULE_OFF = GFS_RA_RULE_OFF, RA_RULE_ZONE = GFS_RA_RULE_ZONE, RA_RULE_A
    windows of all resident readers together do not exceed the cache. */
 __device__ __forceinline__ uint32_t ra_cap_eff(const gfs_dev* d) {
   const uint64_t grid = (uint64_t)gridDim.x * gridDim.y * gridDim.z;
-  const uint64_t r = grid < d->ra_quota_blocks ? grid : d->ra_quota_blocks;
-  uint64_t q = d->nframes / (r ? r : 1);
+  const uint64_t r = grid < H(d)->ra_quota_blocks ? grid : H(d)->ra_quota_blocks;
+  uint64_t q = H(d)->nframes / (r ? r : 1);
   if (q < 1) q = 1;
-  return d->ra_cap < q ? d->ra_cap : (uint32_t)q;
+  return H(d)->ra_cap < q ? H(d)->ra_cap : (uint32_t)q;
 }
 
 /* The detector's constants, read before a block takes the miss lock, so that the holder's
@@ -717,11 +704,11 @@ struct RaParams {
 __device__ __forceinline__ RaParams ra_params(const gfs_dev* d) {
   RaParams q;
   q.cap = ra_cap_eff(d);
-  q.nrec = d->ra_recent;
-  q.nstreams = d->streams;
-  q.near_min = d->ra_near_min;
-  q.init = d->ra_init;
-  q.radius = d->ra_near_pages;
+  q.nrec = H(d)->ra_recent;
+  q.nstreams = H(d)->streams;
+  q.near_min = H(d)->ra_near_min;
+  q.init = H(d)->ra_init;
+  q.radius = H(d)->ra_near_pages;
   return q;
 }
 
@@ -732,7 +719,8 @@ __device__ __forceinline__ RaParams ra_params(const gfs_dev* d) {
  * anyway, so the lock's holder probes no table entries for this: the count is the table as
  * the block saw it when it missed (with accesses made one at a time, the same as under the
  * lock), and the decision uses it alone. */
-__device__ uint32_t ra_history_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint32_t req) {
+__device__ __attribute__((noinline)) uint32_t ra_history_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint32_t req) {
+  d = uniform(d);
   const uint32_t l = lane();
   const uint32_t cap = ra_cap_eff(d);
   const uint32_t r = req < cap ? req : cap;
@@ -797,11 +785,11 @@ __device__ void ra_decide_wave(gfs_file_dev* fe, uint64_t p, uint32_t req, uint3
       j = __ffsll((unsigned long long)inv) - 1;
     } else {
       uint64_t k = l < rp.nstreams ? (((uint64_t)s_last << 8) | l) : ~0ull;
-      for (int off = 32; off > 0; off >>= 1) {
+      for (int off = GFS_MAX_STREAMS / 2; off > 0; off >>= 1) {
         const uint64_t o = __shfl_xor(k, off, 64);
         k = o < k ? o : k;
       }
-      j = (int)(k & 0xff);
+      j = __builtin_amdgcn_readfirstlane((int)(k & 0xff));
     }
     if (near >= rp.near_min) {
       /* many blocks missing close together: the file is read in aggregate (interleaved
@@ -852,17 +840,18 @@ __device__ void ra_decide_wave(gfs_file_dev* fe, uint64_t p, uint32_t req, uint3
  * FILLING (pinned for the demanded page, marked prefetched otherwise) and its reserved
  * table entry is pointed at the frame. Returns how many pages got frames (a prefix of the
  * list); stops after 2 * nframes visits without enough frames. */
-__device__ uint32_t alloc_wave(const gfs_dev* d, uint32_t file, uint64_t demand, BlockState* bs,
+__device__ __attribute__((noinline)) uint32_t alloc_wave(const gfs_dev* d, uint32_t file, uint64_t demand, BlockState* bs,
                                uint32_t n, uint32_t bid, uint64_t mark = ~0ull) {
+  d = uniform(d);
   const uint32_t l = lane();
   uint32_t assigned = 0;
   uint64_t visits = 0;
   uint32_t evicted = 0, wasted = 0;
-  const uint64_t limit = 2ull * d->nframes;
+  const uint64_t limit = 2ull * H(d)->nframes;
   while (assigned < n && visits < limit) {
     const uint32_t need = (n - assigned) < 64u ? (n - assigned) : 64u;
     uint64_t base = 0;
-    if (l == 0) base = fadd64(&d->g->hand, need);
+    if (l == 0) base = fadd64(&H(d)->g->hand, need);
     base = __shfl(base, 0, 64);
     int act = -1;
     uint32_t f = 0;
@@ -870,7 +859,7 @@ __device__ uint32_t alloc_wave(const gfs_dev* d, uint32_t file, uint64_t demand,
     uint32_t vra = 0, seen = 0;
     const uint64_t t = base + l;
     if (l < need) {
-      f = (uint32_t)(t % d->nframes);
+      f = (uint32_t)(t % H(d)->nframes);
       act = hand_visit(d, f, vkey, vra, seen);
       if (act == GFS_HAND_EVICT) {
         const uint32_t vf = (uint32_t)(vkey >> GFS_KEY_PAGE_BITS) - 1u;
@@ -893,14 +882,14 @@ __device__ uint32_t alloc_wave(const gfs_dev* d, uint32_t file, uint64_t demand,
           shadow_set_lane(d, (uint32_t)(vkey >> GFS_KEY_PAGE_BITS) - 1u, vkey & ((1ull << GFS_KEY_PAGE_BITS) - 1));
       }
       const uint64_t key = page_key(file, q);
-      st_rlx(&d->ftag[f], key);
-      st_rlx(&d->ffill[f], 0ull);   /* the request that fills it is not known yet */
+      st_rlx(&H(d)->ftag[f], key);
+      st_rlx(&H(d)->ffill[f], 0ull);   /* the request that fills it is not known yet */
       /* CLAIMED (no flags, no pins of ours) -> FILLING, version + 1, pinned for the demanded
          page, prefetched mark otherwise; an addition keeps pins other blocks hold briefly */
       const uint64_t delta = (GFS_FS_FILLING - GFS_FS_CLAIMED) + GFS_FW_VER_ONE +
                              (q == demand ? GFS_FW_PIN_ONE : GFS_FW_RA) + (q == mark ? GFS_FW_MARK : 0ull);
-      __hip_atomic_fetch_add(&d->fword[f], delta, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      st_rel(d->pt + bs->lslot[k], (key << GFS_ENTRY_FRAME_BITS) | f);
+      __hip_atomic_fetch_add(G(&H(d)->fword[f]), delta, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      st_rel(H(d)->pt + bs->lslot[k], (key << GFS_ENTRY_FRAME_BITS) | f);
       bs->lframe[k] = f;
       trace_ev(d, 1, GFS_EV_ALLOC, bid, file, (uint32_t)q, f, q == demand ? 0u : 1u, t);
     }
@@ -921,15 +910,10 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 /* Block-cooperative copy of n bytes; both pointers 16-byte aligned and in global memory
  * (frames, user buffers). Global rather than generic accesses let loads and stores be
- * waited on separately, so eight 16-byte loads per lane are in flight per round.
- * kStream: the source is read with nontemporal loads, which do not keep its lines in the
- * caches; the copy-out of a frame uses it, so that streaming page bytes through does not
- * push the page table and frame words out of L2 (all-hit pass: +3 % with the reads alone,
- * +6 % with a consumer reading the user buffer back, lookup and pin 0.3 us shorter). */
+ * waited on separately, so eight 16-byte loads per lane are in flight per round. */
 typedef __attribute__((address_space(1))) v4u gv4u;
 
-template <bool kStream = false>
-__device__ __forceinline__ void copy_block_aligned(uint8_t* dst, const uint8_t* src, uint64_t n,
+__device__ __attribute__((noinline)) void copy_block_aligned(uint8_t* dst, const uint8_t* src, uint64_t n,
                                                    uint32_t tid, uint32_t nt) {
   const uint64_t n16 = n >> 4;
   const gv4u* s = (const gv4u*)src;
@@ -938,10 +922,7 @@ __device__ __forceinline__ void copy_block_aligned(uint8_t* dst, const uint8_t* 
   for (; i + 7ull * nt < n16; i += 8ull * nt) {
     v4u a[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (kStream) a[k] = __builtin_nontemporal_load(&s[i + (uint64_t)k * nt]);
-      else a[k] = s[i + (uint64_t)k * nt];
-    }
+    for (int k = 0; k < 8; ++k) a[k] = s[i + (uint64_t)k * nt];
 #pragma unroll
     for (int k = 0; k < 8; ++k) o[i + (uint64_t)k * nt] = a[k];
   }
@@ -949,13 +930,44 @@ __device__ __forceinline__ void copy_block_aligned(uint8_t* dst, const uint8_t* 
   for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) dst[j] = src[j];
 }
 
-/* The copy-out of a frame's bytes to a user buffer (any alignment). */
-__device__ __forceinline__ void copy_block(uint8_t* dst, const uint8_t* src, uint64_t n,
-                                           uint32_t tid, uint32_t nt) {
-  if ((((uintptr_t)dst | (uintptr_t)src) & 15) == 0) {
-    copy_block_aligned<true>(dst, src, n, tid, nt);
-  } else {
-    for (uint64_t j = tid; j < n; j += nt) dst[j] = src[j];
+/* 16 bytes at any address of global memory: one vector load, which the memory unit splits
+   where it crosses lines */
+typedef v4u v4u_any __attribute__((aligned(1)));
+typedef __attribute__((address_space(1))) v4u_any gv4u_any;
+typedef __attribute__((address_space(1))) uint8_t gu8;
+
+/* The copy-out of n bytes of one frame to a user buffer, both at any alignment: 16-byte stores
+ * aligned in dst, loads from wherever the bytes lie in the frame, the fewer than 16 bytes
+ * before and after them one byte a thread. Eight loads a thread are in flight, also in the
+ * last, partly filled round; they are nontemporal, so that page bytes streaming through do
+ * not push the page table and frame words out of L2. */
+__device__ __forceinline__ void copy_out(uint8_t* dst, const uint8_t* src, uint32_t n, uint32_t tid, uint32_t nt) {
+  uint32_t head = (0u - (uint32_t)(uintptr_t)dst) & 15u;
+  if (head > n) head = n;
+  const uint32_t tail = (n - head) & 15u;
+  if (head | tail) {
+    const uint32_t e = tid < 16 ? tid : n - tail + (tid - 16);
+    if (tid < head || (tid >= 16 && tid - 16 < tail)) ((gu8*)dst)[e] = ((const gu8*)src)[e];
+  }
+  const gv4u_any* s = (const gv4u_any*)(src + head);
+  gv4u* o = (gv4u*)(dst + head);
+  const uint32_t n16 = (n - head) >> 4;
+  uint32_t i = tid;
+  for (; i + 7 * nt < n16; i += 8 * nt) {
+    v4u a[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) a[k] = __builtin_nontemporal_load(&s[i + k * nt]);
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) o[i + k * nt] = a[k];
+  }
+  if (i < n16) {
+    v4u a[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k)
+      if (i + k * nt < n16) a[k] = __builtin_nontemporal_load(&s[i + k * nt]);
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k)
+      if (i + k * nt < n16) o[i + k * nt] = a[k];
   }
 }
 
@@ -964,9 +976,10 @@ __device__ __forceinline__ void copy_block(uint8_t* dst, const uint8_t* src, uin
  * try to take over copying this frame's bytes from staging (the PULL bit), so that blocks
  * waiting on a large window pull its pages in parallel. Leaves in bs: status, frame, and
  * pull = 2 with slot/gen/first_page/result when this block must pull frame f. */
-__device__ void join_or_help_lane(const gfs_dev* d, uint32_t f, uint64_t p, uint64_t t0,
+__device__ __attribute__((noinline)) void join_or_help_lane(const gfs_dev* d, uint32_t f, uint64_t p, uint64_t t0,
                                   BlockState* bs) {
-  uint64_t* fw = &d->fword[f];
+  d = uniform(d);
+  uint64_t* fw = &H(d)->fword[f];
   uint32_t n = 0;
   bs->frame = (int32_t)f;
   bs->pull = 0;
@@ -983,21 +996,21 @@ __device__ void join_or_help_lane(const gfs_dev* d, uint32_t f, uint64_t p, uint
       return;
     }
     if (!(w & GFS_FW_PULL)) {
-      const uint64_t ff = ld_rlx(&d->ffill[f]);
+      const uint64_t ff = ld_rlx(&H(d)->ffill[f]);
       if (ff >> 63) {
         /* an asynchronous request: nobody publishes it, so look at the host's completion in
            the ring slot itself (the slot cannot be reused while this frame is filling) */
         const uint32_t s = (uint32_t)((ff >> 40) & 0x7fffff) - 1;
         const uint64_t gen = ff & ((1ull << 40) - 1);
-        gfs_rpc_slot* rs = &d->ring[s];
-        if (__hip_atomic_load(&rs->done_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == gen) {
+        gfs_rpc_slot* rs = &H(d)->ring[s];
+        if (__hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == gen) {
           acquire_system();   /* the staged bytes and the result, written before done_seq */
           if (cas64(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
             bs->status = 0;
             bs->pull = 2;
             bs->slot = s;
             bs->gen = gen;
-            bs->first_page = rs->offset >> d->page_shift;
+            bs->first_page = rs->offset >> H(d)->page_shift;
             bs->result = rs->result;
             bs->help_page = (uint32_t)p;
             return;
@@ -1006,7 +1019,7 @@ __device__ void join_or_help_lane(const gfs_dev* d, uint32_t f, uint64_t p, uint
         }
       } else if (ff) {
         const uint32_t s = (uint32_t)(ff >> 40) - 1;
-        gfs_req_dev* rq = &d->reqd[s];
+        gfs_req_dev* rq = &H(d)->reqd[s];
         const uint64_t ready = ld_rlx(&rq->ready);
         if (ready != 0 && (ready & ((1ull << 40) - 1)) == (ff & ((1ull << 40) - 1))) {
           acquire_agent();   /* the request record, published before ready */
@@ -1085,7 +1098,7 @@ __device__ uint32_t reserve_run_small_wave(const gfs_dev* d, uint32_t file, uint
     if (pick >= 0) {
       uint64_t expect = 0;
       uint64_t* sp = slot_ptr(d, b1, b2, pick);
-      if (cas64_rlx(sp, expect, ent)) slot = (int64_t)(sp - d->pt);
+      if (cas64_rlx(sp, expect, ent)) slot = (int64_t)(sp - H(d)->pt);
       else slot = pt_reserve_lane(d, key);    /* the entry was taken meanwhile: reload */
     }
     bs->list[i] = (uint32_t)q;
@@ -1106,26 +1119,26 @@ __device__ uint32_t reserve_run_small_wave(const gfs_dev* d, uint32_t file, uint
  * waiting (or is not issued), because its pages are pulled only when readers reach them, and a
  * ticketed request queued behind such a slot could wait for readers that wait for it. */
 __device__ __forceinline__ void ring_ticket_lane(const gfs_dev* d, uint32_t bid, uint64_t& tk) {
-  const uint32_t S = d->sync_slots;
-  if (d->partitioned) {
+  const uint32_t S = H(d)->sync_slots;
+  if (H(d)->partitioned) {
     const uint32_t s = bid % S;
-    tk = fadd64(&d->slot_tail[s], 1) * S + s;
+    tk = fadd64(&H(d)->slot_tail[s], 1) * S + s;
   } else {
-    tk = fadd64(&d->g->ring_tail, 1);
+    tk = fadd64(&H(d)->g->ring_tail, 1);
   }
 }
 __device__ __forceinline__ uint32_t ring_slot(const gfs_dev* d, uint32_t, uint64_t tk) {
-  return (uint32_t)(tk % d->sync_slots);
+  return (uint32_t)(tk % H(d)->sync_slots);
 }
-__device__ __forceinline__ uint64_t ring_gen(const gfs_dev* d, uint64_t tk) { return tk / d->sync_slots + 1; }
+__device__ __forceinline__ uint64_t ring_gen(const gfs_dev* d, uint64_t tk) { return tk / H(d)->sync_slots + 1; }
 
 /* Lane: take a free slot of the asynchronous windows (busy 0 -> 1), starting at the block's
    own; -1 if every one is held. The slot's next generation is one past its last completed. */
 __device__ int32_t async_slot_take_lane(const gfs_dev* d, uint32_t bid) {
-  const uint32_t A = d->rpc_slots - d->sync_slots;
+  const uint32_t A = H(d)->rpc_slots - H(d)->sync_slots;
   for (uint32_t i = 0; i < A; ++i) {
-    const uint32_t s = d->sync_slots + (bid + i) % A;
-    uint64_t* b = &d->reqd[s].busy;
+    const uint32_t s = H(d)->sync_slots + (bid + i) % A;
+    uint64_t* b = &H(d)->reqd[s].busy;
     uint64_t z = 0;
     if (ld_rlx(b) == 0 && cas64(b, z, 1ull)) return (int32_t)s;
   }
@@ -1145,9 +1158,9 @@ __device__ int64_t reserve_unique_wave(const gfs_dev* d, uint64_t key);
 /* Lane: claim frame f of the block's share: FREE, or VALID with no pins (its page is
    evicted; the reference bit plays no part). CLAIMED on success. */
 __device__ int lra_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t& vra) {
-  uint64_t* fw = &d->fword[f];
+  uint64_t* fw = &H(d)->fword[f];
   uint64_t w = ld_rlx(fw);
-  const uint64_t tag = ld_rlx(&d->ftag[f]);
+  const uint64_t tag = ld_rlx(&H(d)->ftag[f]);
   const uint64_t st = w & GFS_FW_STATE;
   const uint64_t claimed = (((w >> GFS_FW_VER_SHIFT) + 1) << GFS_FW_VER_SHIFT) | GFS_FS_CLAIMED;
   if (w & GFS_FW_PINS) return GFS_HAND_SKIP;
@@ -1162,8 +1175,9 @@ __device__ int lra_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t&
 
 /* Wave 0: the miss path of the private policy. 0: done (bs filled in), 1: look again,
    2: timed out. */
-__device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint64_t key, uint64_t fsize,
-                                 BlockState* bs, uint32_t bid, uint64_t t0, uint32_t& naps) {
+__device__ __attribute__((noinline)) int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint64_t key, uint64_t fsize,
+                                 BlockState* bs, uint32_t bid, uint64_t t0) {
+  d = uniform(d);
   const uint32_t l = lane();
   /* the page's table entry, made unique without the file's lock (the policy decides nothing
      under it: the window is the static prefetch after p, into the block's own buffer) */
@@ -1177,7 +1191,7 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
     if (!expired(d, t0)) {
       if (l == 0) {
         bcount(bs, GFS_C_RETRIES, 1);
-        nap(naps);
+        nap(bs->naps);
       }
       return 1;
     }
@@ -1190,15 +1204,15 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
   }
   int status = 0;
   if (l == 0) {
-    gfs_pslot* ps = &d->pslots[bs->pslot];
-    const uint64_t npages = d->files[file].npages;
-    const uint32_t cap = d->ra_cap;
+    gfs_pslot* ps = &H(d)->pslots[bs->pslot];
+    const uint64_t npages = H(d)->files[file].npages;
+    const uint32_t cap = H(d)->ra_cap;
     const uint32_t span = (uint32_t)((npages - p) < (uint64_t)(1 + cap) ? (npages - p) : (uint64_t)(1 + cap));
     const bool in_pb = ps->n && ps->file == file && ps->first <= p && p < ps->first + ps->n;
     trace_ev(d, 1, GFS_EV_MISS, bid, file, (uint32_t)p, 0, in_pb ? 1u : span, p);
     /* a frame of the block's share, least recently allocated first */
     const uint64_t ta0 = wall_clock64();
-    const uint32_t q = d->quota;
+    const uint32_t q = H(d)->quota;
     const uint32_t base = (uint32_t)bs->pslot * q;
     int32_t fr = -1;
     for (uint32_t i = 0; i < 2 * q && fr < 0; ++i) {
@@ -1222,15 +1236,15 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
     bcount(bs, GFS_C_HAND, 1);
     if (fr < 0) {
       /* every frame of the share is pinned by other blocks: give the page back, retry */
-      st_rel(d->pt + slot, 0ull);
+      st_rel(H(d)->pt + slot, 0ull);
       bcount(bs, GFS_C_NOFRAME, 1);
       status = 1;
     } else {
-      st_rlx(&d->ftag[fr], key);
-      st_rlx(&d->ffill[fr], 0ull);
-      __hip_atomic_fetch_add(&d->fword[fr], (GFS_FS_FILLING - GFS_FS_CLAIMED) + GFS_FW_VER_ONE + GFS_FW_PIN_ONE,
+      st_rlx(&H(d)->ftag[fr], key);
+      st_rlx(&H(d)->ffill[fr], 0ull);
+      __hip_atomic_fetch_add(G(&H(d)->fword[fr]), (GFS_FS_FILLING - GFS_FS_CLAIMED) + GFS_FW_VER_ONE + GFS_FW_PIN_ONE,
                              __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      st_rel(d->pt + slot, (key << GFS_ENTRY_FRAME_BITS) | (uint64_t)fr);
+      st_rel(H(d)->pt + slot, (key << GFS_ENTRY_FRAME_BITS) | (uint64_t)fr);
       trace_ev(d, 1, GFS_EV_ALLOC, bid, file, (uint32_t)p, (uint32_t)fr, 0, (uint64_t)ps->lra_next);
       bcount(bs, GFS_T_ALLOC, wall_clock64() - ta0);
       bcount(bs, GFS_C_MISSES, 1);
@@ -1244,8 +1258,8 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
         bs->help_page = (uint32_t)p;
       } else {
         /* one request: the page and the prefetch that follows it */
-        const uint64_t off0 = p << d->page_shift;
-        uint64_t len = (uint64_t)span << d->page_shift;
+        const uint64_t off0 = p << H(d)->page_shift;
+        uint64_t len = (uint64_t)span << H(d)->page_shift;
         if (off0 + len > fsize) len = fsize - off0;
         uint64_t tk;
         ring_ticket_lane(d, bid, tk);
@@ -1253,7 +1267,7 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
         const uint64_t gen = ring_gen(d, tk);
         uint32_t nn = 0;
         const uint64_t ts0 = wall_clock64();
-        while (ld_rlx(&d->slot_free[s]) != gen - 1) {
+        while (ld_rlx(&H(d)->slot_free[s]) != gen - 1) {
           if (expired(d, t0)) {
             status = 2;
             break;
@@ -1263,19 +1277,19 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
         acquire_agent();   /* the slot's last users are done with its staging */
         bcount(bs, GFS_T_SLOT, wall_clock64() - ts0);
         if (status == 0) {
-          gfs_rpc_slot* rs = &d->ring[s];
+          gfs_rpc_slot* rs = &H(d)->ring[s];
           rs->file_id = file;
           rs->npages = span;
           rs->offset = off0;
           rs->length = len;
           rs->ticket = tk;
-          __hip_atomic_store(&rs->req_seq, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+          __hip_atomic_store(G(&rs->req_seq), gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
           trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)p, GFS_NO_FRAME, span, tk);
           bcount(bs, GFS_C_REQUESTS, 1);
           bcount(bs, GFS_C_REQ_BYTES, len);
           bcount(bs, GFS_C_FETCHED, 1);
           const uint64_t th0 = wall_clock64();
-          while (__hip_atomic_load(&rs->done_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != gen) {
+          while (__hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != gen) {
             if (expired(d, t0)) {
               status = 2;
               break;
@@ -1304,7 +1318,7 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
   status = __shfl(status, 0, 64);
   if (status == 1) {
     if (expired(d, t0)) return 2;
-    if (l == 0) nap(naps);
+    if (l == 0) nap(bs->naps);
     return 1;
   }
   return 0;
@@ -1314,8 +1328,9 @@ __device__ int miss_private_wave(const gfs_dev* d, uint32_t file, uint64_t p, ui
  * post one request for the span of those pages, tell blocks waiting on its frames which request
  * fills them, wait for the host, and publish the finished read for the helpers. Leaves in bs:
  * status, the demanded page's frame, pull = 1 (this block pulls the request). Returns 0. */
-__device__ int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, BlockState* bs, uint32_t bid,
+__device__ __attribute__((noinline)) int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, BlockState* bs, uint32_t bid,
                               uint64_t t0, uint32_t got) {
+  d = uniform(d);
   const uint32_t l = lane();
   /* span of the pages that got frames: p and a contiguous piece of the run */
   uint64_t lo = ~0ull, hi = 0;
@@ -1331,8 +1346,8 @@ __device__ int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, B
   }
   /* post the request for the span [lo, hi] and wait for the host */
   const uint32_t span = (uint32_t)(hi - lo + 1);
-  const uint64_t off0 = lo << d->page_shift;
-  uint64_t len = (uint64_t)span << d->page_shift;
+  const uint64_t off0 = lo << H(d)->page_shift;
+  uint64_t len = (uint64_t)span << H(d)->page_shift;
   if (off0 + len > fsize) len = fsize - off0;
   int64_t status = 0;
   uint64_t tk = 0;
@@ -1342,7 +1357,7 @@ __device__ int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, B
     const uint64_t gen = ring_gen(d, tk);
     uint32_t nn = 0;
     const uint64_t ts0 = wall_clock64();
-    while (ld_rlx(&d->slot_free[s]) != gen - 1) {
+    while (ld_rlx(&H(d)->slot_free[s]) != gen - 1) {
       if (expired(d, t0)) {
         status = -kETIMEDOUT;
         break;
@@ -1352,13 +1367,13 @@ __device__ int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, B
     acquire_agent();   /* the slot's last users are done with its staging */
     bcount(bs, GFS_T_SLOT, wall_clock64() - ts0);
     if (status == 0) {
-      gfs_rpc_slot* rs = &d->ring[s];
+      gfs_rpc_slot* rs = &H(d)->ring[s];
       rs->file_id = file;
       rs->npages = span;
       rs->offset = off0;
       rs->length = len;
       rs->ticket = tk;
-      __hip_atomic_store(&rs->req_seq, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(G(&rs->req_seq), gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
       trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)lo, GFS_NO_FRAME, span, tk);
       bcount(bs, GFS_C_MISSES, 1);
       bcount(bs, GFS_C_REQUESTS, 1);
@@ -1374,14 +1389,14 @@ __device__ int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, B
   if (status == 0) {
     /* tell waiting blocks which request fills each frame: (slot + 1) << 40 | gen */
     const uint64_t fill = ((uint64_t)(s + 1) << 40) | (gen & ((1ull << 40) - 1));
-    for (uint32_t k = l; k < got; k += 64) st_rel(&d->ffill[bs->lframe[k]], fill);
+    for (uint32_t k = l; k < got; k += 64) st_rel(&H(d)->ffill[bs->lframe[k]], fill);
   }
   if (l == 0) {
     if (status == 0) {
-      gfs_rpc_slot* rs = &d->ring[s];
+      gfs_rpc_slot* rs = &H(d)->ring[s];
       uint32_t nn = 0;
       const uint64_t th0 = wall_clock64();
-      while (__hip_atomic_load(&rs->done_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) !=
+      while (__hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) !=
              gen) {
         if (expired(d, t0)) {
           status = -kETIMEDOUT;
@@ -1394,11 +1409,11 @@ __device__ int post_wait_wave(const gfs_dev* d, uint32_t file, uint64_t fsize, B
       if (status == 0) {
         bs->result = rs->result;
         /* let blocks waiting on frames of this request pull their own pages */
-        gfs_req_dev* rq = &d->reqd[s];
+        gfs_req_dev* rq = &H(d)->reqd[s];
         rq->result = bs->result;
         rq->first_page = lo;
         rq->file = file;
-        __hip_atomic_store(&rq->remaining, got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(G(&rq->remaining), got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         st_rel(&rq->ready, gen);
       }
     }
@@ -1456,7 +1471,7 @@ __device__ int64_t reserve_unique_wave(const gfs_dev* d, uint64_t key) {
       }
       return -1;
     }
-    return (int64_t)(sp - d->pt);
+    return (int64_t)(sp - H(d)->pt);
   }
   return -2;
 }
@@ -1465,8 +1480,9 @@ __device__ int64_t reserve_unique_wave(const gfs_dev* d, uint64_t key) {
  * no detector decision to make, so no miss lock; the page's reservation is made unique by
  * reserve_unique_wave. Same results and trace events as the locked path for such a file.
  * Returns as miss_shared_wave. */
-__device__ int miss_one_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint64_t key, uint64_t fsize,
-                                  BlockState* bs, uint32_t bid, uint64_t t0, uint32_t& naps) {
+__device__ __attribute__((noinline)) int miss_one_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint64_t key, uint64_t fsize,
+                                  BlockState* bs, uint32_t bid, uint64_t t0) {
+  d = uniform(d);
   const uint32_t l = lane();
   const uint64_t tr0 = wall_clock64();
   const int64_t slot = reserve_unique_wave(d, key);
@@ -1476,7 +1492,7 @@ __device__ int miss_one_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
     if (!expired(d, t0)) {
       if (l == 0) {
         bcount(bs, GFS_C_RETRIES, 1);
-        nap(naps);
+        nap(bs->naps);
       }
       return 1;
     }
@@ -1501,11 +1517,11 @@ __device__ int miss_one_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
   if (got == 0) {
     /* every frame pinned or filling: give the page back and retry the access */
     if (l == 0) {
-      st_rel(d->pt + slot, 0ull);
+      st_rel(H(d)->pt + slot, 0ull);
       bcount(bs, GFS_C_NOFRAME, 1);
     }
     if (expired(d, t0)) return 2;
-    if (l == 0) nap(naps);
+    if (l == 0) nap(bs->naps);
     return 1;
   }
   return post_wait_wave(d, file, fsize, bs, bid, t0, 1);
@@ -1519,9 +1535,10 @@ __device__ int miss_one_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
  * the wait timed out. */
 __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint32_t file, uint64_t p,
                                                           uint64_t key, uint64_t fsize, BlockState* bs,
-                                                          uint32_t bid, uint64_t t0, uint32_t& naps) {
-  if (d->ra_cap == 0 || ld_rlx32(&d->files[file].advice) == GFS_ADV_RANDOM)
-    return miss_one_page_wave(d, file, p, key, fsize, bs, bid, t0, naps);
+                                                          uint32_t bid, uint64_t t0) {
+  d = uniform(d);
+  if (H(d)->ra_cap == 0 || ld_rlx32(&H(d)->files[file].advice) == GFS_ADV_RANDOM)
+    return miss_one_page_wave(d, file, p, key, fsize, bs, bid, t0);
   const uint32_t l = lane();
   /* the pages of the read that missed, from p on */
   const uint64_t rl = bs->read_last;
@@ -1531,19 +1548,26 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   const RaParams rp = ra_params(d);
   /* what the critical section needs from the device and file records, read now: after the
      grant's acquire, each would be a load from memory on the path every waiter waits on */
-  gfs_file_dev* const fe = &d->files[file];
-  uint64_t* const clp = d->claims[file].e;
-  uint64_t* const lq = d->lockq + (uint64_t)file * GFS_LOCK_SLOTS;
-  uint64_t* const pt = d->pt;
-  const uint32_t ptmask = d->nbuckets_mask;
+  gfs_file_dev* const fe = &H(d)->files[file];
+  uint64_t* const clp = H(d)->claims[file].e;
+  uint64_t* const lq = H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS;
   const uint64_t npages = fe->npages;
-  const bool tracing = d->trace_level >= 1;
-  const bool async_on = d->ra_async != 0;
+  /* the table entry this lane looks at (lanes 32-63 repeat) */
+  uint64_t* pslot;
+  {
+    uint32_t b1, b2;
+    key_buckets_m(H(d)->nbuckets_mask, key, b1, b2);
+    pslot = H(d)->pt + (uint64_t)((l & GFS_BUCKET_SLOTS) ? b2 : b1) * GFS_BUCKET_SLOTS + (l & 15);
+    asm volatile("" : "+v"(pslot));   /* computed here, not with the lock held */
+  }
+  const bool tracing = H(d)->trace_level >= 1;
+  const bool async_on = H(d)->ra_async != 0;
   const uint64_t tl0 = wall_clock64();
-  uint64_t ticket;
-  const int lk = lock_file_wave(d, file, key, p, t0, ticket);
+  const uint64_t lr = lock_file_wave(d, file, key, p, t0);
+  const int lk = (int)(lr & 3);
+  const uint64_t ticket = lr >> 2;
   const uint64_t tl1 = wall_clock64();
-  if (l == 0) bcount(bs, GFS_T_LOCK, tl1 - tl0);
+  if (lk != LOCK_OWN && l == 0) bcount(bs, GFS_T_LOCK, tl1 - tl0);
   if (lk == LOCK_TIMEOUT) return 2;
   if (lk == LOCK_LEFT) {
     if (l == 0) bcount(bs, GFS_C_LOCK_LEFT, 1);
@@ -1556,7 +1580,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     uint32_t nw = 0;
     while (pt_lookup_wave(d, key) < 0 && !expired(d, t0)) {
       uint64_t cl = 0;
-      if (l < GFS_CLAIMS) cl = ld_rlx(&d->claims[file].e[l]);
+      if (l < GFS_CLAIMS) cl = ld_rlx(&H(d)->claims[file].e[l]);
       const uint64_t c_lo = cl >> 32, c_hi = (cl >> 32) + ((cl & 0xffffffffull) >> 1);
       if (__ballot(l < GFS_CLAIMS && (cl & 1ull) && c_lo <= p && p < c_hi) == 0) break;
       if (l == 0) nap_short(nw);
@@ -1564,33 +1588,37 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     acquire_agent();   /* the reservations, published before the claim was cleared */
     return 1;
   }
-  if (l == 0) bcount(bs, GFS_C_LOCKS, 1);
-  /* every block waiting on this file's lock waits for this wave: let it issue first */
+  /* every block waiting on this file's lock waits for this wave: let it issue first, and keep
+     the statistics until the lock is passed on */
   __builtin_amdgcn_s_setprio(3);
   /* one round: the detector state and the file's window claims; then, ordered after the
      claims, the table probe (a claim cleared after its reservations means they show) */
-  const RaState ras = ra_load_lane(fe, rp.nrec, rp.nstreams);
-  uint64_t cl = 0;
-  if (l < GFS_CLAIMS) cl = ld_rlx(&clp[l]);
+  RaState ras = ra_load_lane(fe, rp.nrec, rp.nstreams);
+  uint64_t cl = ld_rlx(&clp[l & (GFS_CLAIMS - 1)]);
   /* the queue slots behind this ticket, read now for the hand-off: a waiter that arrives or
      leaves after this read is handled by the grant's exchange (it returns what the slot
      holds), and a stale "waiting" value only makes the covered mark's compare-and-swap fail */
-  const uint64_t qv = ld_rlx(lq + ((ticket + 1 + l) & (GFS_LOCK_SLOTS - 1)));
+  uint64_t qv = ld_rlx(lq + ((ticket + 1 + l) & (GFS_LOCK_SLOTS - 1)));
   drain_atomics();   /* the table probe below goes out after the claims were read */
+  ra_loaded(ras, cl, qv);
   const bool cl_on = l < GFS_CLAIMS && (cl & 1ull);
   const uint64_t cl_lo = cl >> 32, cl_hi = (cl >> 32) + ((cl & 0xffffffffull) >> 1);
   const bool covered = __ballot(cl_on && cl_lo <= p && p < cl_hi) != 0;
   const uint64_t free_cl = __ballot(l < GFS_CLAIMS && !cl_on);
-  const bool present = pt_lookup_at(pt, ptmask, key) >= 0;
+  const bool present = __ballot(l < 2 * GFS_BUCKET_SLOTS && (ld_rlx(pslot) >> GFS_ENTRY_FRAME_BITS) == key) != 0;
   if (present || covered || free_cl == 0) {
     /* filled, reserved, or about to be reserved by a window being claimed: go to the pin
        path (after a nap if the claim is still running) */
     unlock_slots_wave(lq, ticket, 0, 0, false, 0);
     __builtin_amdgcn_s_setprio(0);
-    if (l == 0) bcount(bs, GFS_T_CRIT, wall_clock64() - tl1);
+    if (l == 0) {
+      bcount(bs, GFS_T_LOCK, tl1 - tl0);
+      bcount(bs, GFS_C_LOCKS, 1);
+      bcount(bs, GFS_T_CRIT, wall_clock64() - tl1);
+    }
     if (!present) {
       if (expired(d, t0)) return 2;
-      if (l == 0) nap(naps);
+      if (l == 0) nap(bs->naps);
     }
     return 1;
   }
@@ -1601,7 +1629,6 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   const uint64_t td0 = wall_clock64();
   ra_decide_wave(fe, p, req, hist_pre, rp, ras, ws, wn, near, hist, rule, rslot);
   const uint64_t td1 = wall_clock64();
-  if (l == 0) bcount(bs, GFS_T_DECIDE, td1 - td0);
   if (ws + wn > npages) wn = (uint32_t)(npages - ws);
   /* asynchronous readahead: the page after the demanded one is the stream's marker */
   uint64_t mark = ~0ull;
@@ -1632,6 +1659,9 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   __builtin_amdgcn_s_setprio(0);
   const uint64_t tl2 = wall_clock64();
   if (l == 0) {
+    bcount(bs, GFS_T_LOCK, tl1 - tl0);
+    bcount(bs, GFS_C_LOCKS, 1);
+    bcount(bs, GFS_T_DECIDE, td1 - td0);
     bcount(bs, GFS_T_CRIT, tl2 - tl1);
     bcount(bs, GFS_T_UNLOCK, tl2 - tu0);
   }
@@ -1651,7 +1681,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
       const bool valid = (uint64_t)l < base - cws;
       bool stop = !valid;
       if (valid)
-        stop = pt_present_lane(d, page_key(file, base - 1 - l)) | (clip && shadow_lane(d, file, base - 1 - l));
+        stop = (int)pt_present_lane(d, page_key(file, base - 1 - l)) | (int)(clip && shadow_lane(d, file, base - 1 - l));
       const uint64_t sm = __ballot(stop);
       const uint32_t k = sm ? (uint32_t)__builtin_ctzll(sm) : 64u;
       a = base - k;
@@ -1662,7 +1692,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     for (uint64_t base = p + 1; base < cwe;) {
       const bool valid = (uint64_t)l < cwe - base;
       bool stop = !valid;
-      if (valid) stop = pt_present_lane(d, page_key(file, base + l)) | (clip && shadow_lane(d, file, base + l));
+      if (valid) stop = (int)pt_present_lane(d, page_key(file, base + l)) | (int)(clip && shadow_lane(d, file, base + l));
       const uint64_t sm = __ballot(stop);
       const uint32_t k = sm ? (uint32_t)__builtin_ctzll(sm) : 64u;
       b = base + k - 1;
@@ -1708,7 +1738,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   /* release reservations that got no frame (the table was full or no frame was free) */
   for (uint32_t i = got + l; i < n; i += 64) {
     if (bs->lslot[i] != 0xffffffffu)
-      st_rel(d->pt + bs->lslot[i], 0ull);
+      st_rel(H(d)->pt + bs->lslot[i], 0ull);
   }
   if (got == 0) {
     if (l == 0) bcount(bs, keep ? GFS_C_NOFRAME : GFS_C_RETRIES, 1);
@@ -1722,7 +1752,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
       return 0;
     }
     if (expired(d, t0)) return 2;
-    if (l == 0) nap(naps);
+    if (l == 0) nap(bs->naps);
     return 1;   /* buckets full of reservations in flight, or every frame pinned or
                    filling: back off and retry the access */
   }
@@ -1733,37 +1763,26 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
 
 /* ------------------------------------------------------------------ one page, wave 0
  * Leaves in bs: status; on success the pinned frame, and pull = 1 when this block posted
- * the request and must pull it. */
-__device__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint64_t fsize,
-                                  BlockState* bs, uint32_t bid) {
+ * the request and must pull it. absent: the caller's group pass has just found no table
+ * entry for the page, so the first look is taken as made (the miss path looks again). */
+__device__ __forceinline__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, uint64_t fsize,
+                                  BlockState* bs, uint32_t bid, bool absent) {
+  d = uniform(d);
   const uint64_t key = page_key(file, p);
   const uint32_t l = lane();
-  uint64_t t0 = 0;   /* the wait deadline's start: read at the first step that may wait */
-  uint32_t naps = 0;
-  /* untraced runs check a hit's tag with its copy (frame_pin_fast) */
-  const bool fast = d->trace_level == 0;
+  const uint64_t t0 = wall_clock64();   /* the wait deadline's start */
   if (l == 0) {
-    bs->tagkey = 0;
     bs->trig = 0;
+    bs->naps = 0;
   }
   while (true) {
-    int32_t f = pt_lookup_wave(d, key);
+    const int32_t f = absent ? -1 : pt_lookup_wave(d, key);
+    absent = false;
     if (f >= 0 && (uint32_t)f != kReserved) {
       int r = PIN_RETRY;
       uint64_t w = 0;
-      if (l == 0) r = fast ? frame_pin_fast(d, (uint32_t)f, key, w) : frame_pin(d, (uint32_t)f, key, &w);
+      if (l == 0) r = frame_pin(d, (uint32_t)f, key, &w);
       r = __shfl(r, 0, 64);
-      if (r == PIN_VALID_UNCHECKED) {
-        if (l == 0) {
-          bs->frame = f;
-          bs->status = 0;
-          bs->pull = 0;
-          bs->tagkey = key;
-          bs->pinw = w;
-        }
-        return;
-      }
-      if (t0 == 0) t0 = wall_clock64();
       if (r == PIN_VALID) {
         if (l == 0) {
           bcount(bs, GFS_C_HITS, 1);
@@ -1771,7 +1790,7 @@ __device__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
           bs->frame = f;
           bs->status = 0;
           bs->pull = 0;
-          if (d->ra_async && (w & GFS_FW_MARK)) bs->trig = mark_take_lane(d, (uint32_t)f) ? 1u : 0u;
+          if (H(d)->ra_async && (w & GFS_FW_MARK)) bs->trig = mark_take_lane(d, (uint32_t)f) ? 1u : 0u;
         }
         return;
       }
@@ -1779,7 +1798,7 @@ __device__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
         if (l == 0) {
           bcount(bs, GFS_C_JOINS, 1);
           trace_ev(d, 2, GFS_EV_JOIN, bid, file, (uint32_t)p, (uint32_t)f, 0, 0);
-          if (d->ra_async && (w & GFS_FW_MARK)) bs->trig = mark_take_lane(d, (uint32_t)f) ? 1u : 0u;
+          if (H(d)->ra_async && (w & GFS_FW_MARK)) bs->trig = mark_take_lane(d, (uint32_t)f) ? 1u : 0u;
           const uint64_t tj0 = wall_clock64();
           join_or_help_lane(d, (uint32_t)f, p, t0, bs);
           bcount(bs, GFS_T_JOIN, wall_clock64() - tj0);
@@ -1796,11 +1815,10 @@ __device__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
       }
       if (l == 0) bcount(bs, GFS_C_RETRIES, 1);
     }
-    if (t0 == 0) t0 = wall_clock64();
     if (f >= 0 && (uint32_t)f != kReserved) {
       /* the pin lost a race (the frame changed under it): wait a little and look again */
-    } else if (f < 0 && d->policy == GFS_POLICY_PRIVATE) {
-      const int r = miss_private_wave(d, file, p, key, fsize, bs, bid, t0, naps);
+    } else if (f < 0 && H(d)->policy == GFS_POLICY_PRIVATE) {
+      const int r = miss_private_wave(d, file, p, key, fsize, bs, bid, t0);
       if (r == 0) return;
       if (r == 2) break;
       continue;
@@ -1815,14 +1833,14 @@ __device__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
       }
       return;
     } else if (f < 0) {
-      const int r = miss_shared_wave(d, file, p, key, fsize, bs, bid, t0, naps);
+      const int r = miss_shared_wave(d, file, p, key, fsize, bs, bid, t0);
       if (r == 0) return;
       if (r == 2) break;
       continue;
     }
     /* reserved by another block's miss, or a lost race: wait a little and look again */
     if (expired(d, t0)) break;
-    if (l == 0) nap(naps);
+    if (l == 0) nap(bs->naps);
   }
   if (l == 0) {
     bcount(bs, GFS_C_TIMEOUTS, 1);
@@ -1836,18 +1854,18 @@ __device__ void acquire_page_wave(const gfs_dev* d, uint32_t file, uint64_t p, u
  * what the host returned and to the file). */
 __device__ __forceinline__ uint64_t staged_bytes(const gfs_dev* d, uint64_t q, uint64_t first,
                                                  int64_t result, uint64_t fsize) {
-  const uint64_t P = d->page_size;
+  const uint64_t P = H(d)->page_size;
   const uint64_t rel = (q - first) * P;
   int64_t avail = result - (int64_t)rel;
   if (avail < 0) avail = 0;
-  uint64_t pb = fsize - (q << d->page_shift);
+  uint64_t pb = fsize - (q << H(d)->page_shift);
   if (pb > P) pb = P;
   return (uint64_t)avail < pb ? (uint64_t)avail : pb;
 }
 __device__ __forceinline__ bool staged_short(const gfs_dev* d, uint64_t q, uint64_t first,
                                              int64_t result, uint64_t fsize) {
-  const uint64_t P = d->page_size;
-  uint64_t pb = fsize - (q << d->page_shift);
+  const uint64_t P = H(d)->page_size;
+  uint64_t pb = fsize - (q << H(d)->page_shift);
   if (pb > P) pb = P;
   return result < 0 || (uint64_t)result < (q - first) * P + pb;
 }
@@ -1858,7 +1876,8 @@ __device__ __forceinline__ bool staged_short(const gfs_dev* d, uint64_t q, uint6
  * another request, which the caller must not touch. The word is read first (acquire) and the
  * fill word after it, and the claim is a compare-and-swap against that word, so a frame that
  * changed hands in between is not claimed. */
-__device__ void claim_pulls_wave(const gfs_dev* d, BlockState* bs, uint64_t fill) {
+__device__ __attribute__((noinline)) void claim_pulls_wave(const gfs_dev* d, BlockState* bs, uint64_t fill) {
+  d = uniform(d);
   const uint32_t l = lane();
   uint32_t nclaim = 0;
   for (uint32_t base = 0; base < bs->list_n; base += 64) {
@@ -1866,9 +1885,9 @@ __device__ void claim_pulls_wave(const gfs_dev* d, BlockState* bs, uint64_t fill
     bool won = false;
     if (k < bs->list_n) {
       const uint32_t f = bs->lframe[k];
-      uint64_t* fw = &d->fword[f];
+      uint64_t* fw = &H(d)->fword[f];
       uint64_t w = ld_acq(fw);
-      while ((w & GFS_FW_STATE) == GFS_FS_FILLING && !(w & GFS_FW_PULL) && ld_rlx(&d->ffill[f]) == fill) {
+      while ((w & GFS_FW_STATE) == GFS_FS_FILLING && !(w & GFS_FW_PULL) && ld_rlx(&H(d)->ffill[f]) == fill) {
         if (cas64(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
           won = true;
           break;
@@ -1887,25 +1906,25 @@ __device__ void claim_pulls_wave(const gfs_dev* d, BlockState* bs, uint64_t fill
  * pull == 1: the frames listed in lslot[0..nclaim); pull == 2: the one helped frame. */
 __device__ void block_pull(const gfs_dev* d, const BlockState* bs, uint64_t fsize) {
   const uint32_t tid = thread_id(), nt = block_threads();
-  const uint64_t P = d->page_size;
-  const uint8_t* stg = d->staging + (uint64_t)bs->slot * d->max_req_bytes;
+  const uint64_t P = H(d)->page_size;
+  const uint8_t* stg = H(d)->staging + (uint64_t)bs->slot * H(d)->max_req_bytes;
   if (bs->pull == 2) {
     const uint64_t q = bs->help_page;
-    copy_block_aligned(d->frames + (uint64_t)(uint32_t)bs->frame * P, stg + (q - bs->first_page) * P,
+    copy_block_aligned(H(d)->frames + (uint64_t)(uint32_t)bs->frame * P, stg + (q - bs->first_page) * P,
                        staged_bytes(d, q, bs->first_page, bs->result, fsize), tid, nt);
     return;
   }
   for (uint32_t c = 0; c < bs->nclaim; ++c) {
     const uint32_t k = bs->lslot[c];
     const uint64_t q = bs->list[k];
-    copy_block_aligned(d->frames + (uint64_t)bs->lframe[k] * P, stg + (q - bs->first_page) * P,
+    copy_block_aligned(H(d)->frames + (uint64_t)bs->lframe[k] * P, stg + (q - bs->first_page) * P,
                        staged_bytes(d, q, bs->first_page, bs->result, fsize), tid, nt);
   }
 }
 
 /* Lane: publish a pulled frame VALID (reference bit set, ERR if the host read came short). */
 __device__ __forceinline__ void publish_frame(const gfs_dev* d, uint32_t f, bool short_read) {
-  uint64_t* fw = &d->fword[f];
+  uint64_t* fw = &H(d)->fword[f];
   uint64_t w = ld_rlx(fw);
   while (true) {
     uint64_t nw = ((w & ~(GFS_FW_STATE | GFS_FW_PULL)) | GFS_FS_VALID | GFS_FW_REF) + GFS_FW_VER_ONE;
@@ -1919,11 +1938,11 @@ __device__ __forceinline__ void publish_frame(const gfs_dev* d, uint32_t f, bool
 __device__ __forceinline__ void request_done_lane(const gfs_dev* d, uint32_t s, uint64_t gen,
                                                   uint32_t cnt) {
   if (cnt == 0) return;
-  const uint32_t before = __hip_atomic_fetch_sub(&d->reqd[s].remaining, cnt, __ATOMIC_ACQ_REL,
+  const uint32_t before = __hip_atomic_fetch_sub(G(&H(d)->reqd[s].remaining), cnt, __ATOMIC_ACQ_REL,
                                                  __HIP_MEMORY_SCOPE_AGENT);
   if (before == cnt) {
-    st_rel(&d->slot_free[s], gen);
-    if (s >= d->sync_slots) st_rel(&d->reqd[s].busy, 0ull);   /* an asynchronous window's slot */
+    st_rel(&H(d)->slot_free[s], gen);
+    if (s >= H(d)->sync_slots) st_rel(&H(d)->reqd[s].busy, 0ull);   /* an asynchronous window's slot */
   }
 }
 
@@ -1931,8 +1950,9 @@ __device__ __forceinline__ void request_done_lane(const gfs_dev* d, uint32_t s, 
  * this block pulled and count them off. Returns the status of this block's page: for its
  * own request the demanded page (list[0]), which a helper may be pulling, so it may wait.
  * On an error the block's pin on its page has been dropped. */
-__device__ int64_t publish_pull_wave(const gfs_dev* d, BlockState* bs, uint64_t fsize,
+__device__ __attribute__((noinline)) int64_t publish_pull_wave(const gfs_dev* d, BlockState* bs, uint64_t fsize,
                                      uint64_t t0) {
+  d = uniform(d);
   const uint32_t l = lane();
   uint32_t bad = 0;
   int64_t st = 0;
@@ -1974,19 +1994,19 @@ __device__ int64_t publish_pull_wave(const gfs_dev* d, BlockState* bs, uint64_t 
  * rest of the span into the private buffer. */
 __device__ void private_pull(const gfs_dev* d, const BlockState* bs, uint64_t fsize) {
   const uint32_t tid = thread_id(), nt = block_threads();
-  const uint64_t P = d->page_size;
+  const uint64_t P = H(d)->page_size;
   const uint32_t f = (uint32_t)bs->frame;
-  const gfs_pslot* ps = &d->pslots[bs->pslot];
-  uint8_t* pb = d->pbuf + (uint64_t)bs->pslot * d->ra_cap * P;
+  const gfs_pslot* ps = &H(d)->pslots[bs->pslot];
+  uint8_t* pb = H(d)->pbuf + (uint64_t)bs->pslot * H(d)->ra_cap * P;
   if (bs->pull == 3) {
     const uint64_t q = bs->help_page;
-    uint64_t n = fsize - (q << d->page_shift);
+    uint64_t n = fsize - (q << H(d)->page_shift);
     if (n > P) n = P;
-    copy_block_aligned(d->frames + (uint64_t)f * P, pb + (q - ps->first) * P, n, tid, nt);
+    copy_block_aligned(H(d)->frames + (uint64_t)f * P, pb + (q - ps->first) * P, n, tid, nt);
     return;
   }
-  const uint8_t* stg = d->staging + (uint64_t)bs->slot * d->max_req_bytes;
-  copy_block_aligned(d->frames + (uint64_t)f * P, stg,
+  const uint8_t* stg = H(d)->staging + (uint64_t)bs->slot * H(d)->max_req_bytes;
+  copy_block_aligned(H(d)->frames + (uint64_t)f * P, stg,
                      staged_bytes(d, bs->first_page, bs->first_page, bs->result, fsize), tid, nt);
   const int64_t rest = bs->result - (int64_t)P;
   if (rest > 0) copy_block_aligned(pb, stg + P, (uint64_t)rest, tid, nt);
@@ -1996,19 +2016,19 @@ __device__ void private_pull(const gfs_dev* d, const BlockState* bs, uint64_t fs
  * free its ring slot and make the rest of the span the private buffer (only whole pages
  * unless the read stopped at the end of the file). 0 or -EIO (the pin is then dropped). */
 __device__ int64_t private_publish_lane(const gfs_dev* d, BlockState* bs, uint64_t fsize) {
-  gfs_pslot* ps = &d->pslots[bs->pslot];
+  gfs_pslot* ps = &H(d)->pslots[bs->pslot];
   const uint32_t f = (uint32_t)bs->frame;
   if (bs->pull == 3) {
     publish_frame(d, f, false);
     ps->used += 1;
     return 0;
   }
-  const uint64_t P = d->page_size;
+  const uint64_t P = H(d)->page_size;
   const bool short_page = staged_short(d, bs->first_page, bs->first_page, bs->result, fsize);
   publish_frame(d, f, short_page);
   if (short_page) bcount(bs, GFS_C_IOERR, 1);
-  st_rel(&d->slot_free[bs->slot], bs->gen);
-  const uint64_t off0 = bs->first_page << d->page_shift;
+  st_rel(&H(d)->slot_free[bs->slot], bs->gen);
+  const uint64_t off0 = bs->first_page << H(d)->page_shift;
   uint64_t expect = (uint64_t)bs->list_n * P;
   if (expect > fsize - off0) expect = fsize - off0;
   const int64_t rest = bs->result - (int64_t)P;
@@ -2075,7 +2095,7 @@ __device__ uint32_t reserve_from_wave(const gfs_dev* d, uint32_t file, uint64_t 
       if (pick >= 0) {
         uint64_t expect = 0;
         uint64_t* sp = slot_ptr(d, b1, b2, pick);
-        if (cas64_rlx(sp, expect, (key << GFS_ENTRY_FRAME_BITS) | kReserved)) slot = (int64_t)(sp - d->pt);
+        if (cas64_rlx(sp, expect, (key << GFS_ENTRY_FRAME_BITS) | kReserved)) slot = (int64_t)(sp - H(d)->pt);
         else slot = pt_reserve_lane(d, key);
       }
       bs->list[base + l] = (uint32_t)q;
@@ -2097,6 +2117,7 @@ __device__ uint32_t reserve_from_wave(const gfs_dev* d, uint32_t file, uint64_t 
    the window is empty, a running claim holds its first page, or no frame is free. */
 __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uint32_t file, uint64_t m, uint64_t fsize, BlockState* bs,
                                  uint32_t bid, uint64_t t0) {
+  d = uniform(d);
   const uint32_t l = lane();
   /* a slot of its own first: with none free the window is not issued (readers then miss at
      its first page and the stream goes on synchronously) */
@@ -2105,26 +2126,26 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   aslot = __shfl(aslot, 0, 64);
   if (aslot < 0) return;
   const uint32_t s = (uint32_t)aslot;
-  uint64_t ticket;
   /* the waiter announces no page of any window, so no holder marks it covered */
-  const int lk = lock_file_wave(d, file, 0, 0x7fffffffull, t0, ticket, false);
-  if (lk != LOCK_OWN) {
-    if (l == 0) st_rel(&d->reqd[s].busy, 0ull);
+  const uint64_t lk = lock_file_wave(d, file, 0, 0x7fffffffull, t0, false);
+  const uint64_t ticket = lk >> 2;
+  if ((lk & 3) != LOCK_OWN) {
+    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   __builtin_amdgcn_s_setprio(3);
-  const RaState ras = ra_load_lane(&d->files[file], d->ra_recent, d->streams);
+  const RaState ras = ra_load_lane(&H(d)->files[file], H(d)->ra_recent, H(d)->streams);
   uint64_t cl = 0;
-  if (l < GFS_CLAIMS) cl = ld_rlx(&d->claims[file].e[l]);
-  const uint64_t npages = d->files[file].npages;
+  if (l < GFS_CLAIMS) cl = ld_rlx(&H(d)->claims[file].e[l]);
+  const uint64_t npages = H(d)->files[file].npages;
   /* the window leaves out pages evicted after use, unless the marker page is one */
   const bool clip = !shadow_lane(d, file, m);
   drain_atomics();
-  const uint64_t sm = __ballot(l < d->streams && ras.s_valid && ras.s_marker == (uint32_t)m);
+  const uint64_t sm = __ballot(l < H(d)->streams && ras.s_valid && ras.s_marker == (uint32_t)m);
   if (sm == 0) {
     unlock_file_wave(d, file, ticket, 0, 0);
     __builtin_amdgcn_s_setprio(0);
-    if (l == 0) st_rel(&d->reqd[s].busy, 0ull);
+    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   const int j = __ffsll((unsigned long long)sm) - 1;
@@ -2133,7 +2154,7 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   const uint32_t sz = __shfl(ras.s_size, j, 64);
   const uint32_t cap = ra_cap_eff(d);
   const uint32_t wn = 2 * sz < cap ? 2 * sz : cap;
-  gfs_file_dev* fe = &d->files[file];
+  gfs_file_dev* fe = &H(d)->files[file];
   if (l == 0) {
     gfs_stream* st = &fe->streams[j];
     st_rlx(&st->next, ws + wn);
@@ -2161,11 +2182,11 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   if (wnc == 0 || held || free_cl == 0 || cwe <= ws) {
     unlock_file_wave(d, file, ticket, 0, 0);
     __builtin_amdgcn_s_setprio(0);
-    if (l == 0) st_rel(&d->reqd[s].busy, 0ull);
+    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   const uint32_t cj = (uint32_t)__builtin_ctzll(free_cl);
-  uint64_t* claim = &d->claims[file].e[cj];
+  uint64_t* claim = &H(d)->claims[file].e[cj];
   if (l == 0) st_rlx(claim, (ws << 32) | ((cwe - ws) << 1) | 1ull);
   unlock_file_wave(d, file, ticket, ws, cwe);
   __builtin_amdgcn_s_setprio(0);
@@ -2188,33 +2209,33 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   /* no demanded page: every page is prefetched; the window's first page is the new marker */
   const uint32_t got = keep ? alloc_wave(d, file, ~0ull, bs, keep, bid, ws) : 0;
   for (uint32_t i = got + l; i < n; i += 64)
-    if (bs->lslot[i] != 0xffffffffu) st_rel(d->pt + bs->lslot[i], 0ull);
+    if (bs->lslot[i] != 0xffffffffu) st_rel(H(d)->pt + bs->lslot[i], 0ull);
   if (got == 0) {
-    if (l == 0) st_rel(&d->reqd[s].busy, 0ull);
+    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   if (got < n && l == 0) trace_ev(d, 1, GFS_EV_NOFRAME, bid, file, bs->list[got], GFS_NO_FRAME, 0, 0);
   /* the pages that got frames are [ws, ws + got) */
-  const uint64_t off0 = ws << d->page_shift;
-  uint64_t len = (uint64_t)got << d->page_shift;
+  const uint64_t off0 = ws << H(d)->page_shift;
+  uint64_t len = (uint64_t)got << H(d)->page_shift;
   if (off0 + len > fsize) len = fsize - off0;
   /* the slot is this window's alone: its staging is free once its last request was counted
      off (that cleared busy), and its next generation is one past the last completed */
   acquire_agent();
-  const uint64_t gen = ld_rlx(&d->slot_free[s]) + 1;
-  const uint64_t tk = (gen - 1) * d->rpc_slots + s;   /* for the trace only */
+  const uint64_t gen = ld_rlx(&H(d)->slot_free[s]) + 1;
+  const uint64_t tk = (gen - 1) * H(d)->rpc_slots + s;   /* for the trace only */
   if (l == 0)   /* frames count themselves off the request as they are published */
-    __hip_atomic_store(&d->reqd[s].remaining, got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(G(&H(d)->reqd[s].remaining), got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t fill = (1ull << 63) | ((uint64_t)(s + 1) << 40) | (gen & ((1ull << 40) - 1));
-  for (uint32_t k = l; k < got; k += 64) st_rel(&d->ffill[bs->lframe[k]], fill);
+  for (uint32_t k = l; k < got; k += 64) st_rel(&H(d)->ffill[bs->lframe[k]], fill);
   if (l == 0) {
-    gfs_rpc_slot* rs = &d->ring[s];
+    gfs_rpc_slot* rs = &H(d)->ring[s];
     rs->file_id = file;
     rs->npages = got;
     rs->offset = off0;
     rs->length = len;
     rs->ticket = tk;
-    __hip_atomic_store(&rs->req_seq, gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(G(&rs->req_seq), gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)ws, GFS_NO_FRAME, got, tk);
     bcount(bs, GFS_C_REQUESTS, 1);
     bcount(bs, GFS_C_REQ_BYTES, len);
@@ -2232,12 +2253,13 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
 /* Block-collective: finish the block's outstanding asynchronous request, if any: wait for the
    host, pull every frame no other block has claimed, publish them. 0 or -ETIMEDOUT. */
 __device__ __attribute__((noinline)) int64_t async_finish_block(const gfs_dev* d, BlockState* bs) {
+  d = uniform(d);
   const uint32_t tid = thread_id();
   __syncthreads();
   if (!bs->a_pending) return 0;
   const uint64_t t0 = wall_clock64();
   if (tid == 0) {
-    gfs_rpc_slot* rs = &d->ring[bs->a_slot];
+    gfs_rpc_slot* rs = &H(d)->ring[bs->a_slot];
     uint32_t nn = 0;
     int st = 0;
     const uint64_t th0 = wall_clock64();
@@ -2245,7 +2267,7 @@ __device__ __attribute__((noinline)) int64_t async_finish_block(const gfs_dev* d
        blocks that joined its frames pulled and published every one of them, and the slot went
        to a later request (nothing is left to claim: no frame's fill word names this one) */
     uint64_t ds;
-    while ((int64_t)((ds = __hip_atomic_load(&rs->done_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) -
+    while ((int64_t)((ds = __hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) -
                      bs->a_gen) < 0) {
       if (expired(d, t0)) {
         st = -kETIMEDOUT;
@@ -2269,7 +2291,7 @@ __device__ __attribute__((noinline)) int64_t async_finish_block(const gfs_dev* d
   __syncthreads();
   int64_t st = bs->a_status;
   if (st == 0) {
-    const uint64_t fsize = d->files[bs->a_file].size;
+    const uint64_t fsize = H(d)->files[bs->a_file].size;
     if (tid < 64)
       claim_pulls_wave(d, bs, (1ull << 63) | ((uint64_t)(bs->a_slot + 1) << 40) | (bs->a_gen & ((1ull << 40) - 1)));
     __syncthreads();
@@ -2287,228 +2309,212 @@ __device__ __attribute__((noinline)) int64_t async_finish_block(const gfs_dev* d
   return st < 0 ? st : 0;
 }
 
-}  // namespace gfsd
-
-/* ====================================================================== public API */
-
-__device__ int gopen_id(const gfs_dev* d, int file_id, int flags) {
-  gfsd::BlockState* bs = gfsd::block_state();
-  if (gfsd::thread_id() == 0) {
-    int v;
-    if (flags != GFS_O_RDONLY) {
-      v = -gfsd::kEROFS;
-    } else if (file_id < 0 || (uint32_t)file_id >= d->max_files ||
-               gfsd::ld_rlx32(&d->files[file_id].open) == 0) {
-      v = -gfsd::kENOENT;
-    } else {
-      __hip_atomic_fetch_add(&d->files[file_id].handles, 1u, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-      v = file_id;
-    }
-    bs->pslot = -1;
-    if (v >= 0 && d->policy == GFS_POLICY_PRIVATE) {
-      /* the block's private slot: its own frames and private buffer until gclose. A slot
-         given back by a block that just ended may not show yet: look again, with naps,
-         until the wait timeout */
-      const uint64_t t0 = wall_clock64();
-      uint32_t naps = 0;
-      while (bs->pslot < 0) {
-        for (uint32_t i = 0; i < d->npslots && bs->pslot < 0; ++i) {
-          const uint32_t s = (gfsd::block_id() + i) % d->npslots;
-          uint32_t z = 0;
-          if (gfsd::ld_rlx32(&d->pslots[s].owner) == 0 && gfsd::cas32(&d->pslots[s].owner, z, 1u))
-            bs->pslot = (int32_t)s;
-        }
-        if (bs->pslot >= 0 || gfsd::expired(d, t0)) break;
-        gfsd::nap(naps);
-      }
-      if (bs->pslot < 0) {
-        __hip_atomic_fetch_sub(&d->files[file_id].handles, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        v = -gfsd::kENOSPC;
-      } else {
-        gfs_pslot* ps = &d->pslots[bs->pslot];
-        ps->n = 0;   /* a new owner starts with an empty private buffer */
-        ps->used = 0;
-      }
-    }
-    for (int c = 0; c < GFS_C_COUNT; ++c) bs->ctr[c] = 0;
-    bs->pull = 0;
-    bs->trig = 0;
-    bs->a_pending = 0;   /* an asynchronous request is finished by gclose, before the next gopen */
-    bs->open_result = v;
-    bs->open_fd = v;
-    bs->open_size = v >= 0 ? d->files[v].size : 0;
-  }
-  __syncthreads();
-  const int v = bs->open_result;
-  __syncthreads();
-  return v;
+/* ------------------------------------------------------------------ the group pass
+ * A read's pages are taken 64 at a time. Those the cache holds are looked up and pinned
+ * together, copied by the whole block and unpinned together: two dependent round trips
+ * (table, pin) a group instead of two a page. The others go through gread_page, in order.
+ * Not used while the policy trace is recorded: a traced run makes its accesses one at a time
+ * in page order.
+ *
+ * Every wave of the block looks up its share. Half a wave takes a page: its 32 lanes load the
+ * page's two buckets, two 128-byte lines, where one lane a page would load 32 scattered
+ * entries (32 pages of 4 KiB: 2048 separate fetches). Lane j of wave w then owns page
+ * group_page(j, w, W): it pins the frame, keeps the frame's tag in flight beside the copy and
+ * compares it before the unpin. */
+__device__ __forceinline__ uint32_t group_page(uint32_t j, uint32_t w, uint32_t W) {
+  return (((j >> 1) * W + w) << 1) + (j & 1u);
 }
 
-__device__ int gopen(const gfs_dev* d, const char* path, int flags) {
-  gfsd::BlockState* bs = gfsd::block_state();
-  if (gfsd::thread_id() == 0) {
-    int id = -1;
-    for (uint32_t i = 0; i < d->max_files && id < 0; ++i) {
-      if (gfsd::ld_rlx32(&d->files[i].open) == 0) continue;
-      const char* nm = d->names + (uint64_t)i * GFS_NAME_MAX;
-      uint32_t j = 0;
-      while (j < GFS_NAME_MAX && nm[j] == path[j] && nm[j] != 0) ++j;
-      if (j < GFS_NAME_MAX && nm[j] == 0 && path[j] == 0) id = (int)i;
-    }
-    bs->open_result = id;
-  }
-  __syncthreads();
-  const int id = bs->open_result;
-  __syncthreads();
-  if (flags != GFS_O_RDONLY) return -gfsd::kEROFS;
-  if (id < 0) return -gfsd::kENOENT;
-  return gopen_id(d, id, flags);
-}
-
-__device__ int gclose(const gfs_dev* d, int fd) {
-  if (fd < 0 || (uint32_t)fd >= d->max_files) return -gfsd::kEBADF;
-  gfsd::BlockState* bs = gfsd::block_state();
-  /* an asynchronous request still outstanding is pulled in before the block lets go */
-  (void)gfsd::async_finish_block(d, bs);
-  __syncthreads();
-  if (gfsd::thread_id() == 0) {
-    __hip_atomic_fetch_sub(&d->files[fd].handles, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (d->policy == GFS_POLICY_PRIVATE && bs->pslot >= 0) {
-      gfs_pslot* ps = &d->pslots[bs->pslot];
-      bs->ctr[GFS_C_PB_WASTED] += ps->n - ps->used;   /* the private buffer is dropped */
-      ps->n = 0;
-      ps->used = 0;
-      __hip_atomic_store(&ps->owner, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      bs->pslot = -1;
-    }
-    for (int c = 0; c < GFS_C_COUNT; ++c) {
-      if (bs->ctr[c]) gfsd::fadd64(&d->g->ctr[c], bs->ctr[c]);
-      bs->ctr[c] = 0;
-    }
-    bs->open_fd = -1;
-  }
-  __syncthreads();
-  return 0;
-}
-
-__device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd, uint64_t offset,
-                                                        uint64_t size, void* dst) {
-  using namespace gfsd;
-  BlockState* bs = block_state();
-  if (fd < 0 || (uint32_t)fd >= d->max_files) return -kEBADF;
-  uint64_t fsize;
-  if (fd == bs->open_fd) {
-    fsize = bs->open_size;   /* checked by gopen */
-  } else {
-    gfs_file_dev* fe = &d->files[fd];
-    if (ld_rlx32(&fe->open) == 0) return -kEBADF;
-    fsize = fe->size;
-  }
-  const uint32_t nt = block_threads();
-  if (nt & 63u) return -kEINVAL;
-  if (size == 0 || offset >= fsize) return 0;
-  const uint64_t end = (size > fsize - offset) ? fsize : offset + size;
-  const uint32_t tid = thread_id();
-  const uint32_t bid = block_id();
-  const uint64_t P = d->page_size;
-  const uint32_t sh_bits = d->page_shift;
-  const uint64_t pfirst = offset >> sh_bits, plast = (end - 1) >> sh_bits;
-  int64_t err = 0;
-  /* Reads of several pages first take every page that is cached and valid in one pass:
-     lane i of wave 0 looks up and pins page base + i, the block copies all of them, and
-     the pins are dropped together. The remaining pages (misses, frames being filled) go
-     through the one-page path below, in order. Off while the policy trace is recorded, so
-     that a traced run makes its accesses one at a time in page order. */
-  const bool batched = plast > pfirst && d->trace_level == 0;
-  if (batched) {
-    const uint32_t cnt = (uint32_t)((plast - pfirst + 1) < 64 ? (plast - pfirst + 1) : 64);
-    const uint64_t tb0 = d->page_timers ? wall_clock64() : 0;
-    if (tid < 64) {
-      int32_t f = -1;
-      if (tid < cnt) {
-        const uint64_t key = page_key((uint32_t)fd, pfirst + tid);
-        f = pt_find_lane(d, key);
-        if (f >= 0 && (uint32_t)f != kReserved) {
-          uint64_t w = 0;
-          const int r = frame_pin(d, (uint32_t)f, key, &w);
-          if (r != PIN_VALID || (d->ra_async && (w & GFS_FW_MARK))) {
-            /* the one-page path joins a filling frame, and takes a marker page's mark */
-            if (r == PIN_FILLING || r == PIN_VALID) frame_unpin(d, (uint32_t)f);
-            f = -1;
-          }
-        } else {
-          f = -1;
-        }
-      }
-      bs->bframe[tid] = f;
-      const uint64_t got = __ballot(f >= 0);
-      if (tid == 0) bcount(bs, GFS_C_HITS, (uint64_t)__popcll(got));
-    }
-    __syncthreads();
-    /* whole pages: one pass over all their 16-byte units, eight in flight per thread */
-    const bool aligned = ((((uintptr_t)dst) | offset) & 15) == 0;
-    const uint32_t ush = sh_bits - 4;
-    const uint64_t total = (uint64_t)cnt << ush;
-    if (aligned) {
-      for (uint64_t u0 = tid; u0 < total; u0 += 8ull * nt) {
-        v4u a[8];
-        bool ok[8];
+/* One wave: look up its pages of the group (base + i for the set bits i of todo below n), lane
+ * j returning page group_page(j)'s frame, kAbsent or kNotReady. Four pairs of pages are loaded
+ * before the first is waited for. */
+__device__ __forceinline__ int32_t group_lookup(const gfs_dev* d, uint32_t file, uint64_t base, uint32_t n,
+                                                uint64_t todo, uint32_t w, uint32_t W) {
+  const uint32_t l = lane();
+  uint64_t* const pt = H(d)->pt;
+  const uint32_t mask = H(d)->nbuckets_mask;
+  int32_t f = kAbsent;
+  for (uint32_t r0 = 0; group_page(2 * r0, w, W) < n; r0 += 4) {
+    uint64_t e[4], key[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint64_t u = u0 + (uint64_t)j * nt;
-          const uint32_t i = (uint32_t)(u >> ush);
-          const uint64_t pos = ((pfirst + i) << sh_bits) + ((u & ((1ull << ush) - 1)) << 4);
-          const int32_t f = u < total ? bs->bframe[i] : -1;
-          ok[j] = f >= 0 && pos >= offset && pos + 16 <= end;
-          if (ok[j]) a[j] = ((const gv4u*)(d->frames + (uint64_t)f * P))[u & ((1ull << ush) - 1)];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint64_t u = u0 + (uint64_t)j * nt;
-          const uint64_t pos = ((pfirst + (u >> ush)) << sh_bits) + ((u & ((1ull << ush) - 1)) << 4);
-          if (ok[j]) ((gv4u*)((uint8_t*)dst + (pos - offset)))[0] = a[j];
-        }
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = group_page(2 * (r0 + u) + (l >> 5), w, W);
+      e[u] = 0;
+      key[u] = page_key(file, base + i);
+      if (i < n && ((todo >> i) & 1)) {
+        uint32_t b1, b2;
+        key_buckets_m(mask, key[u], b1, b2);
+        e[u] = ld_rlx(pt + (uint64_t)((l & GFS_BUCKET_SLOTS) ? b2 : b1) * GFS_BUCKET_SLOTS + (l & 15));
       }
     }
-    /* bytes the unit pass left: unaligned buffers, and the ends of partly covered pages */
-    for (uint32_t i = 0; i < cnt; ++i) {
-      const int32_t f = bs->bframe[i];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint64_t m = __ballot((e[u] >> GFS_ENTRY_FRAME_BITS) == key[u]);   /* keys are never 0 */
+      const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+      const int fe = (int)((uint32_t)e[u] & (uint32_t)kFrameMask);
+      if (lo) {
+        const int g = __builtin_amdgcn_readlane(fe, (int)__builtin_ctz(lo));
+        if (l == 2 * (r0 + u)) f = g;
+      }
+      if (hi) {
+        const int g = __builtin_amdgcn_readlane(fe, 32 + (int)__builtin_ctz(hi));
+        if (l == 2 * (r0 + u) + 1) f = g;
+      }
+    }
+  }
+  return f == (int32_t)kReserved ? kNotReady : f;
+}
+
+/* The block copies the pinned pages of a group smaller than a round of the whole block each:
+ * all their 16-byte units in one sequence, eight loads a thread in flight. Units are aligned
+ * in dst; page bytes before its first and after its last unit go one byte a thread. */
+__device__ __forceinline__ void copy_group(const gfs_dev* d, const int32_t* frame, uint64_t base, uint32_t n,
+                                           uint64_t offset, uint64_t end, uint8_t* dst, uint32_t tid, uint32_t nt) {
+  const uint32_t sh = H(d)->page_shift, ush = sh - 4, P = 1u << sh;
+  const uint8_t* const frames = H(d)->frames;
+  /* dst address of the first page's start (maybe before dst), and the first dst-aligned
+     position in every page */
+  uint8_t* const d0 = dst + (int64_t)((base << sh) - offset);
+  const uint32_t h = (0u - (uint32_t)(uintptr_t)d0) & 15u;
+  const uint64_t pb = base << sh;
+  /* bytes wanted, relative to the group's first page */
+  const uint32_t lo = offset > pb ? (uint32_t)(offset - pb) : 0u;
+  const uint32_t hi = end - pb < ((uint64_t)n << sh) ? (uint32_t)(end - pb) : n << sh;
+  const uint32_t total = n << ush;
+  for (uint32_t u0 = tid; u0 < total; u0 += 8 * nt) {
+    v4u a[8];
+    uint32_t ok = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) {
+      const uint32_t u = u0 + j * nt;
+      const uint32_t i = u >> ush, at = ((u & ((1u << ush) - 1)) << 4) + h, pos = (i << sh) + at;
+      const int32_t f = u < total ? frame[i] : kAbsent;
+      if (f >= 0 && at + 16 <= P && pos >= lo && pos + 16 <= hi) {
+        ok |= 1u << j;
+        a[j] = __builtin_nontemporal_load((const gv4u_any*)(frames + ((uint64_t)(uint32_t)f << sh) + at));
+      }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) {
+      const uint32_t u = u0 + j * nt;
+      if ((ok >> j) & 1) *(gv4u*)(d0 + (((u >> ush) << sh) + ((u & ((1u << ush) - 1)) << 4) + h)) = a[j];
+    }
+  }
+  if ((h | lo | hi) & 15u) {
+    /* 32 threads a page: 16 for the bytes before its first unit, 16 for those after its last */
+    for (uint32_t i = tid >> 5; i < n; i += nt >> 5) {
+      const int32_t f = frame[i];
       if (f < 0) continue;
-      const uint64_t pbase = (pfirst + i) << sh_bits;
-      const uint64_t lo = offset > pbase ? offset : pbase;
-      const uint64_t hi = end < pbase + P ? end : pbase + P;
-      if (!aligned) {
-        copy_block((uint8_t*)dst + (lo - offset), d->frames + (uint64_t)f * P + (lo - pbase), hi - lo, tid, nt);
-      } else {
-        /* units cover [lo16, hi16): copy the head and tail bytes outside them */
-        const uint64_t lo16 = (lo + 15) & ~15ull, hi16 = hi & ~15ull;
-        for (uint64_t b = lo + tid; b < (lo16 < hi ? lo16 : hi); b += nt)
-          ((uint8_t*)dst)[b - offset] = d->frames[(uint64_t)f * P + (b - pbase)];
-        for (uint64_t b = (hi16 > lo16 ? hi16 : lo16) + tid; b < hi; b += nt)
-          ((uint8_t*)dst)[b - offset] = d->frames[(uint64_t)f * P + (b - pbase)];
+      const uint32_t p0 = i << sh;
+      const uint32_t plo = lo > p0 ? lo - p0 : 0u, phi = hi - p0 < P ? hi - p0 : P;
+      uint32_t a = plo <= h ? h : h + ((plo - h + 15u) & ~15u);
+      if (a > phi) a = phi;
+      const uint32_t b = a + ((phi - a) & ~15u);
+      const uint32_t k = tid & 15u;
+      const uint32_t at = (tid & 16u) ? b + k : plo + k;
+      if (at < ((tid & 16u) ? phi : a))
+        ((gu8*)d0)[p0 + at] = ((const gu8*)frames)[((uint64_t)(uint32_t)f << sh) + at];
+    }
+  }
+}
+
+/* Block-collective: deliver the cached, valid pages among base + i, i a set bit of todo (below
+ * n <= 64). Returns the pages delivered; first_absent is set if the first page left over has
+ * no table entry. Every thread's copies are complete and the pins dropped on return. */
+__device__ __forceinline__ uint64_t group_pass(const gfs_dev* d, BlockState* bs, uint32_t file, uint64_t base,
+                                               uint32_t n, uint64_t todo, uint64_t offset, uint64_t end,
+                                               uint8_t* dst, bool& first_absent) {
+  const uint32_t tid = thread_id(), nt = block_threads(), l = lane();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6), W = nt >> 6;
+  const bool timed = H(d)->page_timers != 0;
+  const uint64_t t0 = timed ? wall_clock64() : 0;
+  const uint32_t par = bs->par;
+  const uint32_t mine = group_page(l, w, W);
+  int32_t f = group_lookup(d, file, base, n, todo, w, W);
+  uint64_t pw = 0, tag = 0;
+  if (f >= 0) {
+    pw = __hip_atomic_fetch_add(G(&H(d)->fword[f]), GFS_FW_PIN_ONE, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+    /* a frame being filled is joined, a failed one reported and a marker page's mark taken by
+       gread_page */
+    if ((pw & GFS_FW_STATE) != GFS_FS_VALID || (pw & GFS_FW_ERR) || (H(d)->ra_async && (pw & GFS_FW_MARK))) {
+      frame_unpin(d, (uint32_t)f);
+      f = kNotReady;
+    } else {
+      /* read after the pin, so it names the page the bytes belong to: a pinned frame cannot
+         be claimed. Waited for after the copy */
+      tag = ld_rlx(&H(d)->ftag[f]);
+    }
+  }
+  if (mine < n) bs->bframe[par][mine] = f;
+  __syncthreads();
+  const int32_t fl = l < n ? bs->bframe[par][l] : kAbsent;
+  uint64_t hits = __ballot(fl >= 0);
+  if (tid == 0) {
+    bs->par = par ^ 1u;   /* every thread has read par, and has left the other half */
+    bs->bbad[par ^ 1u] = 0;
+  }
+  const uint64_t t1 = timed ? wall_clock64() : 0;
+  const uint32_t sh = H(d)->page_shift;
+  if (hits) {
+    if (n > 1 && (1u << sh) < 128u * nt) {
+      copy_group(d, bs->bframe[par], base, n, offset, end, dst, tid, nt);
+    } else {
+      for (uint64_t m = hits; m; m &= m - 1) {
+        const uint32_t i = (uint32_t)__builtin_ctzll(m);
+        const uint64_t pb = (base + i) << sh;
+        const uint64_t lo = offset > pb ? offset : pb;
+        const uint64_t hi = end < pb + (1ull << sh) ? end : pb + (1ull << sh);
+        copy_out(dst + (lo - offset), H(d)->frames + ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(fl, (int)i) << sh) + (lo - pb),
+                 (uint32_t)(hi - lo), tid, nt);
       }
     }
-    __syncthreads();
-    if (tid < cnt && bs->bframe[tid] >= 0) frame_unpin(d, (uint32_t)bs->bframe[tid]);
-    if (tid == 0 && d->page_timers) bcount(bs, GFS_T_COPY, wall_clock64() - tb0);
-    __syncthreads();
+    /* bytes copied from a frame that holds another page (it was reused between the lookup and
+       the pin) are overwritten by the next look: gread has not returned, nobody reads dst yet */
+    if (f >= 0 && tag != page_key(file, base + mine))
+      __hip_atomic_fetch_or(&bs->bbad[par], 1ull << mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  if (tid == 0) bs->read_last = plast;   /* read by wave 0's miss path, after this store */
-  for (uint64_t p = pfirst; p <= plast; ++p) {
-    if (batched && p - pfirst < 64 && bs->bframe[p - pfirst] >= 0) continue;
-    const bool ptm = d->page_timers != 0;
+  __syncthreads();
+  const uint64_t bad = bs->bbad[par];
+  const uint64_t t2 = timed ? wall_clock64() : 0;
+  if (f >= 0) {
+    if (!((bad >> mine) & 1)) frame_pin_bits(d, (uint32_t)f, pw);
+    frame_unpin(d, (uint32_t)f);
+  }
+  hits &= ~bad;
+  if (tid == 0) {
+    bcount(bs, GFS_C_HITS, (uint64_t)__popcll(hits));
+    if (bad) bcount(bs, GFS_C_RETRIES, (uint64_t)__popcll(bad));
+    if (timed) {
+      bcount(bs, GFS_T_ACQUIRE, t1 - t0);
+      bcount(bs, GFS_T_COPY, t2 - t1);
+      bcount(bs, GFS_T_UNPIN, wall_clock64() - t2);
+    }
+  }
+  const uint64_t left = todo & ~hits;
+  first_absent = left && __builtin_amdgcn_readlane(fl, (int)__builtin_ctzll(left)) == kAbsent;
+  return hits;
+}
+
+/* Block-collective: deliver page p of the read [offset, end) through the one-page path: a hit,
+ * a join, or a miss that fetches it. Out of line, so that the registers of the miss path are
+ * not the caller's. absent: the page was just looked up and has no table entry. 0 or -errno. */
+__device__ __attribute__((noinline)) int64_t gread_page(const gfs_dev* d, BlockState* bs, uint32_t file, uint64_t p,
+                                                        uint64_t fsize, uint64_t offset, uint64_t end, uint8_t* dst,
+                                                        bool absent) {
+  d = uniform(d);
+  const uint32_t tid = thread_id(), nt = block_threads();
+  const uint32_t bid = block_id();
+  const uint64_t P = H(d)->page_size;
+  const bool ptm = H(d)->page_timers != 0;
+  while (true) {
     const uint64_t ta0 = ptm ? wall_clock64() : 0;
-    if (tid < 64) acquire_page_wave(d, (uint32_t)fd, p, fsize, bs, bid);
+    if (tid < 64) acquire_page_wave(d, file, p, fsize, bs, bid, absent);
+    absent = false;
     __syncthreads();
     if (bs->pull == 5) {
       /* a miss while this block's asynchronous request is outstanding: finish it, look again */
       const int64_t e = async_finish_block(d, bs);
-      if (e < 0) {
-        err = e;
-        break;
-      }
-      --p;   /* the same page again (unsigned wrap at 0 is undone by the loop's ++p) */
+      if (e < 0) return e;
       continue;
     }
     if (bs->pull >= 3) {
@@ -2543,71 +2549,185 @@ __device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd
       }
       __syncthreads();
     }
-
     const int64_t st = bs->status;
     const int32_t f = bs->frame;
+    const bool trig = bs->trig != 0;
     if (st < 0) {
-      err = st;
       __syncthreads();
-      break;
+      return st;
     }
     const uint64_t ta1 = ptm ? wall_clock64() : 0;
-    const uint64_t pbase = p << sh_bits;
+    const uint64_t pbase = p << H(d)->page_shift;
     const uint64_t lo = offset > pbase ? offset : pbase;
     const uint64_t hi = end < pbase + P ? end : pbase + P;
-    /* a hit pinned with its tag unchecked: thread 0's tag load goes out just before its share
-       of the copy, so the check costs no round trip of its own; if the frame turns out to hold
-       another page (reused between the lookup and the pin), the bytes copied to dst are
-       overwritten by the next look (gread has not returned, so nobody may read dst yet) */
-    const uint64_t tk = bs->tagkey;
-    uint64_t tag = 0;
-    if (tk && tid == 0) tag = ld_rlx(&d->ftag[f]);
-    copy_block((uint8_t*)dst + (lo - offset), d->frames + (uint64_t)f * P + (lo - pbase), hi - lo,
-               tid, nt);
-    if (tk && tid == 0) {
-      const bool ok = tag == tk;
-      bs->tag_ok = ok ? 1 : 0;
-      if (ok && d->ra_async && (bs->pinw & GFS_FW_MARK)) bs->trig = mark_take_lane(d, (uint32_t)f) ? 1u : 0u;
-    }
+    copy_out(dst + (lo - offset), H(d)->frames + (uint64_t)f * P + (lo - pbase), (uint32_t)(hi - lo), tid, nt);
     __syncthreads();
-    const bool trig = bs->trig != 0;
-    if (tk && !bs->tag_ok) {
-      __syncthreads();
-      if (tid == 0) {
-        frame_unpin(d, (uint32_t)f);
-        bcount(bs, GFS_C_RETRIES, 1);
-      }
-      --p;   /* look the same page up again (unsigned wrap at 0 is undone by the loop's ++p) */
-      continue;
-    }
     if (tid == 0) {
-      if (tk) {
-        frame_pin_bits(d, (uint32_t)f, bs->pinw);
-        bcount(bs, GFS_C_HITS, 1);
-      }
+      const uint64_t ta2 = ptm ? wall_clock64() : 0;
+      frame_unpin(d, (uint32_t)f);
       if (ptm) {
-        const uint64_t ta2 = wall_clock64();
-        frame_unpin(d, (uint32_t)f);
         bcount(bs, GFS_T_ACQUIRE, ta1 - ta0);
         bcount(bs, GFS_T_COPY, ta2 - ta1);
         bcount(bs, GFS_T_UNPIN, wall_clock64() - ta2);
-      } else {
-        frame_unpin(d, (uint32_t)f);
       }
     }
     if (trig) {
       /* this access took its stream's marker: finish the block's previous asynchronous
          request, then issue the stream's next window without waiting for it */
       const int64_t e = async_finish_block(d, bs);
-      if (e < 0) {
-        err = e;
-        break;
-      }
-      if (tid < 64) async_issue_wave(d, (uint32_t)fd, p, fsize, bs, bid, wall_clock64());
+      if (e < 0) return e;
+      if (tid < 64) async_issue_wave(d, file, p, fsize, bs, bid, wall_clock64());
       __syncthreads();
     }
+    return 0;
   }
-  if (err) return err;
+}
+
+}  // namespace gfsd
+
+/* ====================================================================== public API */
+
+__device__ int gopen_id(const gfs_dev* d, int file_id, int flags) {
+  gfsd::BlockState* bs = gfsd::block_state();
+  __syncthreads();   /* every thread is past the block's earlier calls */
+  if (gfsd::thread_id() == 0) {
+    int v;
+    if (flags != GFS_O_RDONLY) {
+      v = -gfsd::kEROFS;
+    } else if (file_id < 0 || (uint32_t)file_id >= gfsd::H(d)->max_files ||
+               gfsd::ld_rlx32(&gfsd::H(d)->files[file_id].open) == 0) {
+      v = -gfsd::kENOENT;
+    } else {
+      __hip_atomic_fetch_add(gfsd::G(&gfsd::H(d)->files[file_id].handles), 1u, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+      v = file_id;
+    }
+    bs->pslot = -1;
+    if (v >= 0 && gfsd::H(d)->policy == GFS_POLICY_PRIVATE) {
+      /* the block's private slot: its own frames and private buffer until gclose. A slot
+         given back by a block that just ended may not show yet: look again, with naps,
+         until the wait timeout */
+      const uint64_t t0 = wall_clock64();
+      uint32_t naps = 0;
+      while (bs->pslot < 0) {
+        for (uint32_t i = 0; i < gfsd::H(d)->npslots && bs->pslot < 0; ++i) {
+          const uint32_t s = (gfsd::block_id() + i) % gfsd::H(d)->npslots;
+          uint32_t z = 0;
+          if (gfsd::ld_rlx32(&gfsd::H(d)->pslots[s].owner) == 0 && gfsd::cas32(&gfsd::H(d)->pslots[s].owner, z, 1u))
+            bs->pslot = (int32_t)s;
+        }
+        if (bs->pslot >= 0 || gfsd::expired(d, t0)) break;
+        gfsd::nap(naps);
+      }
+      if (bs->pslot < 0) {
+        __hip_atomic_fetch_sub(gfsd::G(&gfsd::H(d)->files[file_id].handles), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = -gfsd::kENOSPC;
+      } else {
+        gfs_pslot* ps = &gfsd::H(d)->pslots[bs->pslot];
+        ps->n = 0;   /* a new owner starts with an empty private buffer */
+        ps->used = 0;
+      }
+    }
+    for (int c = 0; c < GFS_C_COUNT; ++c) bs->ctr[c] = 0;
+    bs->pull = 0;
+    bs->trig = 0;
+    bs->par = 0;
+    bs->bbad[0] = 0;
+    bs->a_pending = 0;   /* an asynchronous request is finished by gclose, before the next gopen */
+    bs->open_result = v;
+    bs->open_fd = v;
+    bs->open_size = v >= 0 ? gfsd::H(d)->files[v].size : 0;
+  }
+  __syncthreads();
+  const int v = bs->open_result;
+  __syncthreads();
+  return v;
+}
+
+__device__ int gopen(const gfs_dev* d, const char* path, int flags) {
+  gfsd::BlockState* bs = gfsd::block_state();
+  if (gfsd::thread_id() == 0) {
+    int id = -1;
+    for (uint32_t i = 0; i < gfsd::H(d)->max_files && id < 0; ++i) {
+      if (gfsd::ld_rlx32(&gfsd::H(d)->files[i].open) == 0) continue;
+      const char* nm = gfsd::H(d)->names + (uint64_t)i * GFS_NAME_MAX;
+      uint32_t j = 0;
+      while (j < GFS_NAME_MAX && nm[j] == path[j] && nm[j] != 0) ++j;
+      if (j < GFS_NAME_MAX && nm[j] == 0 && path[j] == 0) id = (int)i;
+    }
+    bs->open_result = id;
+  }
+  __syncthreads();
+  const int id = bs->open_result;
+  __syncthreads();
+  if (flags != GFS_O_RDONLY) return -gfsd::kEROFS;
+  if (id < 0) return -gfsd::kENOENT;
+  return gopen_id(d, id, flags);
+}
+
+__device__ int gclose(const gfs_dev* d, int fd) {
+  if (fd < 0 || (uint32_t)fd >= gfsd::H(d)->max_files) return -gfsd::kEBADF;
+  gfsd::BlockState* bs = gfsd::block_state();
+  /* an asynchronous request still outstanding is pulled in before the block lets go */
+  (void)gfsd::async_finish_block(d, bs);
+  __syncthreads();
+  if (gfsd::thread_id() == 0) {
+    __hip_atomic_fetch_sub(gfsd::G(&gfsd::H(d)->files[fd].handles), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (gfsd::H(d)->policy == GFS_POLICY_PRIVATE && bs->pslot >= 0) {
+      gfs_pslot* ps = &gfsd::H(d)->pslots[bs->pslot];
+      bs->ctr[GFS_C_PB_WASTED] += ps->n - ps->used;   /* the private buffer is dropped */
+      ps->n = 0;
+      ps->used = 0;
+      __hip_atomic_store(gfsd::G(&ps->owner), 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      bs->pslot = -1;
+    }
+    for (int c = 0; c < GFS_C_COUNT; ++c) {
+      if (bs->ctr[c]) gfsd::fadd64(&gfsd::H(d)->g->ctr[c], bs->ctr[c]);
+      bs->ctr[c] = 0;
+    }
+    bs->open_fd = -1;
+  }
+  __syncthreads();
+  return 0;
+}
+
+__device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd, uint64_t offset,
+                                                        uint64_t size, void* dst) {
+  using namespace gfsd;
+  BlockState* bs = block_state();
+  if (fd < 0 || (uint32_t)fd >= H(d)->max_files) return -kEBADF;
+  uint64_t fsize;
+  if (fd == bs->open_fd) {
+    fsize = bs->open_size;   /* checked by gopen */
+  } else {
+    gfs_file_dev* fe = &H(d)->files[fd];
+    if (ld_rlx32(&fe->open) == 0) return -kEBADF;
+    fsize = fe->size;
+  }
+  if (block_threads() & 63u) return -kEINVAL;
+  if (size == 0 || offset >= fsize) return 0;
+  const uint64_t end = (size > fsize - offset) ? fsize : offset + size;
+  const uint32_t tid = thread_id();
+  const uint32_t sh = H(d)->page_shift;
+  const uint64_t plast = (end - 1) >> sh;
+  const bool grouped = H(d)->trace_level == 0;
+  if (tid == 0) bs->read_last = plast;   /* read by wave 0's miss path, after this store */
+  for (uint64_t base = offset >> sh; base <= plast; base += 64) {
+    const uint32_t n = plast - base < 64 ? (uint32_t)(plast - base) + 1 : 64u;
+    uint64_t todo = n == 64 ? ~0ull : (1ull << n) - 1;
+    while (true) {
+      bool absent = false;
+      if (grouped) todo &= ~group_pass(d, bs, (uint32_t)fd, base, n, todo, offset, end, (uint8_t*)dst, absent);
+      if (todo == 0) break;
+      /* the first page not delivered; the window its miss fetches may hold the next ones, so
+         the group is looked at again */
+      const int64_t e = gread_page(d, bs, (uint32_t)fd, base + (uint64_t)__builtin_ctzll(todo), fsize, offset, end,
+                                   (uint8_t*)dst, absent);
+      if (e < 0) return e;
+      todo &= todo - 1;
+      if (todo == 0) break;
+    }
+  }
   if (tid == 0) bcount(bs, GFS_C_DELIVERED, end - offset);
   return (int64_t)(end - offset);
 }

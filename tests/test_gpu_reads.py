@@ -1,0 +1,95 @@
+"""gread's copies at the edges of their 16-byte units, pages and groups of 64 pages: every
+alignment of the file offset against the user buffer, reads shorter than a unit, up to a page's
+edge, over it, and over more than 64 pages, by blocks of one to four waves, cold and cached; and
+bytes beside the read's destination left alone."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2109_05366_amd import build, gfs, runner
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gfs.lib()
+    return torch
+
+
+def _file(tmp_path, size, seed):
+    data = np.random.RandomState(seed).randint(0, 256, size, dtype=np.uint8)
+    p = str(tmp_path / "f.bin")
+    data.tofile(p)
+    return p, data
+
+
+@pytest.mark.parametrize("page,threads", [(4 << 10, 256), (4 << 10, 64), (16 << 10, 192), (64 << 10, 256), (64 << 10, 128)])
+def test_reads_at_every_offset_alignment(page, threads, tmp_path, cuda):
+    size = 70 * page + 4093                      # more than 64 pages, a ragged last one
+    path, data = _file(tmp_path, size, page + threads)
+    at = [a for a in range(16)]
+    starts = ([a for a in at] + [page - 24 + a for a in at] + [63 * page + 5 * a for a in at] +
+              [size - 40 - 16 * a for a in at] + [size - 1, size, size + 7])
+    reads = {16: starts, 48: starts, page + 32: starts, 3 * page: starts[::3], 69 * page + 16: starts[::5]}
+    cfg = runner.make_config(page, 128 * page, ra_cap_bytes=8 * page, timeout_s=20)
+    for n, offs in reads.items():
+        print(f"[gpu] reads page={page} threads={threads} size={n}", flush=True)
+        with gfs.PageCache(cfg) as cache:
+            fid = cache.open(path)
+            offsets = np.array(offs, dtype=np.uint64)[:, None]
+            for _ in range(2):                   # cold, then cached
+                r = runner.ListReader(offsets, n, 2, threads)
+                r.buf.fill_(0xA5)
+                r.launch(cache, fid)
+                res = r.result()
+                want = np.full((len(offs), n), 0xA5, dtype=np.uint8)
+                for i, o in enumerate(offs):
+                    got = data[o:o + n]
+                    want[i, :len(got)] = got
+                np.testing.assert_array_equal(res.status, [len(data[o:o + n]) for o in offs])
+                np.testing.assert_array_equal(res.out, want)
+            st = cache.stats()
+        assert st["timeouts"] == 0 and st["io_errors"] == 0 and st["hits"] > 0
+
+
+def _probe():
+    vp, u64, u32 = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_uint32
+    L = ctypes.CDLL(build.PROBE_LIB)
+    L.gfs_test_api_probe.argtypes = [vp, vp, vp, ctypes.c_int, u64, u64, u64, u32, vp, vp, vp]
+    L.gfs_test_api_probe.restype = ctypes.c_int
+    return L
+
+
+@pytest.mark.parametrize("page", [4 << 10, 64 << 10])
+def test_reads_into_every_buffer_alignment(page, tmp_path, cuda):
+    torch = cuda
+    size = 5 * page + 77
+    path, data = _file(tmp_path, size, page + 1)
+    L = _probe()
+    cfg = runner.make_config(page, 64 * page, ra_cap_bytes=4 * page, timeout_s=20)
+    with gfs.PageCache(cfg) as cache:
+        fid = cache.open(path)
+        unused = cache.open(path)
+        cache.close_file(unused)
+        name = torch.tensor(list(path.encode()) + [0], dtype=torch.uint8, device="cuda")
+        missing = torch.tensor(list(b"/none") + [0], dtype=torch.uint8, device="cuda")
+        out = torch.zeros(10, dtype=torch.int64, device="cuda")
+        for n in (1, 15, 16, 17, 31, 200, page + 3, 3 * page + 5):
+            print(f"[gpu] buffer alignments page={page} size={n}", flush=True)
+            for a in range(16):
+                off = page - 9 + (5 * a) % 16
+                buf = torch.full((n + 128,), 0xA5, dtype=torch.uint8, device="cuda")
+                rc = L.gfs_test_api_probe(cache.handle, name.data_ptr(), missing.data_ptr(), unused, off, n, size, 256,
+                                          buf.data_ptr() + 16 + a, out.data_ptr(),
+                                          torch.cuda.current_stream().cuda_stream)
+                assert rc == 0
+                torch.cuda.synchronize()
+                assert out[0].item() == fid and out[5].item() == n
+                want = np.full(n + 128, 0xA5, dtype=np.uint8)
+                want[16 + a:16 + a + n] = data[off:off + n]
+                np.testing.assert_array_equal(buf.cpu().numpy(), want)
