@@ -930,45 +930,87 @@ __device__ __attribute__((noinline)) void copy_block_aligned(uint8_t* dst, const
   for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) dst[j] = src[j];
 }
 
-/* 16 bytes at any address of global memory: one vector load, which the memory unit splits
-   where it crosses lines */
-typedef v4u v4u_any __attribute__((aligned(1)));
-typedef __attribute__((address_space(1))) v4u_any gv4u_any;
+/* ------------------------------------------------------------------ reading frames
+ * A frame is written by blocks of any XCD and reused for page after page, and the XCDs' L2s do
+ * not follow each other's writes. Its bytes are read with device-scope loads (sc1), which do
+ * not take a line another XCD has replaced, so a pin needs no acquire. With one per
+ * hit, emptying the XCD's L2 each time, 256 MiB of cached 4 KiB pages in 128 KiB reads took
+ * 253 us instead of 165, 4080-byte records 332 instead of 273. The loads go out after the pin's result was seen (and a block barrier for
+ * the other waves), and the bytes reached memory before the frame was published (the fill's
+ * release). They are nontemporal as well: page bytes pass once.
+ * N loads of 16 bytes at any alignment, issued together and waited for in the same statement;
+ * every address must be readable. */
+template <int N>
+__device__ __forceinline__ void ld_frame(v4u (&a)[N], const uint8_t* const (&p)[N]) {
+  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "loads issued together");
+  if constexpr (N == 1) {
+    asm volatile("global_load_dwordx4 %0, %1, off sc1 nt\n\ts_waitcnt vmcnt(0)" : "=&v"(a[0]) : "v"(p[0]) : "memory");
+  } else if constexpr (N == 2) {
+    asm volatile("global_load_dwordx4 %0, %2, off sc1 nt\n\t"
+                 "global_load_dwordx4 %1, %3, off sc1 nt\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(a[0]), "=&v"(a[1]) : "v"(p[0]), "v"(p[1]) : "memory");
+  } else if constexpr (N == 4) {
+    asm volatile("global_load_dwordx4 %0, %4, off sc1 nt\n\t"
+                 "global_load_dwordx4 %1, %5, off sc1 nt\n\t"
+                 "global_load_dwordx4 %2, %6, off sc1 nt\n\t"
+                 "global_load_dwordx4 %3, %7, off sc1 nt\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+                 : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]) : "memory");
+  } else {
+    asm volatile("global_load_dwordx4 %0, %8, off sc1 nt\n\t"
+                 "global_load_dwordx4 %1, %9, off sc1 nt\n\t"
+                 "global_load_dwordx4 %2, %10, off sc1 nt\n\t"
+                 "global_load_dwordx4 %3, %11, off sc1 nt\n\t"
+                 "global_load_dwordx4 %4, %12, off sc1 nt\n\t"
+                 "global_load_dwordx4 %5, %13, off sc1 nt\n\t"
+                 "global_load_dwordx4 %6, %14, off sc1 nt\n\t"
+                 "global_load_dwordx4 %7, %15, off sc1 nt\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(a[4]), "=&v"(a[5]), "=&v"(a[6]), "=&v"(a[7])
+                 : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]) : "memory");
+  }
+}
 typedef __attribute__((address_space(1))) uint8_t gu8;
+__device__ __forceinline__ uint8_t ld_frame_byte(const uint8_t* p) {
+  return __hip_atomic_load((const gu8*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+/* One round of a copy of n16 16-byte units: units i, i + nt, ... (N of them) of this thread.
+   Loads past the last unit read it again and are not stored. */
+template <int N>
+__device__ __forceinline__ void copy_round(gv4u* o, const uint8_t* src, uint32_t i, uint32_t n16, uint32_t nt) {
+  v4u a[N];
+  const uint8_t* p[N];
+#pragma unroll
+  for (uint32_t k = 0; k < N; ++k) {
+    const uint32_t u = i + k * nt;
+    p[k] = src + ((uint64_t)(u < n16 ? u : n16 - 1) << 4);
+  }
+  ld_frame(a, p);
+#pragma unroll
+  for (uint32_t k = 0; k < N; ++k)
+    if (i + k * nt < n16) o[i + k * nt] = a[k];
+}
 
 /* The copy-out of n bytes of one frame to a user buffer, both at any alignment: 16-byte stores
- * aligned in dst, loads from wherever the bytes lie in the frame, the fewer than 16 bytes
- * before and after them one byte a thread. Eight loads a thread are in flight, also in the
- * last, partly filled round; they are nontemporal, so that page bytes streaming through do
- * not push the page table and frame words out of L2. */
+ * aligned in dst, loads from wherever the bytes lie in the frame (the memory unit splits one
+ * that crosses lines), the fewer than 16 bytes before and after them one byte a thread. Eight
+ * loads a thread are in flight, in the last round as many as it needs. */
 __device__ __forceinline__ void copy_out(uint8_t* dst, const uint8_t* src, uint32_t n, uint32_t tid, uint32_t nt) {
   uint32_t head = (0u - (uint32_t)(uintptr_t)dst) & 15u;
   if (head > n) head = n;
   const uint32_t tail = (n - head) & 15u;
   if (head | tail) {
     const uint32_t e = tid < 16 ? tid : n - tail + (tid - 16);
-    if (tid < head || (tid >= 16 && tid - 16 < tail)) ((gu8*)dst)[e] = ((const gu8*)src)[e];
+    if (tid < head || (tid >= 16 && tid - 16 < tail)) ((gu8*)dst)[e] = ld_frame_byte(src + e);
   }
-  const gv4u_any* s = (const gv4u_any*)(src + head);
-  gv4u* o = (gv4u*)(dst + head);
   const uint32_t n16 = (n - head) >> 4;
-  uint32_t i = tid;
-  for (; i + 7 * nt < n16; i += 8 * nt) {
-    v4u a[8];
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) a[k] = __builtin_nontemporal_load(&s[i + k * nt]);
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) o[i + k * nt] = a[k];
-  }
-  if (i < n16) {
-    v4u a[8];
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k)
-      if (i + k * nt < n16) a[k] = __builtin_nontemporal_load(&s[i + k * nt]);
-#pragma unroll
-    for (uint32_t k = 0; k < 8; ++k)
-      if (i + k * nt < n16) o[i + k * nt] = a[k];
-  }
+  src += head;
+  gv4u* o = (gv4u*)(dst + head);
+  uint32_t i0 = 0;   /* the same in every thread */
+  for (; i0 + 4 * nt < n16; i0 += 8 * nt) copy_round<8>(o, src, i0 + tid, n16, nt);
+  if (i0 + 2 * nt < n16) copy_round<4>(o, src, i0 + tid, n16, nt);
+  else if (i0 + nt < n16) copy_round<2>(o, src, i0 + tid, n16, nt);
+  else if (i0 < n16) copy_round<1>(o, src, i0 + tid, n16, nt);
 }
 
 /* Lane: this block holds a pin on frame f (page p), which another block's request is
@@ -2383,17 +2425,18 @@ __device__ __forceinline__ void copy_group(const gfs_dev* d, const int32_t* fram
   const uint32_t total = n << ush;
   for (uint32_t u0 = tid; u0 < total; u0 += 8 * nt) {
     v4u a[8];
+    const uint8_t* p[8];
     uint32_t ok = 0;
 #pragma unroll
     for (uint32_t j = 0; j < 8; ++j) {
       const uint32_t u = u0 + j * nt;
       const uint32_t i = u >> ush, at = ((u & ((1u << ush) - 1)) << 4) + h, pos = (i << sh) + at;
       const int32_t f = u < total ? frame[i] : kAbsent;
-      if (f >= 0 && at + 16 <= P && pos >= lo && pos + 16 <= hi) {
-        ok |= 1u << j;
-        a[j] = __builtin_nontemporal_load((const gv4u_any*)(frames + ((uint64_t)(uint32_t)f << sh) + at));
-      }
+      const bool take = f >= 0 && at + 16 <= P && pos >= lo && pos + 16 <= hi;
+      if (take) ok |= 1u << j;
+      p[j] = frames + (take ? ((uint64_t)(uint32_t)f << sh) + at : 0);   /* not taken: any readable bytes */
     }
+    ld_frame(a, p);
 #pragma unroll
     for (uint32_t j = 0; j < 8; ++j) {
       const uint32_t u = u0 + j * nt;
@@ -2413,7 +2456,7 @@ __device__ __forceinline__ void copy_group(const gfs_dev* d, const int32_t* fram
       const uint32_t k = tid & 15u;
       const uint32_t at = (tid & 16u) ? b + k : plo + k;
       if (at < ((tid & 16u) ? phi : a))
-        ((gu8*)d0)[p0 + at] = ((const gu8*)frames)[((uint64_t)(uint32_t)f << sh) + at];
+        ((gu8*)d0)[p0 + at] = ld_frame_byte(frames + ((uint64_t)(uint32_t)f << sh) + at);
     }
   }
 }
@@ -2433,7 +2476,7 @@ __device__ __forceinline__ uint64_t group_pass(const gfs_dev* d, BlockState* bs,
   int32_t f = group_lookup(d, file, base, n, todo, w, W);
   uint64_t pw = 0, tag = 0;
   if (f >= 0) {
-    pw = __hip_atomic_fetch_add(G(&H(d)->fword[f]), GFS_FW_PIN_ONE, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+    pw = __hip_atomic_fetch_add(G(&H(d)->fword[f]), GFS_FW_PIN_ONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     /* a frame being filled is joined, a failed one reported and a marker page's mark taken by
        gread_page */
     if ((pw & GFS_FW_STATE) != GFS_FS_VALID || (pw & GFS_FW_ERR) || (H(d)->ra_async && (pw & GFS_FW_MARK))) {
