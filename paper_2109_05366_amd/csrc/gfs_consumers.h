@@ -25,16 +25,15 @@ __device__ __forceinline__ uint64_t checksum_part(const uint8_t* buf, uint64_t n
 #pragma unroll
     for (int k = 0; k < 8; ++k) s += (uint64_t)x[k].x + x[k].y + x[k].z + x[k].w;
   }
-  for (; i + 3ull * nt < n16; i += 4ull * nt) {
-    gfsd::v4u x[4];
+  if (i < n16) {   // the last, partly filled round, its loads in flight together as well
+    gfsd::v4u x[8];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = v[i + (uint64_t)k * nt];
+    for (int k = 0; k < 8; ++k) {
+      x[k] = gfsd::v4u{0, 0, 0, 0};
+      if (i + (uint64_t)k * nt < n16) x[k] = v[i + (uint64_t)k * nt];
+    }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s += (uint64_t)x[k].x + x[k].y + x[k].z + x[k].w;
-  }
-  for (; i < n16; i += nt) {
-    const gfsd::v4u x = v[i];
-    s += (uint64_t)x.x + x.y + x.z + x.w;
+    for (int k = 0; k < 8; ++k) s += (uint64_t)x[k].x + x[k].y + x[k].z + x[k].w;
   }
   // remaining bytes (n not a multiple of 16): whole words, then the zero-padded last word
   const uint64_t rem0 = n16 << 4;
@@ -47,19 +46,51 @@ __device__ __forceinline__ uint64_t checksum_part(const uint8_t* buf, uint64_t n
   return s;
 }
 
+// Byte histogram. The block counts into kHistColumns copies of the 256 counters, lane l into copy
+// l mod kHistColumns, laid out so that a lane's counters all lie in its own LDS bank: no two
+// lanes of half a wave ever wait for each other, whatever the bytes (with one copy, 64 random
+// bytes met in a bank 4-5 at a time, equal bytes 64 at a time). Eight 16-byte loads a thread
+// are in flight; with one, the loop waited a cache round trip for every 16 bytes.
+// 512 MiB of cached 256 KiB pages, gread and histogram: 322 us (one load, one copy), 300 (eight
+// loads), 291; 64 files of 345 MiB, checksum and histogram: 384 -> 310.
+constexpr uint32_t kHistColumns = 32;
+constexpr uint32_t kHistWords = 256 * kHistColumns;   // 32 KiB of LDS
+
+__device__ __forceinline__ void histogram_clear(uint32_t* hist, uint32_t tid, uint32_t nt) {
+  for (uint32_t i = tid; i < kHistWords; i += nt) hist[i] = 0;
+}
+
 __device__ __forceinline__ void histogram_part(const uint8_t* buf, uint64_t n, uint32_t tid,
                                                uint32_t nt, uint32_t* hist) {
   const uint64_t n16 = n >> 4;
   const gfsd::gv4u* v = (const gfsd::gv4u*)buf;
-  for (uint64_t i = tid; i < n16; i += nt) {
-    const gfsd::v4u x = v[i];
-    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+  uint32_t* const mine = hist + (tid & (kHistColumns - 1));
+  const auto count = [&](uint32_t w) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int b = 0; b < 4; ++b) atomicAdd(&mine[((w >> (8 * b)) & 0xff) * kHistColumns], 1u);
+  };
+  for (uint64_t i = tid; i < n16; i += 8ull * nt) {
+    gfsd::v4u x[8];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) atomicAdd(&hist[(w[k] >> (8 * b)) & 0xff], 1u);
+    for (int k = 0; k < 8; ++k)
+      if (i + (uint64_t)k * nt < n16) x[k] = v[i + (uint64_t)k * nt];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (i + (uint64_t)k * nt < n16) {
+        count(x[k].x);
+        count(x[k].y);
+        count(x[k].z);
+        count(x[k].w);
+      }
   }
-  for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) atomicAdd(&hist[buf[j]], 1u);
+  for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) atomicAdd(&mine[buf[j] * kHistColumns], 1u);
+}
+
+// The count of byte value v over all copies (after a barrier); each lane starts at a copy of its own.
+__device__ __forceinline__ uint32_t histogram_count(const uint32_t* hist, uint32_t v) {
+  uint32_t s = 0;
+  for (uint32_t c = 0; c < kHistColumns; ++c) s += hist[v * kHistColumns + ((c + v) & (kHistColumns - 1))];
+  return s;
 }
 
 __device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, uint64_t* red, uint32_t tid, uint32_t nt) {

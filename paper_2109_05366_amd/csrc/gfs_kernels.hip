@@ -15,7 +15,11 @@ namespace {
 
 using gfs_consumers::block_sum_u64;
 using gfs_consumers::checksum_part;
+using gfs_consumers::histogram_clear;
+using gfs_consumers::histogram_count;
 using gfs_consumers::histogram_part;
+using gfs_consumers::kHistColumns;
+using gfs_consumers::kHistWords;
 
 __global__ void zero_kernel(uint64_t* p, uint64_t n8) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -46,14 +50,13 @@ __global__ void purge_file_kernel(const gfs_dev* d, uint32_t nframes, uint64_t p
 __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) list_reader_kernel(const gfs_dev* d, int file_id, const uint64_t* offsets,
                                    uint32_t reads, uint64_t read_size, int consumer,
                                    uint8_t* buf, void* out, int64_t* status, uint64_t* turn) {
-  __shared__ uint32_t hist[256];
+  __shared__ uint32_t hist[kHistWords];
   __shared__ uint64_t red[16];
   __shared__ int gate_err;
   __shared__ uint64_t offs[64];   /* the block's next read offsets, fetched 64 at a time */
   const uint32_t b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   uint8_t* mybuf = buf + (uint64_t)b * read_size;
-  if (consumer == 1)
-    for (uint32_t i = tid; i < 256; i += nt) hist[i] = 0;
+  if (consumer == 1) histogram_clear(hist, tid, nt);
   __syncthreads();
   const int fd = gopen_id(d, file_id, GFS_O_RDONLY);
   int64_t err = fd < 0 ? fd : 0;
@@ -115,7 +118,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) list_reader_kernel(c
     }
   } else if (consumer == 1) {
     __syncthreads();
-    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = hist[i];
+    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = histogram_count(hist, i);
   }
   if (tid == 0) status[b] = err ? err : total;
 }
@@ -128,11 +131,10 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
                                                                               const uint64_t* offsets, uint32_t reads,
                                                                               uint64_t read_size, int consumer,
                                                                               void* out, int64_t* status) {
-  __shared__ uint32_t hist[256];
+  extern __shared__ uint32_t hist[];   // kHistWords if the consumer is the histogram
   __shared__ uint64_t red[16];
   const uint32_t b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
-  if (consumer == 1)
-    for (uint32_t i = tid; i < 256; i += nt) hist[i] = 0;
+  if (consumer == 1) histogram_clear(hist, tid, nt);
   __syncthreads();
   int64_t total = 0;
   uint64_t csum = 0;
@@ -153,7 +155,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
         csum += word;
       }
     } else {
-      for (uint64_t j = tid; j < n; j += nt) atomicAdd(&hist[p[j]], 1u);
+      for (uint64_t j = tid; j < n; j += nt) atomicAdd(&hist[p[j] * kHistColumns + (tid & (kHistColumns - 1))], 1u);
     }
   }
   __syncthreads();
@@ -161,7 +163,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
     const uint64_t s = block_sum_u64(csum, red, tid, nt);
     if (tid == 0) ((uint64_t*)out)[b] = s;
   } else {
-    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = hist[i];
+    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = histogram_count(hist, i);
   }
   if (tid == 0) status[b] = total;
 }
@@ -172,12 +174,12 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
 __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(const gfs_dev* d, const gfs_unit* units, uint64_t nunits,
                                     uint64_t* counter, uint8_t* buf, uint64_t unit_bytes,
                                     uint64_t* csum, uint32_t* hist, int64_t* status) {
-  __shared__ uint32_t lhist[256];
+  __shared__ uint32_t lhist[kHistWords];
   __shared__ uint64_t red[16];
   __shared__ uint64_t s_unit;
   const uint32_t tid = threadIdx.x, nt = blockDim.x;
   uint8_t* mybuf = buf + (uint64_t)blockIdx.x * unit_bytes;
-  for (uint32_t i = tid; i < 256; i += nt) lhist[i] = 0;
+  histogram_clear(lhist, tid, nt);
   int fd = -1;
   uint32_t cur_file = 0xffffffffu, cur_out = 0;
   uint64_t part = 0;
@@ -196,9 +198,11 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
         if (tid == 0) __hip_atomic_fetch_add(&csum[cur_out], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         for (uint32_t i = tid; i < 256; i += nt) {
-          if (lhist[i]) atomicAdd(&hist[(uint64_t)cur_out * 256 + i], lhist[i]);
-          lhist[i] = 0;
+          const uint32_t c = histogram_count(lhist, i);
+          if (c) atomicAdd(&hist[(uint64_t)cur_out * 256 + i], c);
         }
+        __syncthreads();
+        histogram_clear(lhist, tid, nt);
         part = 0;
         dirty = false;
       }
@@ -226,8 +230,10 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
     const uint64_t s = block_sum_u64(part, red, tid, nt);
     if (tid == 0) __hip_atomic_fetch_add(&csum[cur_out], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    for (uint32_t i = tid; i < 256; i += nt)
-      if (lhist[i]) atomicAdd(&hist[(uint64_t)cur_out * 256 + i], lhist[i]);
+    for (uint32_t i = tid; i < 256; i += nt) {
+      const uint32_t c = histogram_count(lhist, i);
+      if (c) atomicAdd(&hist[(uint64_t)cur_out * 256 + i], c);
+    }
   }
   if (fd >= 0) gclose(d, fd);
   if (tid == 0) status[blockIdx.x] = err ? err : total;
@@ -258,7 +264,8 @@ extern "C" int gfs_launch_buffer_reader(const void* data_dev, uint64_t data_size
   if (threads == 0 || threads % 64 || threads > GFS_MAX_BLOCK_THREADS) return -EINVAL;
   if (read_size == 0 || (consumer != 0 && consumer != 1)) return -EINVAL;
   if (((uintptr_t)out) & 15) return -EINVAL;
-  hipLaunchKernelGGL(buffer_reader_kernel, dim3(blocks), dim3(threads), 0, (hipStream_t)hip_stream,
+  const uint32_t lds = consumer == 1 ? kHistWords * sizeof(uint32_t) : 0;
+  hipLaunchKernelGGL(buffer_reader_kernel, dim3(blocks), dim3(threads), lds, (hipStream_t)hip_stream,
                      (const uint8_t*)data_dev, data_size, offsets, reads, read_size, consumer, out, status);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
