@@ -197,7 +197,10 @@ __device__ __forceinline__ uint64_t fadd64(uint64_t* p, uint64_t v) {
   return __hip_atomic_fetch_add(G(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 /* block-local statistics: only thread 0 of the block (lane 0 of wave 0) adds */
-__device__ __forceinline__ void bcount(BlockState* bs, int c, uint64_t v) { bs->ctr[c] += v; }
+__device__ __forceinline__ void bcount(BlockState* bs, int c, uint64_t v) {
+  /* an LDS addition that returns nothing: not waited for, unlike a load and a store */
+  __hip_atomic_fetch_add(&bs->ctr[c], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 /* ------------------------------------------------------------------ waiting */
 __device__ __forceinline__ void nap(uint32_t& n) {
@@ -2375,13 +2378,16 @@ __device__ __forceinline__ int32_t group_lookup(const gfs_dev* d, uint32_t file,
   const uint32_t l = lane();
   uint64_t* const pt = H(d)->pt;
   const uint32_t mask = H(d)->nbuckets_mask;
+  const uint32_t un = __builtin_amdgcn_readfirstlane(n);   /* whole pairs are skipped by a branch */
   int32_t f = kAbsent;
-  for (uint32_t r0 = 0; group_page(2 * r0, w, W) < n; r0 += 4) {
+  for (uint32_t r0 = 0; group_page(2 * r0, w, W) < un; r0 += 4) {
     uint64_t e[4], key[4];
 #pragma unroll
     for (uint32_t u = 0; u < 4; ++u) {
-      const uint32_t i = group_page(2 * (r0 + u) + (l >> 5), w, W);
       e[u] = 0;
+      key[u] = ~0ull;
+      if (group_page(2 * (r0 + u), w, W) >= un) continue;
+      const uint32_t i = group_page(2 * (r0 + u) + (l >> 5), w, W);
       key[u] = page_key(file, base + i);
       if (i < n && ((todo >> i) & 1)) {
         uint32_t b1, b2;
@@ -2391,6 +2397,7 @@ __device__ __forceinline__ int32_t group_lookup(const gfs_dev* d, uint32_t file,
     }
 #pragma unroll
     for (uint32_t u = 0; u < 4; ++u) {
+      if (group_page(2 * (r0 + u), w, W) >= un) continue;
       const uint64_t m = __ballot((e[u] >> GFS_ENTRY_FRAME_BITS) == key[u]);   /* keys are never 0 */
       const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
       const int fe = (int)((uint32_t)e[u] & (uint32_t)kFrameMask);
@@ -2633,12 +2640,17 @@ __device__ __attribute__((noinline)) int64_t gread_page(const gfs_dev* d, BlockS
 __device__ int gopen_id(const gfs_dev* d, int file_id, int flags) {
   gfsd::BlockState* bs = gfsd::block_state();
   __syncthreads();   /* every thread is past the block's earlier calls */
+  for (uint32_t c = gfsd::thread_id(); c < GFS_C_COUNT; c += gfsd::block_threads()) bs->ctr[c] = 0;
   if (gfsd::thread_id() == 0) {
+    /* one round trip for both fields */
+    const bool id_ok = file_id >= 0 && (uint32_t)file_id < gfsd::H(d)->max_files;
+    gfs_file_dev* fe = &gfsd::H(d)->files[id_ok ? file_id : 0];
+    const uint32_t is_open = gfsd::ld_rlx32(&fe->open);
+    const uint64_t size = gfsd::ld_rlx(&fe->size);
     int v;
     if (flags != GFS_O_RDONLY) {
       v = -gfsd::kEROFS;
-    } else if (file_id < 0 || (uint32_t)file_id >= gfsd::H(d)->max_files ||
-               gfsd::ld_rlx32(&gfsd::H(d)->files[file_id].open) == 0) {
+    } else if (!id_ok || is_open == 0) {
       v = -gfsd::kENOENT;
     } else {
       __hip_atomic_fetch_add(gfsd::G(&gfsd::H(d)->files[file_id].handles), 1u, __ATOMIC_RELAXED,
@@ -2671,7 +2683,6 @@ __device__ int gopen_id(const gfs_dev* d, int file_id, int flags) {
         ps->used = 0;
       }
     }
-    for (int c = 0; c < GFS_C_COUNT; ++c) bs->ctr[c] = 0;
     bs->pull = 0;
     bs->trig = 0;
     bs->par = 0;
@@ -2679,7 +2690,7 @@ __device__ int gopen_id(const gfs_dev* d, int file_id, int flags) {
     bs->a_pending = 0;   /* an asynchronous request is finished by gclose, before the next gopen */
     bs->open_result = v;
     bs->open_fd = v;
-    bs->open_size = v >= 0 ? gfsd::H(d)->files[v].size : 0;
+    bs->open_size = v >= 0 ? size : 0;
   }
   __syncthreads();
   const int v = bs->open_result;
@@ -2712,22 +2723,27 @@ __device__ int gclose(const gfs_dev* d, int fd) {
   if (fd < 0 || (uint32_t)fd >= gfsd::H(d)->max_files) return -gfsd::kEBADF;
   gfsd::BlockState* bs = gfsd::block_state();
   /* an asynchronous request still outstanding is pulled in before the block lets go */
-  (void)gfsd::async_finish_block(d, bs);
   __syncthreads();
-  if (gfsd::thread_id() == 0) {
-    __hip_atomic_fetch_sub(gfsd::G(&gfsd::H(d)->files[fd].handles), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (gfsd::H(d)->policy == GFS_POLICY_PRIVATE && bs->pslot >= 0) {
+  if (bs->a_pending) (void)gfsd::async_finish_block(d, bs);
+  if (gfsd::H(d)->policy == GFS_POLICY_PRIVATE) {
+    if (gfsd::thread_id() == 0 && bs->pslot >= 0) {
       gfs_pslot* ps = &gfsd::H(d)->pslots[bs->pslot];
-      bs->ctr[GFS_C_PB_WASTED] += ps->n - ps->used;   /* the private buffer is dropped */
+      gfsd::bcount(bs, GFS_C_PB_WASTED, ps->n - ps->used);   /* the private buffer is dropped */
       ps->n = 0;
       ps->used = 0;
       __hip_atomic_store(gfsd::G(&ps->owner), 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
       bs->pslot = -1;
     }
-    for (int c = 0; c < GFS_C_COUNT; ++c) {
-      if (bs->ctr[c]) gfsd::fadd64(&gfsd::H(d)->g->ctr[c], bs->ctr[c]);
-      bs->ctr[c] = 0;
-    }
+    __syncthreads();
+  }
+  /* a counter a thread */
+  for (uint32_t c = gfsd::thread_id(); c < GFS_C_COUNT; c += gfsd::block_threads()) {
+    const uint64_t v = bs->ctr[c];
+    if (v) gfsd::fadd64(&gfsd::H(d)->g->ctr[c], v);
+    bs->ctr[c] = 0;
+  }
+  if (gfsd::thread_id() == 0) {
+    __hip_atomic_fetch_sub(gfsd::G(&gfsd::H(d)->files[fd].handles), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bs->open_fd = -1;
   }
   __syncthreads();

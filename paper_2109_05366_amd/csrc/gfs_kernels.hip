@@ -57,6 +57,8 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) list_reader_kernel(c
   const uint32_t b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   uint8_t* mybuf = buf + (uint64_t)b * read_size;
   if (consumer == 1) histogram_clear(hist, tid, nt);
+  // the first 64 read offsets, in flight while the file is opened
+  const uint64_t off0 = tid < 64 && tid < reads ? offsets[(uint64_t)b * reads + tid] : 0;
   __syncthreads();
   const int fd = gopen_id(d, file_id, GFS_O_RDONLY);
   int64_t err = fd < 0 ? fd : 0;
@@ -67,7 +69,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) list_reader_kernel(c
     if ((k & 63) == 0) {
       // one round trip for the next 64 offsets instead of one before every read (every thread
       // has passed gread's barriers since it read the previous ones)
-      if (tid < 64 && k + tid < reads) offs[tid] = offsets[(uint64_t)b * reads + k + tid];
+      if (tid < 64 && k + tid < reads) offs[tid] = k == 0 ? off0 : offsets[(uint64_t)b * reads + k + tid];
       __syncthreads();
     }
     const uint64_t my_turn = (uint64_t)k * gridDim.x + b;
