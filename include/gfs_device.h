@@ -481,80 +481,110 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
 }
 
 /* ------------------------------------------------------------------ per-file miss lock
- * A FIFO ticket lock whose waiters can leave the queue. Blocks get the lock in ticket
- * order, which keeps the readers of a file together (an unfair lock lets a few blocks run
- * far ahead and spreads the misses over the whole file). Each ticket has a 64-bit queue
- * slot (GFS_LOCK_SLOTS per file, more than the blocks the device can hold at once). A
- * waiter announces the page it missed in its slot ("waiting n, page"); the holder passes
- * the lock by writing "granted n" into the slot of ticket n. A waiter whose page appears
- * in the table while it waits (another block's window covered it) writes "left n" instead,
- * by compare-and-swap against the grant, and goes to the pin path. A holder that has just
- * claimed a window marks the waiters right behind it whose pages lie in that window
- * "covered n" (their pages are about to be reserved, so the lock has nothing to decide for
- * them) and passes the lock to the first ticket that is neither left nor covered. Ticket 0
- * of a cold file holds the lock at once. The low word of every slot value carries the
- * ticket, so stale values of earlier tickets never match. */
+ * A FIFO ticket lock whose waiters can leave the queue, and whose holder decides for the
+ * waiters behind it. Blocks get the lock in ticket order, which keeps the readers of a file
+ * together (an unfair lock lets a few blocks run far ahead and spreads the misses over the
+ * whole file). Each ticket has a 64-bit queue slot and a 64-bit note beside it (GFS_LOCK_SLOTS
+ * per file, more than the blocks the device can hold at once). A waiter writes what the
+ * detector needs of its miss into the note and then announces the page in its slot
+ * ("waiting n, page"); the holder passes the lock by writing "granted n" into the slot of
+ * ticket n. A waiter whose page appears in the table while it waits (another block's window
+ * covered it) writes "left n" instead, by compare-and-swap against the grant, and goes to the
+ * pin path. A holder that has just claimed windows marks the waiters right behind it whose
+ * pages lie in them "covered n" (their pages are about to be reserved, so the lock has nothing
+ * to decide for them) and passes the lock to the first ticket that is neither left nor covered.
+ * Ticket 0 of a cold file holds the lock at once. The low word of every slot value carries the
+ * ticket, so stale values of earlier tickets never match.
+ *
+ * Deciding for others: what a decision costs under the lock is round trips to memory (state,
+ * table probe, write-back, hand-off), not the decision, which is a few hundred nanoseconds in
+ * registers. So the holder takes up to GFS_LOCK_BATCH - 1 waiters right behind it along: it
+ * turns their slots from "waiting" to "taken" (a waiter can no longer leave then) while the
+ * table probes for all their pages are in flight, decides for each in ticket order on the
+ * state it holds, exactly as if each had held the lock in turn, claims their windows, writes
+ * state and claims back once, and leaves each its outcome in its slot ("decided n, window" or
+ * "covered n"). LOCK_FIGURES */
 
-enum { LOCK_OWN = 0, LOCK_LEFT = 1, LOCK_TIMEOUT = 2, LOCK_COVERED = 3 };
+enum { LOCK_OWN = 0, LOCK_LEFT = 1, LOCK_TIMEOUT = 2, LOCK_COVERED = 3, LOCK_DECIDED = 4 };
 
+constexpr uint32_t kNoPage = 0x7fffffffu;   /* announced by a waiter that has no page: it must hold the lock itself */
 __device__ __forceinline__ uint64_t lock_granted(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 1u); }
 __device__ __forceinline__ uint64_t lock_left(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 2u); }
 __device__ __forceinline__ uint64_t lock_covered(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 3u); }
 __device__ __forceinline__ uint64_t lock_waiting(uint64_t n, uint64_t page) {
   return (1ull << 63) | (page << 32) | (uint64_t)((uint32_t)n << 2);
 }
-__device__ __forceinline__ uint64_t* lock_slot(const gfs_dev* d, uint32_t file, uint64_t n) {
-  return H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS + (n & (GFS_LOCK_SLOTS - 1));
+__device__ __forceinline__ uint64_t lock_taken(uint64_t n) { return (1ull << 62) | (uint64_t)((uint32_t)n << 2); }
+/* decided: the claimed window [page - below, page + above) in claim slot `claim`; marked: the page
+   after the demanded one is its stream's marker */
+__device__ __forceinline__ uint64_t lock_decided(uint64_t n, uint32_t below, uint32_t above, uint32_t claim, bool marked) {
+  const uint32_t w = below | (above << 10) | (claim << 21) | (marked ? 1u << 25 : 0u);
+  return (1ull << 62) | ((uint64_t)w << 32) | lock_covered(n);
+}
+static_assert(GFS_MAX_WINDOW_PAGES <= 1024 && GFS_CLAIMS <= 16, "a window's extent and claim slot fit lock_decided");
+/* a miss as its waiter notes it: pages of the read from the missed one on, cached history behind
+   it, the block (for the trace) */
+__device__ __forceinline__ uint64_t lock_note(uint32_t req, uint32_t hist, uint32_t bid) {
+  return (uint64_t)(req < 0xffffffu ? req : 0xffffffu) | ((uint64_t)(hist & 0xfffu) << 24) | ((uint64_t)bid << 36);
+}
+/* a ticket's slot; its note is the word after it. lq: the file's slots */
+__device__ __forceinline__ uint64_t* lock_slot(uint64_t* lq, uint64_t n) {
+  return lq + 2 * (n & (GFS_LOCK_SLOTS - 1));
+}
+__device__ __forceinline__ uint64_t* lock_queue(const gfs_dev* d, uint32_t file) {
+  return H(d)->lockq + (uint64_t)file * (2 * GFS_LOCK_SLOTS);
 }
 
-/* Lane 0: leave the queue if ticket t is not granted yet; true if it is out of the queue
-   (left, or marked covered by the holder), false if the lock was granted meanwhile (then
-   the caller holds it). */
-__device__ bool lock_try_leave_lane(const gfs_dev* d, uint32_t file, uint64_t t) {
-  uint64_t* sl = lock_slot(d, file, t);
-  uint64_t v = __hip_atomic_load(G(sl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  while (v != lock_granted(t)) {
-    if (v == lock_covered(t)) return true;
-    if (__hip_atomic_compare_exchange_strong(G(sl), &v, lock_left(t), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT))
-      return true;
+/* Lane 0: leave the queue if ticket t has no grant or outcome yet; true if it left, false if its
+   slot says something else by now, or soon will (taken): the caller goes on polling. */
+__device__ bool lock_try_leave_lane(uint64_t* sl, uint64_t t) {
+  uint64_t v = ld_rlx(sl);
+  while (v != lock_granted(t) && v != lock_taken(t) && (uint32_t)v != (uint32_t)lock_covered(t)) {
+    if (cas64_rlx(sl, v, lock_left(t))) return true;
   }
   return false;
 }
 
-/* Wave-collective. Waits for the file's miss lock for page `page` (key `key`); while
- * waiting, looks up `key` in the table now and then and leaves the queue if it appeared.
- * Returns the ticket << 2 | LOCK_OWN, LOCK_LEFT, LOCK_COVERED (the holder's window covers the
+/* Wave-collective. Waits for the file's miss lock for page `page` (key `key`), or for the
+ * holder's decision for it; while waiting, looks up `key` in the table now and then and leaves
+ * the queue if it appeared. Returns value << 3 | LOCK_OWN (value: the ticket), LOCK_DECIDED
+ * (value: the window, see lock_decided), LOCK_LEFT, LOCK_COVERED (a holder's window covers the
  * page) or LOCK_TIMEOUT (left the queue after the wait timeout): in registers, as a result
  * through memory would be loaded back with the lock held. */
 __device__ __attribute__((noinline)) uint64_t lock_file_wave(const gfs_dev* d, uint32_t file, uint64_t key,
-                                                             uint64_t page, uint64_t t0, bool may_leave = true) {
+                                                             uint64_t page, uint64_t note, uint64_t t0,
+                                                             bool may_leave = true) {
   d = uniform(d);
+  uint64_t* const lq = lock_queue(d, file);
   uint64_t t = 0;
   if (lane() == 0)
     t = __hip_atomic_fetch_add(G(&H(d)->locks[file].next), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   t = __shfl(t, 0, 64);
+  uint64_t value = t;
   int res = LOCK_OWN;
   if (t != 0) {
-    uint64_t* sl = lock_slot(d, file, t);
-    /* announce the page, unless the grant is already there */
+    uint64_t* sl = lock_slot(lq, t);
+    /* announce the miss, unless the grant is already there */
     int own = 0;
     if (lane() == 0) {
-      uint64_t v = __hip_atomic_load(G(sl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      while (v != lock_granted(t)) {
-        if (__hip_atomic_compare_exchange_strong(G(sl), &v, lock_waiting(t, page), __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-          break;
+      uint64_t v = ld_rlx(sl);
+      if (v != lock_granted(t)) {
+        st_rlx(sl + 1, note);
+        drain_atomics();   /* the note is there before the slot says so */
+        while (v != lock_granted(t)) {
+          if (cas64_rlx(sl, v, lock_waiting(t, page))) break;
+        }
       }
       own = v == lock_granted(t) ? 1 : 0;
     }
     own = __shfl(own, 0, 64);
     for (uint32_t n = 0; !own; ++n) {
       int st = -1;   /* -1: keep waiting */
+      uint64_t v = 0;
       if (lane() == 0) {
-        const uint64_t v = __hip_atomic_load(G(sl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = ld_rlx(sl);
         if (v == lock_granted(t)) st = LOCK_OWN;
-        else if (v == lock_covered(t)) st = LOCK_COVERED;
+        else if ((uint32_t)v == (uint32_t)lock_covered(t)) st = (v >> 62) ? LOCK_DECIDED : LOCK_COVERED;
       }
       st = __shfl(st, 0, 64);
       if (st < 0 && (n & 7) == 7) {
@@ -563,13 +593,14 @@ __device__ __attribute__((noinline)) uint64_t lock_file_wave(const gfs_dev* d, u
         const bool late = expired(d, t0);
         if (present || late) {
           int out = 0;
-          if (lane() == 0) out = lock_try_leave_lane(d, file, t) ? 1 : 0;
+          if (lane() == 0) out = lock_try_leave_lane(sl, t) ? 1 : 0;
           out = __shfl(out, 0, 64);
-          st = out ? (present ? LOCK_LEFT : LOCK_TIMEOUT) : LOCK_OWN;
+          if (out) st = present ? LOCK_LEFT : LOCK_TIMEOUT;
         }
       }
       if (st >= 0) {
         res = st;
+        if (st == LOCK_DECIDED) value = __shfl(v, 0, 64) >> 32;
         break;
       }
       if (lane() == 0) {
@@ -579,39 +610,46 @@ __device__ __attribute__((noinline)) uint64_t lock_file_wave(const gfs_dev* d, u
     }
   }
   drain_atomics();
-  return (t << 2) | (uint64_t)res;
+  return (value << 3) | (uint64_t)res;
 }
 
-/* Wave-collective: pass the lock to the first later ticket that is still waiting for it
- * and whose page is outside [lo, hi). Without a window the next ticket gets the grant by
- * one exchange, and only if that waiter had left does the wave read the following slots,
- * 64 at a time, for the first ticket still in the queue. With a window the wave reads the
- * slots first: tickets that left or were marked covered are passed over, waiting tickets
- * whose announced page lies in the window are marked covered (a compare-and-swap that
- * loses only to the waiter leaving), and the first other ticket gets the grant; if that
- * waiter left just before the exchange, the scan goes on after it. A ticket that has not
- * announced its page yet is granted the lock like any other. */
-/* lq: the file's queue slots, ticket n in lq[n mod GFS_LOCK_SLOTS] */
-__device__ __attribute__((noinline)) void unlock_slots_wave(uint64_t* lq, uint64_t ticket, uint64_t lo, uint64_t hi, bool has_pre,
-                                  uint64_t pre) {
-  drain_atomics();
+/* Wave-collective: pass the lock to the first ticket from n on that is still waiting for it and
+ * whose page is in none of the windows the holder has claimed: lane i's [lo, hi) for the set bits
+ * i of `claimed`. Without a window ticket n gets the grant by one exchange, and only if that
+ * waiter had left does the wave read the following slots, 64 at a time, for the first ticket
+ * still in the queue. With windows the wave looks at the slots first: tickets that left or were
+ * marked covered are passed over, waiting tickets whose announced page lies in a window are
+ * marked covered (a compare-and-swap that loses only to the waiter leaving), and the first other
+ * ticket gets the grant; if that waiter left just before the exchange, the scan goes on after it.
+ * A ticket that has not announced its page yet is granted the lock like any other. has_pre: lane
+ * l's `pre` is the value of ticket n + l's slot, read earlier under the lock (0: not read), and
+ * the first look uses it instead of reading the slots again. Everything the next holder reads
+ * must have been performed before the call (drain_atomics). */
+__device__ __attribute__((noinline)) void unlock_slots_wave(uint64_t* lq, uint64_t n, uint64_t claimed, uint64_t lo,
+                                                            uint64_t hi, bool has_pre, uint64_t pre) {
   const uint32_t l = lane();
-  uint64_t n = ticket + 1;
-  bool look = hi > lo;
+  bool look = claimed != 0;
   while (true) {
     if (look) {
       const uint64_t nl = n + l;
-      uint64_t* sl = lq + (nl & (GFS_LOCK_SLOTS - 1));
-      uint64_t v = has_pre && n == ticket + 1 ? pre : ld_rlx(sl);
+      uint64_t* sl = lock_slot(lq, nl);
+      uint64_t v = has_pre ? pre : ld_rlx(sl);
+      has_pre = false;
       const uint64_t pg = (v >> 32) & 0x7fffffffull;
       const bool gone = v == lock_left(nl) || v == lock_covered(nl);
-      const bool cov = hi > lo && (v >> 63) && (uint32_t)v == ((uint32_t)nl << 2) && pg >= lo && pg < hi;
+      const bool waits = (v >> 63) && (uint32_t)v == ((uint32_t)nl << 2);
+      bool in = false;
+      for (uint64_t m = claimed; m; m &= m - 1) {
+        const int i = __builtin_ctzll(m);
+        const uint64_t wlo = __shfl(lo, i, 64), whi = __shfl(hi, i, 64);
+        in |= pg >= wlo && pg < whi;
+      }
+      const bool cov = waits && in;
       const uint64_t skip = __ballot(gone || cov);
       const uint32_t first = ~skip ? (uint32_t)__builtin_ctzll(~skip) : 64u;
       if (cov && l < first) {
         /* loses only to the waiter leaving, which takes it out of the queue as well */
-        (void)__hip_atomic_compare_exchange_strong(G(sl), &v, lock_covered(nl), __ATOMIC_RELAXED,
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        (void)cas64_rlx(sl, v, lock_covered(nl));
       }
       if (first == 64) {
         n += 64;
@@ -621,18 +659,18 @@ __device__ __attribute__((noinline)) void unlock_slots_wave(uint64_t* lq, uint64
     }
     uint64_t old = 0;
     if (l == 0)
-      old = __hip_atomic_exchange(G(lq + (n & (GFS_LOCK_SLOTS - 1))), lock_granted(n), __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
+      old = __hip_atomic_exchange(G(lock_slot(lq, n)), lock_granted(n), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     old = __shfl(old, 0, 64);
     if (old != lock_left(n)) return;
     ++n;   /* that waiter had left: look for the next one still in the queue */
     look = true;
   }
 }
-/* the same, given the file instead of its queue slots, which have not been read */
+/* the same for the holder of `ticket`, with one window or none (lo == hi), no slot read yet */
 __device__ __forceinline__ void unlock_file_wave(const gfs_dev* d, uint32_t file, uint64_t ticket, uint64_t lo,
                                                  uint64_t hi) {
-  unlock_slots_wave(H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS, ticket, lo, hi, false, 0);
+  drain_atomics();
+  unlock_slots_wave(lock_queue(d, file), ticket + 1, hi > lo ? 1 : 0, lo, hi, false, 0);
 }
 
 /* ------------------------------------------------------------------ readahead detector
@@ -677,9 +715,9 @@ __device__ __forceinline__ RaState ra_load_lane(gfs_file_dev* fe, uint32_t nrec,
 /* The values of a round of loads are used only from here on, after the caller's wait: without
    this the compiler put work on the first of them between the loads, and so a wait for a round
    trip before the last ones were issued. */
-__device__ __forceinline__ void ra_loaded(RaState& st, uint64_t& a, uint64_t& b) {
+__device__ __forceinline__ void ra_loaded(RaState& st, uint64_t& a, uint64_t& b, uint64_t& c) {
   asm volatile("" : "+v"(st.advice), "+v"(st.clk), "+v"(st.rn), "+v"(st.r), "+v"(st.s_next), "+v"(st.s_size),
-               "+v"(st.s_last), "+v"(st.s_valid), "+v"(st.s_marker), "+v"(a), "+v"(b));
+               "+v"(st.s_last), "+v"(st.s_valid), "+v"(st.s_marker), "+v"(a), "+v"(b), "+v"(c));
 }
 
 /* Which rule decided a window (GFS_RA_RULE_*, recorded in the trace with the detector's inputs). */
@@ -741,53 +779,47 @@ __device__ __attribute__((noinline)) uint32_t ra_history_wave(const gfs_dev* d, 
   return h < hmax ? h : hmax;
 }
 
-__device__ void ra_decide_wave(gfs_file_dev* fe, uint64_t p, uint32_t req, uint32_t hist,
-                               const RaParams& rp, const RaState& st, uint64_t& ws, uint32_t& wn, uint32_t& near_out,
-                               uint32_t& h_out, uint32_t& rule_out, int& slot_out) {
-  const uint32_t advice = st.advice;
+/* The decision, on the state in st, which it advances (clock, recent misses, the stream it
+   uses); `dirty` gets this lane's parts of the state that changed: 1 recent miss, 2 stream. */
+__device__ __forceinline__ void ra_decide_wave(uint64_t p, uint32_t req, uint32_t hist, const RaParams& rp, RaState& st,
+                                               uint32_t& dirty, uint64_t& ws, uint32_t& wn, uint32_t& near_out,
+                                               uint32_t& h_out, uint32_t& rule_out, int& slot_out) {
   ws = p;
   wn = 1;
   near_out = 0;
   h_out = 0;
   rule_out = RA_RULE_OFF;
   slot_out = -1;
-  if (rp.cap == 0 || advice == GFS_ADV_RANDOM) return;
+  if (rp.cap == 0 || __builtin_amdgcn_readfirstlane(st.advice) == GFS_ADV_RANDOM) return;
   const uint32_t l = lane();
   const uint32_t cap = rp.cap;
-  const uint32_t nrec = rp.nrec;
-  uint32_t clk = st.clk;
-  const uint32_t rn = st.rn;
-  const uint64_t r = st.r;
-  const uint64_t s_next = st.s_next;
-  const uint32_t s_size = st.s_size, s_last = st.s_last, s_valid = st.s_valid;
-  clk = __shfl(clk, 0, 64) + 1;
   /* how many of the file's last misses lie near p; then remember p */
   const uint64_t radius = rp.radius;
-  const bool near_l = l < nrec && l < rn && r + radius >= p && r <= p + radius;
+  const bool near_l = l < rp.nrec && l < st.rn && st.r + radius >= p && st.r <= p + radius;
   const uint32_t near = (uint32_t)__popcll(__ballot(near_l));
   near_out = near;
-  if (l == 0) {
-    st_rlx32(&fe->clock, clk);
-    st_rlx(&fe->recent[rn % nrec], p);
-    st_rlx32(&fe->recent_n, rn + 1);
+  st.clk += 1;
+  if (l == st.rn % rp.nrec) {
+    st.r = p;
+    dirty |= 1u;
   }
-  const bool cov = l < rp.nstreams && s_valid && s_next <= p && p < s_next + s_size;
-  const uint64_t cm = __ballot(cov);
+  st.rn += 1;
+  const uint64_t cm = __ballot(l < rp.nstreams && st.s_valid && st.s_next <= p && p < st.s_next + st.s_size);
   int j;
   if (cm) {
     /* p is inside a stream's zone: double that stream's window from its frontier */
-    j = __ffsll((unsigned long long)cm) - 1;
-    const uint64_t nx = __shfl(s_next, j, 64);
-    const uint32_t sz = __shfl(s_size, j, 64);
-    ws = nx;
+    j = __builtin_ctzll(cm);
+    ws = __shfl(st.s_next, j, 64);
+    const uint32_t sz = __builtin_amdgcn_readlane(st.s_size, j);
     wn = 2 * sz < cap ? 2 * sz : cap;
+    if (p >= ws + wn) ws = p;   /* a zone left by a launch with a larger cap: the window must hold p */
     rule_out = RA_RULE_ZONE;
   } else {
-    const uint64_t inv = __ballot(l < rp.nstreams && !s_valid);
+    const uint64_t inv = __ballot(l < rp.nstreams && !st.s_valid);
     if (inv) {
-      j = __ffsll((unsigned long long)inv) - 1;
+      j = __builtin_ctzll(inv);
     } else {
-      uint64_t k = l < rp.nstreams ? (((uint64_t)s_last << 8) | l) : ~0ull;
+      uint64_t k = l < rp.nstreams ? (((uint64_t)st.s_last << 8) | l) : ~0ull;
       for (int off = GFS_MAX_STREAMS / 2; off > 0; off >>= 1) {
         const uint64_t o = __shfl_xor(k, off, 64);
         k = o < k ? o : k;
@@ -814,7 +846,7 @@ __device__ void ra_decide_wave(gfs_file_dev* fe, uint64_t p, uint32_t req, uint3
         w0 = 2 * h;
         rule_out = RA_RULE_CONTEXT;
       } else {
-        w0 = (p == 0 || advice == GFS_ADV_SEQUENTIAL) ? rp.init : 1u;
+        w0 = (p == 0 || st.advice == GFS_ADV_SEQUENTIAL) ? rp.init : 1u;
         rule_out = RA_RULE_NEW;
       }
       if (w0 < r) w0 = r;
@@ -825,14 +857,31 @@ __device__ void ra_decide_wave(gfs_file_dev* fe, uint64_t p, uint32_t req, uint3
       h_out = h;
     }
   }
-  if (l == 0) {
-    gfs_stream* s = &fe->streams[j];
-    st_rlx(&s->next, ws + wn);
-    st_rlx32(&s->size, wn);
-    st_rlx32(&s->last_use, clk);
-    st_rlx32(&s->valid, 1u);
+  if ((int)l == j) {
+    st.s_next = ws + wn;
+    st.s_size = wn;
+    st.s_last = st.clk;
+    st.s_valid = 1u;
+    dirty |= 2u;
   }
   slot_out = j;
+}
+/* Write back what decisions changed. */
+__device__ __forceinline__ void ra_store_lane(gfs_file_dev* fe, const RaState& st, uint32_t dirty, bool async_on) {
+  const uint32_t l = lane();
+  if (dirty & 1u) st_rlx(&fe->recent[l], st.r);
+  if (dirty & 2u) {
+    gfs_stream* sp = &fe->streams[l];
+    st_rlx(&sp->next, st.s_next);
+    st_rlx32(&sp->size, st.s_size);
+    st_rlx32(&sp->last_use, st.s_last);
+    st_rlx32(&sp->valid, st.s_valid);
+    if (async_on) st_rlx32(&sp->marker, st.s_marker);
+  }
+  if (l == 0) {
+    st_rlx32(&fe->clock, st.clk);
+    st_rlx32(&fe->recent_n, st.rn);
+  }
 }
 
 /* ------------------------------------------------------------------ clock allocation
@@ -1595,33 +1644,25 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
      grant's acquire, each would be a load from memory on the path every waiter waits on */
   gfs_file_dev* const fe = &H(d)->files[file];
   uint64_t* const clp = H(d)->claims[file].e;
-  uint64_t* const lq = H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS;
+  uint64_t* const lq = lock_queue(d, file);
   const uint64_t npages = fe->npages;
-  /* the table entry this lane looks at (lanes 32-63 repeat) */
-  uint64_t* pslot;
-  {
-    uint32_t b1, b2;
-    key_buckets_m(H(d)->nbuckets_mask, key, b1, b2);
-    pslot = H(d)->pt + (uint64_t)((l & GFS_BUCKET_SLOTS) ? b2 : b1) * GFS_BUCKET_SLOTS + (l & 15);
-    asm volatile("" : "+v"(pslot));   /* computed here, not with the lock held */
-  }
+  uint64_t* const pt = H(d)->pt;
+  const uint32_t ptmask = H(d)->nbuckets_mask;
   const bool tracing = H(d)->trace_level >= 1;
   const bool async_on = H(d)->ra_async != 0;
   const uint64_t tl0 = wall_clock64();
-  const uint64_t lr = lock_file_wave(d, file, key, p, t0);
-  const int lk = (int)(lr & 3);
-  const uint64_t ticket = lr >> 2;
+  const uint64_t lr = lock_file_wave(d, file, key, p, lock_note(req, hist_pre, bid), t0);
+  const int lk = (int)(lr & 7);
   const uint64_t tl1 = wall_clock64();
-  if (lk != LOCK_OWN && l == 0) bcount(bs, GFS_T_LOCK, tl1 - tl0);
-  if (lk == LOCK_TIMEOUT) return 2;
-  if (lk == LOCK_LEFT) {
-    if (l == 0) bcount(bs, GFS_C_LOCK_LEFT, 1);
-    return 1;   /* the page was reserved while this block waited: go to the pin path */
+  if (lk != LOCK_OWN && l == 0) {
+    bcount(bs, GFS_T_LOCK, tl1 - tl0);
+    bcount(bs, lk == LOCK_DECIDED ? GFS_C_LOCKS : GFS_C_LOCK_LEFT, lk == LOCK_TIMEOUT ? 0 : 1);
   }
+  if (lk == LOCK_TIMEOUT) return 2;
+  if (lk == LOCK_LEFT) return 1;   /* the page was reserved while this block waited: go to the pin path */
   if (lk == LOCK_COVERED) {
-    /* the holder's window covers the page: wait until its reservation shows in the
+    /* a holder's window covers the page: wait until its reservation shows in the
        table or no running claim covers the page any more, then look again */
-    if (l == 0) bcount(bs, GFS_C_LOCK_LEFT, 1);
     uint32_t nw = 0;
     while (pt_lookup_wave(d, key) < 0 && !expired(d, t0)) {
       uint64_t cl = 0;
@@ -1633,82 +1674,189 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     acquire_agent();   /* the reservations, published before the claim was cleared */
     return 1;
   }
-  /* every block waiting on this file's lock waits for this wave: let it issue first, and keep
-     the statistics until the lock is passed on */
-  __builtin_amdgcn_s_setprio(3);
-  /* one round: the detector state and the file's window claims; then, ordered after the
-     claims, the table probe (a claim cleared after its reservations means they show) */
-  RaState ras = ra_load_lane(fe, rp.nrec, rp.nstreams);
-  uint64_t cl = ld_rlx(&clp[l & (GFS_CLAIMS - 1)]);
-  /* the queue slots behind this ticket, read now for the hand-off: a waiter that arrives or
-     leaves after this read is handled by the grant's exchange (it returns what the slot
-     holds), and a stale "waiting" value only makes the covered mark's compare-and-swap fail */
-  uint64_t qv = ld_rlx(lq + ((ticket + 1 + l) & (GFS_LOCK_SLOTS - 1)));
-  drain_atomics();   /* the table probe below goes out after the claims were read */
-  ra_loaded(ras, cl, qv);
-  const bool cl_on = l < GFS_CLAIMS && (cl & 1ull);
-  const uint64_t cl_lo = cl >> 32, cl_hi = (cl >> 32) + ((cl & 0xffffffffull) >> 1);
-  const bool covered = __ballot(cl_on && cl_lo <= p && p < cl_hi) != 0;
-  const uint64_t free_cl = __ballot(l < GFS_CLAIMS && !cl_on);
-  const bool present = __ballot(l < 2 * GFS_BUCKET_SLOTS && (ld_rlx(pslot) >> GFS_ENTRY_FRAME_BITS) == key) != 0;
-  if (present || covered || free_cl == 0) {
-    /* filled, reserved, or about to be reserved by a window being claimed: go to the pin
-       path (after a nap if the claim is still running) */
-    unlock_slots_wave(lq, ticket, 0, 0, false, 0);
+  uint64_t cws, cwe, mark = ~0ull;
+  uint64_t* claim;
+  uint64_t tl2 = tl1;
+  if (lk == LOCK_DECIDED) {
+    const uint32_t w = (uint32_t)(lr >> 3);
+    cws = p - (w & 0x3ffu);
+    cwe = p + ((w >> 10) & 0x7ffu);
+    claim = &clp[(w >> 21) & 15u];
+    if ((w >> 25) & 1u) mark = p + 1;
+  } else {
+    const uint64_t ticket = lr >> 3;
+    /* every block waiting on this file's lock waits for this wave: let it issue first, and
+       keep the statistics until the lock is passed on */
+    __builtin_amdgcn_s_setprio(3);
+    /* one round: the detector state, the file's window claims, and the queue slots and notes
+       behind this ticket (a waiter that arrives or leaves after this read is handled by the
+       compare-and-swaps and the grant's exchange) */
+    RaState ras = ra_load_lane(fe, rp.nrec, rp.nstreams);
+    uint64_t cl = ld_rlx(&clp[l & (GFS_CLAIMS - 1)]);
+    const uint64_t nl = ticket + 1 + l;
+    uint64_t qv = ld_rlx(lock_slot(lq, nl));
+    uint64_t qn = ld_rlx(lock_slot(lq, nl) + 1);
+    drain_atomics();   /* the table probes below go out after the claims were read */
+    ra_loaded(ras, cl, qv, qn);
+    bool cl_on = l < GFS_CLAIMS && (cl & 1ull);
+    uint64_t cl_lo = cl >> 32, cl_hi = (cl >> 32) + ((cl & 0xffffffffull) >> 1);
+    uint64_t free_cl = __ballot(l < GFS_CLAIMS && !cl_on);
+    /* the waiters right behind that can be decided for: announced, with a page, and as many as
+       there are free claims left beside this block's own */
+    const bool gone = qv == lock_left(nl) || (uint32_t)qv == (uint32_t)lock_covered(nl);
+    const bool waits = (qv >> 63) && (uint32_t)qv == ((uint32_t)nl << 2) && (uint32_t)(qv >> 32) != (0x80000000u | kNoPage);
+    const uint64_t stop = __ballot(!gone && !waits);
+    uint32_t end = stop ? (uint32_t)__builtin_ctzll(stop) : 64u;   /* slots looked at: [0, end) */
+    const uint32_t nfree = (uint32_t)__popcll(free_cl);
+    const uint32_t room = nfree ? (nfree - 1 < GFS_LOCK_BATCH - 1 ? nfree - 1 : GFS_LOCK_BATCH - 1) : 0u;
+    uint64_t cand = __ballot(waits) & (end == 64 ? ~0ull : (1ull << end) - 1);
+    {
+      uint64_t m = cand;
+      for (uint32_t k = 0; k < room && m; ++k) m &= m - 1;
+      if (m) {   /* more than there is room for: the first of the rest gets the lock */
+        end = (uint32_t)__builtin_ctzll(m);
+        cand &= (1ull << end) - 1;
+      }
+    }
+    /* take them, and probe the table for all the pages, in one round: items 0 (this block) and
+       1.. (the candidates in order), two a half wave each */
+    uint64_t held = 0;
+    bool took = false;
+    if ((cand >> l) & 1) {
+      uint64_t v = qv;
+      took = cas64_rlx(lock_slot(lq, nl), v, lock_taken(nl));
+    }
+    const uint32_t nitems = 1 + (uint32_t)__popcll(cand);
+    {
+      uint64_t e[GFS_LOCK_BATCH / 2], k[GFS_LOCK_BATCH / 2];
+      uint64_t m = cand;
+#pragma unroll
+      for (uint32_t u = 0; u < GFS_LOCK_BATCH / 2; ++u) {
+        e[u] = 0;
+        k[u] = ~0ull;
+        if (2 * u >= nitems) continue;
+        uint64_t pa = p, pb = p;
+        if (u) {
+          pa = (uint32_t)__builtin_amdgcn_readlane((int)(qv >> 32), __builtin_ctzll(m)) & 0x7fffffffu;
+          m &= m - 1;
+        }
+        const bool second = 2 * u + 1 < nitems;
+        if (second) {
+          pb = (uint32_t)__builtin_amdgcn_readlane((int)(qv >> 32), __builtin_ctzll(m)) & 0x7fffffffu;
+          m &= m - 1;
+        }
+        k[u] = page_key(file, l < 32 ? pa : pb);
+        uint32_t b1, b2;
+        key_buckets_m(ptmask, k[u], b1, b2);
+        e[u] = ld_rlx(pt + (uint64_t)((l & GFS_BUCKET_SLOTS) ? b2 : b1) * GFS_BUCKET_SLOTS + (l & 15));
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < GFS_LOCK_BATCH / 2; ++u) {
+        const uint64_t m2 = __ballot((e[u] >> GFS_ENTRY_FRAME_BITS) == k[u]);
+        held |= ((uint32_t)m2 ? 1ull : 0ull) << (2 * u) | ((m2 >> 32) ? 2ull : 0ull) << (2 * u);
+      }
+    }
+    const uint64_t taken = __ballot(took);
+    /* decide in ticket order */
+    const uint64_t td0 = wall_clock64();
+    uint32_t dirty = 0, ndec = 0;
+    uint64_t claimed = 0, outv = 0;
+    uint32_t own = 0;   /* 0: look again at once, 1: a running claim holds the page, 2: decided */
+    uint64_t own_a = 0, own_b = 0;
+    uint32_t own_cj = 0;
+    uint64_t m = cand;
+    for (uint32_t it = 0; it < nitems; ++it) {
+      uint32_t at = 0;
+      uint64_t ip = p;
+      uint32_t ireq = req, ihist = hist_pre, ibid = bid;
+      if (it) {
+        at = (uint32_t)__builtin_ctzll(m);
+        m &= m - 1;
+        if (((taken >> at) & 1) == 0) continue;   /* it left */
+        ip = (uint32_t)__builtin_amdgcn_readlane((int)(qv >> 32), (int)at) & 0x7fffffffu;
+        const uint32_t n0 = (uint32_t)__builtin_amdgcn_readlane((int)qn, (int)at);
+        const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane((int)(qn >> 32), (int)at);
+        ireq = n0 & 0xffffffu;
+        ihist = (n0 >> 24) | ((n1 & 0xfu) << 8);
+        ibid = n1 >> 4;
+      }
+      const bool covered = __ballot(cl_on && cl_lo <= ip && ip < cl_hi) != 0;
+      const bool present = ((held >> it) & 1) != 0;
+      uint64_t o = lock_covered(ticket + 1 + at);
+      if (!present && !covered && free_cl) {
+        /* a miss: decide the window, clip it to the file and out of running claims, claim it */
+        uint64_t ws;
+        uint32_t wn, near, hist, rule;
+        int rslot;
+        ra_decide_wave(ip, ireq, ihist, rp, ras, dirty, ws, wn, near, hist, rule, rslot);
+        if (ws + wn > npages) wn = (uint32_t)(npages - ws);
+        /* asynchronous readahead: the page after the demanded one is the stream's marker */
+        const bool marked = async_on && rslot >= 0 && ip + 1 < ws + wn;
+        if (async_on && (int)l == rslot) ras.s_marker = marked ? (uint32_t)(ip + 1) : GFS_NO_MARKER;
+        if (tracing && l == 0)
+          trace_ev(d, 1, GFS_EV_MISS, ibid, file, (uint32_t)ip, (near & 0xffu) | (hist << 8) | (rule << 24), wn,
+                   ws | ((uint64_t)ireq << 32));
+        uint64_t a = ws, b = ws + wn;
+        for (uint64_t c = __ballot(cl_on); c; c &= c - 1) {
+          const int i = __builtin_ctzll(c);
+          const uint64_t clo = __shfl(cl_lo, i, 64), chi = __shfl(cl_hi, i, 64);
+          if (chi <= ip) a = a > chi ? a : chi;
+          else b = b < clo ? b : clo;   /* no running claim holds ip, so this one lies above it */
+        }
+        const uint32_t cj = (uint32_t)__builtin_ctzll(free_cl);
+        free_cl &= free_cl - 1;
+        claimed |= 1ull << cj;
+        if (l == cj) {
+          cl_on = true;
+          cl_lo = a;
+          cl_hi = b;
+        }
+        ++ndec;
+        if (it == 0) {
+          own = 2;
+          own_a = a;
+          own_b = b;
+          own_cj = cj;
+          if (marked) mark = p + 1;
+        } else {
+          o = lock_decided(ticket + 1 + at, (uint32_t)(ip - a), (uint32_t)(b - ip), cj, marked);
+        }
+      } else if (it == 0) {
+        own = present ? 0u : 1u;
+      }
+      if (it && l == at) outv = o;
+    }
+    const uint64_t td1 = wall_clock64();
+    /* write back; the outcomes go out, and the lock is passed on, once that has been performed */
+    if (ndec) ra_store_lane(fe, ras, dirty, async_on);
+    if ((claimed >> l) & 1) st_rlx(&clp[l], (cl_lo << 32) | ((cl_hi - cl_lo) << 1) | 1ull);
+    const uint64_t tu0 = wall_clock64();
+    drain_atomics();
+    if (took) st_rlx(lock_slot(lq, nl), outv);
+    /* slots beyond the 64 read count as not announced */
+    const uint64_t pre = l + end < 64 ? __shfl(qv, (int)((l + end) & 63u), 64) : 0ull;
+    unlock_slots_wave(lq, ticket + 1 + end, claimed, cl_lo, cl_hi, true, pre);
     __builtin_amdgcn_s_setprio(0);
+    tl2 = wall_clock64();
     if (l == 0) {
       bcount(bs, GFS_T_LOCK, tl1 - tl0);
       bcount(bs, GFS_C_LOCKS, 1);
-      bcount(bs, GFS_T_CRIT, wall_clock64() - tl1);
+      bcount(bs, GFS_T_DECIDE, td1 - td0);
+      bcount(bs, GFS_T_CRIT, tl2 - tl1);
+      bcount(bs, GFS_T_UNLOCK, tl2 - tu0);
     }
-    if (!present) {
-      if (expired(d, t0)) return 2;
-      if (l == 0) nap(bs->naps);
+    if (own != 2) {
+      /* filled, reserved, or about to be reserved by a window being claimed: go to the pin
+         path (after a nap if the claim is still running) */
+      if (own == 1) {
+        if (expired(d, t0)) return 2;
+        if (l == 0) nap(bs->naps);
+      }
+      return 1;
     }
-    return 1;
-  }
-  /* miss: decide the window, clip it to stay out of running claims, claim it, unlock */
-  uint64_t ws;
-  uint32_t wn, near, hist, rule;
-  int rslot;
-  const uint64_t td0 = wall_clock64();
-  ra_decide_wave(fe, p, req, hist_pre, rp, ras, ws, wn, near, hist, rule, rslot);
-  const uint64_t td1 = wall_clock64();
-  if (ws + wn > npages) wn = (uint32_t)(npages - ws);
-  /* asynchronous readahead: the page after the demanded one is the stream's marker */
-  uint64_t mark = ~0ull;
-  if (async_on && rslot >= 0) {
-    mark = p + 1 < ws + wn ? p + 1 : ~0ull;
-    if (l == 0) st_rlx32(&fe->streams[rslot].marker, mark == ~0ull ? GFS_NO_MARKER : (uint32_t)mark);
-  }
-  if (tracing && l == 0)
-    trace_ev(d, 1, GFS_EV_MISS, bid, file, (uint32_t)p, (near & 0xffu) | (hist << 8) | (rule << 24), wn,
-             ws | ((uint64_t)req << 32));
-  uint64_t cws = ws, cwe = ws + wn;
-  {
-    uint64_t lo_b = cl_on && cl_hi <= p ? cl_hi : 0;
-    uint64_t hi_b = cl_on && cl_lo > p ? cl_lo : ~0ull;
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint64_t a = __shfl_xor(lo_b, off, 64), b = __shfl_xor(hi_b, off, 64);
-      lo_b = a > lo_b ? a : lo_b;
-      hi_b = b < hi_b ? b : hi_b;
-    }
-    cws = cws > lo_b ? cws : lo_b;
-    cwe = cwe < hi_b ? cwe : hi_b;
-  }
-  const uint32_t cj = (uint32_t)__builtin_ctzll(free_cl);
-  uint64_t* claim = &clp[cj];
-  if (l == 0) st_rlx(claim, (cws << 32) | ((cwe - cws) << 1) | 1ull);
-  const uint64_t tu0 = wall_clock64();
-  unlock_slots_wave(lq, ticket, cws, cwe, true, qv);
-  __builtin_amdgcn_s_setprio(0);
-  const uint64_t tl2 = wall_clock64();
-  if (l == 0) {
-    bcount(bs, GFS_T_LOCK, tl1 - tl0);
-    bcount(bs, GFS_C_LOCKS, 1);
-    bcount(bs, GFS_T_DECIDE, td1 - td0);
-    bcount(bs, GFS_T_CRIT, tl2 - tl1);
-    bcount(bs, GFS_T_UNLOCK, tl2 - tu0);
+    cws = own_a;
+    cwe = own_b;
+    claim = &clp[own_cj];
   }
   /* reserve the run of unmapped pages around p inside the claimed window */
   const uint32_t cwn = (uint32_t)(cwe - cws);
@@ -2171,10 +2319,10 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   aslot = __shfl(aslot, 0, 64);
   if (aslot < 0) return;
   const uint32_t s = (uint32_t)aslot;
-  /* the waiter announces no page of any window, so no holder marks it covered */
-  const uint64_t lk = lock_file_wave(d, file, 0, 0x7fffffffull, t0, false);
-  const uint64_t ticket = lk >> 2;
-  if ((lk & 3) != LOCK_OWN) {
+  /* the waiter announces no page, so no holder marks it covered or decides for it */
+  const uint64_t lk = lock_file_wave(d, file, 0, kNoPage, 0, t0, false);
+  const uint64_t ticket = lk >> 3;
+  if ((lk & 7) != LOCK_OWN) {
     if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
     return;
   }

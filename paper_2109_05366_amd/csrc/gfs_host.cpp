@@ -113,7 +113,7 @@ int make_layout(const gfs_config* c, Layout* L) {
   const uint64_t nf = c->max_files;
   L->off_files = o; o = align_up(o + sizeof(gfs_file_dev) * nf, kAlign);
   L->off_locks = o; o = align_up(o + sizeof(gfs_file_lock) * nf, kAlign);
-  L->off_lockq = o; o = align_up(o + 8ull * GFS_LOCK_SLOTS * nf, kAlign);
+  L->off_lockq = o; o = align_up(o + 16ull * GFS_LOCK_SLOTS * nf, kAlign);
   L->off_claims = o; o = align_up(o + sizeof(gfs_file_claims) * nf, kAlign);
   L->off_shadow = o; o = align_up(o + (uint64_t)(GFS_SHADOW_PAGES / 8) * nf, kAlign);
   L->off_pslots = o;
@@ -176,7 +176,7 @@ int zero_file_locks(gfs_ctx* c, int id) {
   int rc = gfs_internal_zero(c->meta + L.off_locks + sizeof(gfs_file_lock) * (uint64_t)id, sizeof(gfs_file_lock),
                              c->stream);
   if (!rc)
-    rc = gfs_internal_zero(c->meta + L.off_lockq + 8ull * GFS_LOCK_SLOTS * (uint64_t)id, 8ull * GFS_LOCK_SLOTS,
+    rc = gfs_internal_zero(c->meta + L.off_lockq + 16ull * GFS_LOCK_SLOTS * (uint64_t)id, 16ull * GFS_LOCK_SLOTS,
                            c->stream);
   if (!rc)
     rc = gfs_internal_zero(c->meta + L.off_claims + sizeof(gfs_file_claims) * (uint64_t)id,
