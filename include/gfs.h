@@ -96,7 +96,7 @@ typedef struct gfs_config {
                                     multiple of 4 KiB, 64 KiB .. 64 MiB; each host thread holds
                                     one bounce buffer of this size for O_DIRECT reads */
   uint32_t max_files;            /* files registered at once (ids 0..max_files-1), 1..GFS_MAX_FILES;
-                                    sizes the per-file metadata (about 130 KiB per file) */
+                                    sizes the per-file metadata (about 98 KiB per file) */
   /* Readahead detector (Sec. 2.3: Linux also follows several readers that interleave on one
      file, by heuristics the paper does not spell out; these are the constants of this library's
      aggregate-reading rule). A

@@ -490,8 +490,8 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
  * A FIFO ticket lock whose waiters can leave the queue, and whose holder decides for the
  * waiters behind it. Blocks get the lock in ticket order, which keeps the readers of a file
  * together (an unfair lock lets a few blocks run far ahead and spreads the misses over the
- * whole file). Each ticket has a 64-bit queue slot and a 64-bit note beside it (GFS_LOCK_SLOTS
- * per file, more than the blocks the device can hold at once). A waiter writes what the
+ * whole file). Each ticket has a 64-bit queue slot (GFS_LOCK_SLOTS per file, more than the blocks
+ * the device can hold at once) and a 64-bit note. A waiter writes what the
  * detector needs of its miss into the note and then announces the page in its slot
  * ("waiting n, page"); the holder passes the lock by writing "granted n" into the slot of
  * ticket n. A waiter whose page appears in the table while it waits (another block's window
@@ -515,7 +515,7 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
 
 enum { LOCK_OWN = 0, LOCK_LEFT = 1, LOCK_TIMEOUT = 2, LOCK_COVERED = 3, LOCK_DECIDED = 4 };
 
-constexpr uint32_t kNoPage = 0x7fffffffu;   /* announced by a waiter that has no page: it must hold the lock itself */
+constexpr uint32_t kNoPage = 0x7fffffffu;   /* announced by a waiter that must hold the lock itself */
 __device__ __forceinline__ uint64_t lock_granted(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 1u); }
 __device__ __forceinline__ uint64_t lock_left(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 2u); }
 __device__ __forceinline__ uint64_t lock_covered(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 3u); }
@@ -530,17 +530,27 @@ __device__ __forceinline__ uint64_t lock_decided(uint64_t n, uint32_t below, uin
   return (1ull << 62) | ((uint64_t)w << 32) | lock_covered(n);
 }
 static_assert(GFS_MAX_WINDOW_PAGES <= 1024 && GFS_CLAIMS <= 16, "a window's extent and claim slot fit lock_decided");
-/* a miss as its waiter notes it: pages of the read from the missed one on, cached history behind
-   it, the block (for the trace) */
+/* A miss as its waiter notes it: pages of the read from the missed one on, cached history behind
+ * it, the block (for the trace); all ones if they do not fit, which no holder decides on. The top
+ * bits say whose note it is, of the files that share the row and the tickets that share the slot:
+ * a holder that finds another one's there grants that waiter the lock instead. (The slot's next
+ * ticket of the same file comes only once this one is gone.) */
+constexpr uint64_t kNoNote = ~0ull;
 __device__ __forceinline__ uint64_t lock_note(uint32_t req, uint32_t hist, uint32_t bid) {
-  return (uint64_t)(req < 0xffffffu ? req : 0xffffffu) | ((uint64_t)(hist & 0xfffu) << 24) | ((uint64_t)bid << 36);
+  if ((req >> 20) | (hist >> 12) | (bid >> 22)) return kNoNote;
+  return (uint64_t)req | ((uint64_t)hist << 20) | ((uint64_t)bid << 32);
 }
-/* a ticket's slot; its note is the word after it. lq: the file's slots */
-__device__ __forceinline__ uint64_t* lock_slot(uint64_t* lq, uint64_t n) {
-  return lq + 2 * (n & (GFS_LOCK_SLOTS - 1));
+__device__ __forceinline__ uint64_t lock_note_tag(uint32_t file, uint64_t n) {
+  return (uint64_t)(file / GFS_LOCK_NOTE_ROWS) | ((n / GFS_LOCK_SLOTS & 63u) << 4);
 }
+static_assert(GFS_MAX_FILES / GFS_LOCK_NOTE_ROWS <= 16, "a note's file fits its tag");
+/* a ticket's slot; lq: the file's slots */
+__device__ __forceinline__ uint64_t* lock_slot(uint64_t* lq, uint64_t n) { return lq + (n & (GFS_LOCK_SLOTS - 1)); }
 __device__ __forceinline__ uint64_t* lock_queue(const gfs_dev* d, uint32_t file) {
-  return H(d)->lockq + (uint64_t)file * (2 * GFS_LOCK_SLOTS);
+  return H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS;
+}
+__device__ __forceinline__ uint64_t* lock_note_at(const gfs_dev* d, uint32_t file, uint64_t n) {
+  return H(d)->lockn + (uint64_t)(file % GFS_LOCK_NOTE_ROWS) * GFS_LOCK_SLOTS + (n & (GFS_LOCK_SLOTS - 1));
 }
 
 /* Lane 0: leave the queue if ticket t has no grant or outcome yet; true if it left, false if its
@@ -577,7 +587,8 @@ __device__ __attribute__((noinline)) uint64_t lock_file_wave(const gfs_dev* d, u
     if (lane() == 0) {
       uint64_t v = ld_rlx(sl);
       if (v != lock_granted(t)) {
-        st_rlx(sl + 1, note);
+        if (note == kNoNote) page = kNoPage;
+        else st_rlx(lock_note_at(d, file, t), note | (lock_note_tag(file, t) << 54));
         drain_atomics();   /* the note is there before the slot says so */
         while (v != lock_granted(t)) {
           if (cas64_rlx(sl, v, lock_waiting(t, page))) break;
@@ -1708,7 +1719,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     uint64_t cl = ld_rlx(&clp[l & (GFS_CLAIMS - 1)]);
     const uint64_t nl = ticket + 1 + l;
     uint64_t qv = ld_rlx(lock_slot(lq, nl));
-    uint64_t qn = ld_rlx(lock_slot(lq, nl) + 1);
+    uint64_t qn = ld_rlx(lock_note_at(d, file, nl));
     drain_atomics();   /* the table probes below go out after the claims were read */
     ra_loaded(ras, cl, qv, qn);
     bool cl_on = l < GFS_CLAIMS && (cl & 1ull);
@@ -1717,7 +1728,8 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     /* the waiters right behind that can be decided for: announced, with a page, and as many as
        there are free claims left beside this block's own */
     const bool gone = qv == lock_left(nl) || (uint32_t)qv == (uint32_t)lock_covered(nl);
-    const bool waits = (qv >> 63) && (uint32_t)qv == ((uint32_t)nl << 2) && (uint32_t)(qv >> 32) != (0x80000000u | kNoPage);
+    const bool waits = (qv >> 63) && (uint32_t)qv == ((uint32_t)nl << 2) &&
+                       (uint32_t)(qv >> 32) != (0x80000000u | kNoPage) && (qn >> 54) == lock_note_tag(file, nl);
     const uint64_t stop = __ballot(!gone && !waits);
     uint32_t end = stop ? (uint32_t)__builtin_ctzll(stop) : 64u;   /* slots looked at: [0, end) */
     const uint32_t nfree = (uint32_t)__popcll(free_cl);
@@ -1789,9 +1801,9 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
         ip = (uint32_t)__builtin_amdgcn_readlane((int)(qv >> 32), (int)at) & 0x7fffffffu;
         const uint32_t n0 = (uint32_t)__builtin_amdgcn_readlane((int)qn, (int)at);
         const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane((int)(qn >> 32), (int)at);
-        ireq = n0 & 0xffffffu;
-        ihist = (n0 >> 24) | ((n1 & 0xfu) << 8);
-        ibid = n1 >> 4;
+        ireq = n0 & 0xfffffu;
+        ihist = n0 >> 20;
+        ibid = n1 & 0x3fffffu;
       }
       const bool covered = __ballot(cl_on && cl_lo <= ip && ip < cl_hi) != 0;
       const bool present = ((held >> it) & 1) != 0;
@@ -2334,7 +2346,7 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   if (aslot < 0) return;
   const uint32_t s = (uint32_t)aslot;
   /* the waiter announces no page, so no holder marks it covered or decides for it */
-  const uint64_t lk = lock_file_wave(d, file, 0, kNoPage, 0, t0, false);
+  const uint64_t lk = lock_file_wave(d, file, 0, kNoPage, kNoNote, t0, false);
   const uint64_t ticket = lk >> 3;
   if ((lk & 7) != LOCK_OWN) {
     if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);

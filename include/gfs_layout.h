@@ -9,8 +9,8 @@
  *   gfs_dev (the handle)             512 B
  *   files[max_files]                 768 B each
  *   locks[max_files]                 128 B each (miss ticket locks)
- *   lockq[max_files][GFS_LOCK_SLOTS][2] u64   queue slots of the miss locks and the waiters'
- *                                    notes beside them (64 KiB per file)
+ *   lockq[max_files][GFS_LOCK_SLOTS] u64   queue slots of the miss locks (32 KiB per file)
+ *   lockn[min(max_files, GFS_LOCK_NOTE_ROWS)][GFS_LOCK_SLOTS] u64   the waiters' notes
  *   claims[max_files]                128 B each (windows being reserved)
  *   pslots[private_slots]            64 B each (private policy)
  *   names[max_files]                 GFS_NAME_MAX B each (registered paths)
@@ -126,6 +126,11 @@ typedef struct gfs_file_lock {
    blocks (12 on a 160 KiB CU, 3072 on 256 CUs); gfs_init checks the device. */
 #define GFS_LOCK_SLOTS 4096u
 
+/* rows of waiters' notes: files share them (id modulo the rows), as a note says whose it is and one
+   that was overwritten only costs its waiter a turn with the lock; 64 rows hold the default
+   max_files without sharing, in 2 MiB */
+#define GFS_LOCK_NOTE_ROWS 64u
+
 /* misses decided by one holder of a file's miss lock: its own and those of waiters behind it.
    Eight: with four lanes' loads each the probes of all fit one round, and half of the window
    claims stay free for the windows still being reserved. */
@@ -218,7 +223,8 @@ typedef struct gfs_dev {
   gfs_globals* g;
   gfs_file_dev* files;
   gfs_file_lock* locks;
-  uint64_t* lockq;              /* [max_files][GFS_LOCK_SLOTS][2] miss-lock queue slots and notes */
+  uint64_t* lockq;              /* [max_files][GFS_LOCK_SLOTS] miss-lock queue slots */
+  uint64_t* lockn;              /* [min(max_files, GFS_LOCK_NOTE_ROWS)][GFS_LOCK_SLOTS] waiters' notes */
   gfs_file_claims* claims;      /* [max_files] windows being reserved */
   uint64_t* shadow;             /* [max_files][GFS_SHADOW_PAGES / 64]: bit set once the page was
                                    evicted after it was consumed (cleared with the cache) */

@@ -54,7 +54,7 @@ struct Layout {
   uint64_t max_req_bytes = 0;
   uint64_t quota = 0;              /* private policy: frames per slot */
   uint64_t pbuf_bytes = 0;         /* private policy: all private buffers */
-  uint64_t off_globals = 0, off_dev = 0, off_files = 0, off_locks = 0, off_lockq = 0, off_claims = 0, off_shadow = 0, off_pslots = 0, off_names = 0, off_fword = 0,
+  uint64_t off_globals = 0, off_dev = 0, off_files = 0, off_locks = 0, off_lockq = 0, off_lockn = 0, off_claims = 0, off_shadow = 0, off_pslots = 0, off_names = 0, off_fword = 0,
            off_ftag = 0, off_pt = 0, off_ffill = 0, off_slot_free = 0, off_slot_tail = 0, off_reqd = 0, off_trace = 0,
            meta_bytes = 0;
 };
@@ -113,7 +113,8 @@ int make_layout(const gfs_config* c, Layout* L) {
   const uint64_t nf = c->max_files;
   L->off_files = o; o = align_up(o + sizeof(gfs_file_dev) * nf, kAlign);
   L->off_locks = o; o = align_up(o + sizeof(gfs_file_lock) * nf, kAlign);
-  L->off_lockq = o; o = align_up(o + 16ull * GFS_LOCK_SLOTS * nf, kAlign);
+  L->off_lockq = o; o = align_up(o + 8ull * GFS_LOCK_SLOTS * nf, kAlign);
+  L->off_lockn = o; o = align_up(o + 8ull * GFS_LOCK_SLOTS * std::min<uint64_t>(nf, GFS_LOCK_NOTE_ROWS), kAlign);
   L->off_claims = o; o = align_up(o + sizeof(gfs_file_claims) * nf, kAlign);
   L->off_shadow = o; o = align_up(o + (uint64_t)(GFS_SHADOW_PAGES / 8) * nf, kAlign);
   L->off_pslots = o;
@@ -176,7 +177,7 @@ int zero_file_locks(gfs_ctx* c, int id) {
   int rc = gfs_internal_zero(c->meta + L.off_locks + sizeof(gfs_file_lock) * (uint64_t)id, sizeof(gfs_file_lock),
                              c->stream);
   if (!rc)
-    rc = gfs_internal_zero(c->meta + L.off_lockq + 16ull * GFS_LOCK_SLOTS * (uint64_t)id, 16ull * GFS_LOCK_SLOTS,
+    rc = gfs_internal_zero(c->meta + L.off_lockq + 8ull * GFS_LOCK_SLOTS * (uint64_t)id, 8ull * GFS_LOCK_SLOTS,
                            c->stream);
   if (!rc)
     rc = gfs_internal_zero(c->meta + L.off_claims + sizeof(gfs_file_claims) * (uint64_t)id,
@@ -350,6 +351,7 @@ int gfs_init(const gfs_config* cfg, void* frames_dev, void* meta_dev, void* hip_
   h.files = (gfs_file_dev*)(c->meta + L.off_files);
   h.locks = (gfs_file_lock*)(c->meta + L.off_locks);
   h.lockq = (uint64_t*)(c->meta + L.off_lockq);
+  h.lockn = (uint64_t*)(c->meta + L.off_lockn);
   h.claims = (gfs_file_claims*)(c->meta + L.off_claims);
   h.shadow = (uint64_t*)(c->meta + L.off_shadow);
   h.policy = cfg->policy;

@@ -93,3 +93,40 @@ def test_reads_into_every_buffer_alignment(page, tmp_path, cuda):
                 want = np.full(n + 128, 0xA5, dtype=np.uint8)
                 want[16 + a:16 + a + n] = data[off:off + n]
                 np.testing.assert_array_equal(buf.cpu().numpy(), want)
+
+
+def test_two_files_that_share_a_row_of_lock_notes(tmp_path, cuda):
+    """Files 0 and 64 keep the notes of their waiting misses in the same place: read together, by
+    more blocks than a holder decides for at once, from offsets that make windows meet."""
+    torch = cuda
+    page, blocks = 4 << 10, 512
+    cfg = runner.make_config(page, 2 * blocks * page, ra_cap_bytes=8 * page, max_files=66, timeout_s=20)
+    with gfs.PageCache(cfg) as cache:
+        ids, datas = [], []
+        for i in range(65):
+            size = 4 * blocks * page + 100 + i if i in (0, 64) else 10
+            data = np.random.RandomState(i).randint(0, 256, size, dtype=np.uint8)
+            p = str(tmp_path / f"f{i}.bin")
+            data.tofile(p)
+            ids.append(cache.open(p))
+            datas.append(data)
+        assert ids[64] - ids[0] == 64
+        n = 2 * page + 48
+        starts = (np.arange(blocks, dtype=np.uint64) * 4 * page)[:, None] + np.arange(2, dtype=np.uint64)[None, :] * 2 * page
+        for rep in range(3):
+            print(f"[gpu] shared notes rep={rep}", flush=True)
+            pairs = [(runner.ListReader(starts, n, 2, 64), torch.cuda.Stream(), f) for f in (0, 64)]
+            torch.cuda.synchronize()
+            for r, s, f in pairs:
+                r.launch(cache, ids[f], stream=s)
+            for r, _, f in pairs:
+                res = r.result()
+                last = starts[:, -1].astype(int)
+                want = np.stack([np.resize(np.pad(datas[f][o:o + n], (0, n)), n) for o in last])
+                got_n = np.array([sum(len(datas[f][int(o):int(o) + n]) for o in row) for row in starts])
+                np.testing.assert_array_equal(res.status, got_n)
+                full = np.array([len(datas[f][o:o + n]) == n for o in last])
+                np.testing.assert_array_equal(res.out[full], want[full])
+            st = cache.stats()
+            assert st["timeouts"] == 0 and st["io_errors"] == 0
+            cache.reset()
