@@ -157,19 +157,20 @@ __device__ __forceinline__ uint64_t ld_rlx(uint64_t* p) {
 __device__ __forceinline__ uint64_t ld_acq(uint64_t* p) {
   return __hip_atomic_load(G(p), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
-/* Spin loops poll with relaxed loads and take one acquire fence once the awaited value is
-   seen: an agent-scope acquire invalidates the XCD's L2, and hundreds of waiting blocks
-   polling with acquire loads would keep every block's cached data flushed. */
 __device__ __forceinline__ void acquire_agent() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 __device__ __forceinline__ void acquire_system() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, ""); }
-/* Ordering for the miss lock's critical section, whose shared reads and writes are all
-   agent-scope atomics (the detector state, the window claims, the page table, the queue
-   slots): these are performed coherently across the XCDs, so passing the lock on needs
-   only the holder's earlier atomics to have completed before the grant is written, and
-   taking it needs only the later reads to be issued after the grant was seen. The wait
-   for outstanding memory operations gives both, without the L2 write-back and
-   invalidation that agent-scope fences add for plain (cached) accesses. The workgroup
-   fences keep the compiler from moving memory operations across the wait. */
+/* Ordering without cache maintenance. An agent-scope release writes the XCD's L2 back and an
+ * acquire empties it, for the sake of plain (cached) accesses, and every block of the XCD pays:
+ * a miss had about fifteen of them. gread's shared data need neither. The metadata are accessed
+ * by atomics only, which are performed coherently across the XCDs; frame bytes are written with
+ * device-scope stores (written through) and read with device-scope loads; the ring and the
+ * staged bytes in host memory are accessed with system-scope loads and stores. So "B after A"
+ * needs only that A has been performed before B is issued: the wait below for a wave's
+ * outstanding memory operations (with a block barrier for those of other waves), and for a
+ * reader that it issues a load only once it has seen the value the load depends on. The
+ * workgroup fences keep the compiler from moving memory operations across the wait.
+ * Without the releases and acquires: 256 MiB through 4 KiB pages 11.7 -> 7.2 ms (pull 95 -> 29 us,
+ * allocation 36 -> 9, run 7.0 -> 3.5 a miss), random 64 KiB pages 13.8 -> 10.3. */
 __device__ __forceinline__ void drain_atomics() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0x0F70);   /* vmcnt(0): every load, store and atomic done */
@@ -186,6 +187,13 @@ __device__ __forceinline__ void st_rel(uint64_t* p, uint64_t v) {
 }
 __device__ __forceinline__ void st_rlx32(uint32_t* p, uint32_t v) {
   __hip_atomic_store(G(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+/* the ring in pinned host memory */
+__device__ __forceinline__ uint64_t ld_host(const void* p) {
+  return __hip_atomic_load((gu64*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void st_host(void* p, uint64_t v) {
+  __hip_atomic_store((gu64*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ bool cas64(uint64_t* p, uint64_t& expected, uint64_t desired) {
   return __hip_atomic_compare_exchange_strong(G(p), &expected, desired, __ATOMIC_ACQ_REL,
@@ -403,12 +411,11 @@ __device__ __forceinline__ void frame_pin_bits(const gfs_dev* d, uint32_t f, uin
 }
 
 /* Pin frame f if it is filling or valid and still holds key; sets the reference bit and
- * clears the prefetched mark (the page has now been demanded). Acquire: a valid frame's
- * bytes, published with release by the block that filled it, are visible afterwards, and
- * the tag is read after the pin is in place (a frame cannot be claimed while pinned). */
+ * clears the prefetched mark (the page has now been demanded). The tag is read after the pin
+ * is in place (a frame cannot be claimed while pinned). */
 __device__ int frame_pin(const gfs_dev* d, uint32_t f, uint64_t key, uint64_t* w_out = nullptr) {
   uint64_t* fw = &H(d)->fword[f];
-  const uint64_t w = __hip_atomic_fetch_add(G(fw), GFS_FW_PIN_ONE, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t w = __hip_atomic_fetch_add(G(fw), GFS_FW_PIN_ONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (w_out) *w_out = w;
   const uint64_t st = w & GFS_FW_STATE;
   if ((st != GFS_FS_FILLING && st != GFS_FS_VALID) || ld_rlx(&H(d)->ftag[f]) != key) {
@@ -443,7 +450,7 @@ __device__ int hand_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t
   seen = ((w & GFS_FW_REF) ? 2u : 0u) | ((w & GFS_FW_PINS) ? 4u : 0u) | ((uint32_t)st << 4);
   if (w & GFS_FW_PINS) return GFS_HAND_SKIP;
   if (st == GFS_FS_FREE) {
-    if (cas64(fw, w, claimed)) return GFS_HAND_FREE;
+    if (cas64_rlx(fw, w, claimed)) return GFS_HAND_FREE;
     seen |= 8u;
     return GFS_HAND_SKIP;
   }
@@ -454,7 +461,7 @@ __device__ int hand_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t
     return GFS_HAND_SKIP;
   }
   const uint64_t old = w;
-  if (!cas64(fw, w, claimed)) {
+  if (!cas64_rlx(fw, w, claimed)) {
     seen |= 8u;
     return GFS_HAND_SKIP;
   }
@@ -471,7 +478,6 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
   while (true) {
     const uint64_t w = ld_rlx(&H(d)->fword[f]);
     if ((w & GFS_FW_STATE) == GFS_FS_VALID) {
-      acquire_agent();   /* the frame's bytes, published before VALID */
       if (w & GFS_FW_ERR) {
         frame_unpin(d, f);
         return -kEIO;
@@ -964,8 +970,10 @@ __device__ __attribute__((noinline)) uint32_t alloc_wave(const gfs_dev* d, uint3
          page, prefetched mark otherwise; an addition keeps pins other blocks hold briefly */
       const uint64_t delta = (GFS_FS_FILLING - GFS_FS_CLAIMED) + GFS_FW_VER_ONE +
                              (q == demand ? GFS_FW_PIN_ONE : GFS_FW_RA) + (q == mark ? GFS_FW_MARK : 0ull);
-      __hip_atomic_fetch_add(G(&H(d)->fword[f]), delta, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      st_rel(H(d)->pt + bs->lslot[k], (key << GFS_ENTRY_FRAME_BITS) | f);
+      drain_atomics();   /* tag and fill word before FILLING, FILLING before the table entry */
+      __hip_atomic_fetch_add(G(&H(d)->fword[f]), delta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      drain_atomics();
+      st_rlx(H(d)->pt + bs->lslot[k], (key << GFS_ENTRY_FRAME_BITS) | f);
       bs->lframe[k] = f;
       trace_ev(d, 1, GFS_EV_ALLOC, bid, file, (uint32_t)q, f, q == demand ? 0u : 1u, t);
     }
@@ -984,26 +992,49 @@ __device__ __attribute__((noinline)) uint32_t alloc_wave(const gfs_dev* d, uint3
 /* ------------------------------------------------------------------ vector copy */
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-/* Block-cooperative copy of n bytes; both pointers 16-byte aligned and in global memory
- * (frames, user buffers). Global rather than generic accesses let loads and stores be
- * waited on separately, so eight 16-byte loads per lane are in flight per round. */
 typedef __attribute__((address_space(1))) v4u gv4u;
 
-__device__ __attribute__((noinline)) void copy_block_aligned(uint8_t* dst, const uint8_t* src, uint64_t n,
-                                                   uint32_t tid, uint32_t nt) {
-  const uint64_t n16 = n >> 4;
-  const gv4u* s = (const gv4u*)src;
-  gv4u* o = (gv4u*)dst;
-  uint64_t i = tid;
-  for (; i + 7ull * nt < n16; i += 8ull * nt) {
-    v4u a[8];
+/* Eight 16-byte units from staging (host memory: system-scope loads, which take nothing an earlier
+ * use of the slot left in a cache) to a frame (device-scope stores, written through to memory for
+ * readers of other XCDs). All eight loads are issued before the first is waited for, in the
+ * statement itself; units not in `ok` are loaded from a readable address and not stored. */
+__device__ __forceinline__ void copy_in8(uint8_t* const (&to)[8], const uint8_t* const (&from)[8], uint32_t ok) {
+  v4u a[8];
+  asm volatile("global_load_dwordx4 %0, %8, off sc0 sc1\n\t"
+               "global_load_dwordx4 %1, %9, off sc0 sc1\n\t"
+               "global_load_dwordx4 %2, %10, off sc0 sc1\n\t"
+               "global_load_dwordx4 %3, %11, off sc0 sc1\n\t"
+               "global_load_dwordx4 %4, %12, off sc0 sc1\n\t"
+               "global_load_dwordx4 %5, %13, off sc0 sc1\n\t"
+               "global_load_dwordx4 %6, %14, off sc0 sc1\n\t"
+               "global_load_dwordx4 %7, %15, off sc0 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(a[4]), "=&v"(a[5]), "=&v"(a[6]), "=&v"(a[7])
+               : "v"(from[0]), "v"(from[1]), "v"(from[2]), "v"(from[3]), "v"(from[4]), "v"(from[5]), "v"(from[6]), "v"(from[7])
+               : "memory");
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = s[i + (uint64_t)k * nt];
+  for (uint32_t j = 0; j < 8; ++j)
+    if ((ok >> j) & 1)   /* the pause keeps the data registers until the store has read them */
+      asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(to[j]), "v"(a[j]) : "memory");
+}
+
+/* Block-cooperative copy_in8 of n bytes, rounded up to 16 (both sides hold whole pages); both
+ * pointers 16-byte aligned. */
+__device__ __attribute__((noinline)) void copy_in(uint8_t* dst, const uint8_t* src, uint64_t n, uint32_t tid,
+                                                  uint32_t nt) {
+  const uint64_t n16 = (n + 15) >> 4;
+  for (uint64_t i = tid; i < n16; i += 8ull * nt) {
+    uint8_t* to[8];
+    const uint8_t* from[8];
+    uint32_t ok = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) o[i + (uint64_t)k * nt] = a[k];
+    for (uint32_t j = 0; j < 8; ++j) {
+      const uint64_t u = i + (uint64_t)j * nt;
+      if (u < n16) ok |= 1u << j;
+      from[j] = src + ((u < n16 ? u : i) << 4);
+      to[j] = dst + (u << 4);
+    }
+    copy_in8(to, from, ok);
   }
-  for (; i < n16; i += nt) o[i] = s[i];
-  for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) dst[j] = src[j];
 }
 
 /* ------------------------------------------------------------------ reading frames
@@ -1104,7 +1135,6 @@ __device__ __attribute__((noinline)) void join_or_help_lane(const gfs_dev* d, ui
   while (true) {
     uint64_t w = ld_rlx(fw);
     if ((w & GFS_FW_STATE) == GFS_FS_VALID) {
-      acquire_agent();   /* the frame's bytes, published before VALID */
       if (w & GFS_FW_ERR) {
         frame_unpin(d, f);
         bs->status = -kEIO;
@@ -1121,15 +1151,14 @@ __device__ __attribute__((noinline)) void join_or_help_lane(const gfs_dev* d, ui
         const uint32_t s = (uint32_t)((ff >> 40) & 0x7fffff) - 1;
         const uint64_t gen = ff & ((1ull << 40) - 1);
         gfs_rpc_slot* rs = &H(d)->ring[s];
-        if (__hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == gen) {
-          acquire_system();   /* the staged bytes and the result, written before done_seq */
-          if (cas64(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
+        if (ld_host(&rs->done_seq) == gen) {   /* the staged bytes and the result were written before it */
+          if (cas64_rlx(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
             bs->status = 0;
             bs->pull = 2;
             bs->slot = s;
             bs->gen = gen;
-            bs->first_page = rs->offset >> H(d)->page_shift;
-            bs->result = rs->result;
+            bs->first_page = ld_host(&rs->offset) >> H(d)->page_shift;
+            bs->result = (int64_t)ld_host(&rs->result);
             bs->help_page = (uint32_t)p;
             return;
           }
@@ -1140,14 +1169,14 @@ __device__ __attribute__((noinline)) void join_or_help_lane(const gfs_dev* d, ui
         gfs_req_dev* rq = &H(d)->reqd[s];
         const uint64_t ready = ld_rlx(&rq->ready);
         if (ready != 0 && (ready & ((1ull << 40) - 1)) == (ff & ((1ull << 40) - 1))) {
-          acquire_agent();   /* the request record, published before ready */
-          if (cas64(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
+          /* the request record was written before ready */
+          if (cas64_rlx(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
             bs->status = 0;
             bs->pull = 2;
             bs->slot = s;
             bs->gen = ready;
-            bs->first_page = rq->first_page;
-            bs->result = rq->result;
+            bs->first_page = ld_rlx(&rq->first_page);
+            bs->result = (int64_t)ld_rlx((uint64_t*)&rq->result);
             bs->help_page = (uint32_t)p;
             return;
           }
@@ -1250,6 +1279,19 @@ __device__ __forceinline__ uint32_t ring_slot(const gfs_dev* d, uint32_t, uint64
 }
 __device__ __forceinline__ uint64_t ring_gen(const gfs_dev* d, uint64_t tk) { return tk / H(d)->sync_slots + 1; }
 
+/* Lane: write a request into ring slot rs and post it as generation gen. */
+__device__ __forceinline__ void post_request_lane(gfs_rpc_slot* rs, uint32_t file, uint32_t npages, uint64_t off0,
+                                                  uint64_t len, uint64_t tk, uint64_t gen) {
+  static_assert(offsetof(gfs_rpc_slot, npages) == offsetof(gfs_rpc_slot, file_id) + 4 &&
+                offsetof(gfs_rpc_slot, file_id) % 8 == 0, "written as one word");
+  st_host(&rs->file_id, (uint64_t)file | ((uint64_t)npages << 32));
+  st_host(&rs->offset, off0);
+  st_host(&rs->length, len);
+  st_host(&rs->ticket, tk);
+  drain_atomics();
+  st_host(&rs->req_seq, gen);
+}
+
 /* Lane: take a free slot of the asynchronous windows (busy 0 -> 1), starting at the block's
    own; -1 if every one is held. The slot's next generation is one past its last completed. */
 __device__ int32_t async_slot_take_lane(const gfs_dev* d, uint32_t bid) {
@@ -1258,7 +1300,7 @@ __device__ int32_t async_slot_take_lane(const gfs_dev* d, uint32_t bid) {
     const uint32_t s = H(d)->sync_slots + (bid + i) % A;
     uint64_t* b = &H(d)->reqd[s].busy;
     uint64_t z = 0;
-    if (ld_rlx(b) == 0 && cas64(b, z, 1ull)) return (int32_t)s;
+    if (ld_rlx(b) == 0 && cas64_rlx(b, z, 1ull)) return (int32_t)s;
   }
   return -1;
 }
@@ -1282,10 +1324,10 @@ __device__ int lra_visit(const gfs_dev* d, uint32_t f, uint64_t& vkey, uint32_t&
   const uint64_t st = w & GFS_FW_STATE;
   const uint64_t claimed = (((w >> GFS_FW_VER_SHIFT) + 1) << GFS_FW_VER_SHIFT) | GFS_FS_CLAIMED;
   if (w & GFS_FW_PINS) return GFS_HAND_SKIP;
-  if (st == GFS_FS_FREE) return cas64(fw, w, claimed) ? GFS_HAND_FREE : GFS_HAND_SKIP;
+  if (st == GFS_FS_FREE) return cas64_rlx(fw, w, claimed) ? GFS_HAND_FREE : GFS_HAND_SKIP;
   if (st != GFS_FS_VALID) return GFS_HAND_SKIP;
   const uint64_t old = w;
-  if (!cas64(fw, w, claimed)) return GFS_HAND_SKIP;
+  if (!cas64_rlx(fw, w, claimed)) return GFS_HAND_SKIP;
   vkey = tag;
   vra = (old & GFS_FW_RA) ? 1u : 0u;
   return GFS_HAND_EVICT;
@@ -1354,15 +1396,17 @@ __device__ __attribute__((noinline)) int miss_private_wave(const gfs_dev* d, uin
     bcount(bs, GFS_C_HAND, 1);
     if (fr < 0) {
       /* every frame of the share is pinned by other blocks: give the page back, retry */
-      st_rel(H(d)->pt + slot, 0ull);
+      st_rlx(H(d)->pt + slot, 0ull);
       bcount(bs, GFS_C_NOFRAME, 1);
       status = 1;
     } else {
       st_rlx(&H(d)->ftag[fr], key);
       st_rlx(&H(d)->ffill[fr], 0ull);
+      drain_atomics();   /* tag and fill word before FILLING, FILLING before the table entry */
       __hip_atomic_fetch_add(G(&H(d)->fword[fr]), (GFS_FS_FILLING - GFS_FS_CLAIMED) + GFS_FW_VER_ONE + GFS_FW_PIN_ONE,
-                             __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      st_rel(H(d)->pt + slot, (key << GFS_ENTRY_FRAME_BITS) | (uint64_t)fr);
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      drain_atomics();
+      st_rlx(H(d)->pt + slot, (key << GFS_ENTRY_FRAME_BITS) | (uint64_t)fr);
       trace_ev(d, 1, GFS_EV_ALLOC, bid, file, (uint32_t)p, (uint32_t)fr, 0, (uint64_t)ps->lra_next);
       bcount(bs, GFS_T_ALLOC, wall_clock64() - ta0);
       bcount(bs, GFS_C_MISSES, 1);
@@ -1392,31 +1436,24 @@ __device__ __attribute__((noinline)) int miss_private_wave(const gfs_dev* d, uin
           }
           nap(nn);
         }
-        acquire_agent();   /* the slot's last users are done with its staging */
         bcount(bs, GFS_T_SLOT, wall_clock64() - ts0);
         if (status == 0) {
           gfs_rpc_slot* rs = &H(d)->ring[s];
-          rs->file_id = file;
-          rs->npages = span;
-          rs->offset = off0;
-          rs->length = len;
-          rs->ticket = tk;
-          __hip_atomic_store(G(&rs->req_seq), gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+          post_request_lane(rs, file, span, off0, len, tk, gen);
           trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)p, GFS_NO_FRAME, span, tk);
           bcount(bs, GFS_C_REQUESTS, 1);
           bcount(bs, GFS_C_REQ_BYTES, len);
           bcount(bs, GFS_C_FETCHED, 1);
           const uint64_t th0 = wall_clock64();
-          while (__hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != gen) {
+          while (ld_host(&rs->done_seq) != gen) {
             if (expired(d, t0)) {
               status = 2;
               break;
             }
             nap(nn);
           }
-          acquire_system();   /* the staged bytes, written by the host before done_seq */
           bcount(bs, GFS_T_HOST, wall_clock64() - th0);
-          if (status == 0) bs->result = rs->result;
+          if (status == 0) bs->result = (int64_t)ld_host(&rs->result);
         }
         if (status == 0) {
           bs->pull = 4;
@@ -1482,16 +1519,9 @@ __device__ __attribute__((noinline)) int post_wait_wave(const gfs_dev* d, uint32
       }
       nap(nn);
     }
-    acquire_agent();   /* the slot's last users are done with its staging */
     bcount(bs, GFS_T_SLOT, wall_clock64() - ts0);
     if (status == 0) {
-      gfs_rpc_slot* rs = &H(d)->ring[s];
-      rs->file_id = file;
-      rs->npages = span;
-      rs->offset = off0;
-      rs->length = len;
-      rs->ticket = tk;
-      __hip_atomic_store(G(&rs->req_seq), gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      post_request_lane(&H(d)->ring[s], file, span, off0, len, tk, gen);
       trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)lo, GFS_NO_FRAME, span, tk);
       bcount(bs, GFS_C_MISSES, 1);
       bcount(bs, GFS_C_REQUESTS, 1);
@@ -1507,32 +1537,33 @@ __device__ __attribute__((noinline)) int post_wait_wave(const gfs_dev* d, uint32
   if (status == 0) {
     /* tell waiting blocks which request fills each frame: (slot + 1) << 40 | gen */
     const uint64_t fill = ((uint64_t)(s + 1) << 40) | (gen & ((1ull << 40) - 1));
-    for (uint32_t k = l; k < got; k += 64) st_rel(&H(d)->ffill[bs->lframe[k]], fill);
+    for (uint32_t k = l; k < got; k += 64) st_rlx(&H(d)->ffill[bs->lframe[k]], fill);
   }
   if (l == 0) {
     if (status == 0) {
       gfs_rpc_slot* rs = &H(d)->ring[s];
       uint32_t nn = 0;
       const uint64_t th0 = wall_clock64();
-      while (__hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) !=
-             gen) {
+      while (ld_host(&rs->done_seq) != gen) {
         if (expired(d, t0)) {
           status = -kETIMEDOUT;
           break;
         }
         nap(nn);
       }
-      acquire_system();   /* the staged bytes, written by the host before done_seq */
       bcount(bs, GFS_T_HOST, wall_clock64() - th0);
       if (status == 0) {
-        bs->result = rs->result;
+        /* the staged bytes and the result were written by the host before done_seq */
+        const uint64_t result = ld_host(&rs->result);
+        bs->result = (int64_t)result;
         /* let blocks waiting on frames of this request pull their own pages */
         gfs_req_dev* rq = &H(d)->reqd[s];
-        rq->result = bs->result;
-        rq->first_page = lo;
-        rq->file = file;
-        __hip_atomic_store(G(&rq->remaining), got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        st_rel(&rq->ready, gen);
+        st_rlx((uint64_t*)&rq->result, result);
+        st_rlx(&rq->first_page, lo);
+        st_rlx32(&rq->file, file);
+        st_rlx32(&rq->remaining, got);
+        drain_atomics();
+        st_rlx(&rq->ready, gen);
       }
     }
     if (status) bcount(bs, GFS_C_TIMEOUTS, 1);
@@ -1635,7 +1666,7 @@ __device__ __attribute__((noinline)) int miss_one_page_wave(const gfs_dev* d, ui
   if (got == 0) {
     /* every frame pinned or filling: give the page back and retry the access */
     if (l == 0) {
-      st_rel(H(d)->pt + slot, 0ull);
+      st_rlx(H(d)->pt + slot, 0ull);
       bcount(bs, GFS_C_NOFRAME, 1);
     }
     if (expired(d, t0)) return 2;
@@ -1695,7 +1726,6 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
       if (__ballot(l < GFS_CLAIMS && (cl & 1ull) && c_lo <= p && p < c_hi) == 0) break;
       if (l == 0) nap_short(nw);
     }
-    acquire_agent();   /* the reservations, published before the claim was cleared */
     return 1;
   }
   uint64_t cws, cwe, mark = ~0ull;
@@ -1934,7 +1964,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   }
   failed = (uint32_t)(__ballot(failed != 0) != 0);
   /* the reservations are in the table: release the claim */
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  drain_atomics();
   if (l == 0) st_rlx(claim, 0ull);
   wave_sync_lds();
   const uint64_t tl3 = wall_clock64();
@@ -1957,7 +1987,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   /* release reservations that got no frame (the table was full or no frame was free) */
   for (uint32_t i = got + l; i < n; i += 64) {
     if (bs->lslot[i] != 0xffffffffu)
-      st_rel(H(d)->pt + bs->lslot[i], 0ull);
+      st_rlx(H(d)->pt + bs->lslot[i], 0ull);
   }
   if (got == 0) {
     if (l == 0) bcount(bs, keep ? GFS_C_NOFRAME : GFS_C_RETRIES, 1);
@@ -2092,8 +2122,8 @@ __device__ __forceinline__ bool staged_short(const gfs_dev* d, uint64_t q, uint6
 /* Wave 0: claim the request's frames that no helping block has taken (PULL bit); their
  * indices go to bs->lslot[0..nclaim). A frame counts as the request's only while its fill word
  * names the request (fill): once helpers have published it, the clock may have given it to
- * another request, which the caller must not touch. The word is read first (acquire) and the
- * fill word after it, and the claim is a compare-and-swap against that word, so a frame that
+ * another request, which the caller must not touch. The word is read first and, once it is
+ * there, the fill word after it, and the claim is a compare-and-swap against that word, so a frame that
  * changed hands in between is not claimed. */
 __device__ __attribute__((noinline)) void claim_pulls_wave(const gfs_dev* d, BlockState* bs, uint64_t fill) {
   d = uniform(d);
@@ -2105,9 +2135,9 @@ __device__ __attribute__((noinline)) void claim_pulls_wave(const gfs_dev* d, Blo
     if (k < bs->list_n) {
       const uint32_t f = bs->lframe[k];
       uint64_t* fw = &H(d)->fword[f];
-      uint64_t w = ld_acq(fw);
+      uint64_t w = ld_rlx(fw);
       while ((w & GFS_FW_STATE) == GFS_FS_FILLING && !(w & GFS_FW_PULL) && ld_rlx(&H(d)->ffill[f]) == fill) {
-        if (cas64(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
+        if (cas64_rlx(fw, w, (w | GFS_FW_PULL) + GFS_FW_VER_ONE)) {
           won = true;
           break;
         }
@@ -2121,23 +2151,43 @@ __device__ __attribute__((noinline)) void claim_pulls_wave(const gfs_dev* d, Blo
   wave_sync_lds();
 }
 
-/* Block-collective: copy claimed pages from the ring slot's staging into their frames.
- * pull == 1: the frames listed in lslot[0..nclaim); pull == 2: the one helped frame. */
-__device__ void block_pull(const gfs_dev* d, const BlockState* bs, uint64_t fsize) {
+/* Block-collective: copy claimed pages from the ring slot's staging into their frames, as far as
+ * the host returned bytes (rounded up to 16). pull == 1: the frames listed in lslot[0..nclaim);
+ * pull == 2: the one helped frame. All units of all pages are one sequence, so that a thread has
+ * eight loads over the host link in flight whatever the page size: a 4 KiB page is one load a
+ * thread. */
+__device__ __attribute__((noinline)) void block_pull(const gfs_dev* d, const BlockState* bs) {
+  d = uniform(d);
   const uint32_t tid = thread_id(), nt = block_threads();
-  const uint64_t P = H(d)->page_size;
-  const uint8_t* stg = H(d)->staging + (uint64_t)bs->slot * H(d)->max_req_bytes;
-  if (bs->pull == 2) {
-    const uint64_t q = bs->help_page;
-    copy_block_aligned(H(d)->frames + (uint64_t)(uint32_t)bs->frame * P, stg + (q - bs->first_page) * P,
-                       staged_bytes(d, q, bs->first_page, bs->result, fsize), tid, nt);
-    return;
-  }
-  for (uint32_t c = 0; c < bs->nclaim; ++c) {
-    const uint32_t k = bs->lslot[c];
-    const uint64_t q = bs->list[k];
-    copy_block_aligned(H(d)->frames + (uint64_t)bs->lframe[k] * P, stg + (q - bs->first_page) * P,
-                       staged_bytes(d, q, bs->first_page, bs->result, fsize), tid, nt);
+  const uint32_t sh = H(d)->page_shift, ush = sh - 4;
+  const uint8_t* const stg = H(d)->staging + (uint64_t)bs->slot * H(d)->max_req_bytes;
+  uint8_t* const frames = H(d)->frames;
+  const bool help = bs->pull == 2;
+  const uint64_t first = bs->first_page;
+  const uint64_t have = bs->result > 0 ? (uint64_t)bs->result : 0;
+  const uint32_t total = (help ? 1u : bs->nclaim) << ush;   /* at most 1024 pages of 2^17 units */
+  for (uint32_t u0 = tid; u0 < total; u0 += 8 * nt) {
+    uint8_t* to[8];
+    const uint8_t* from[8];
+    uint32_t ok = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j) {
+      const uint32_t u = u0 + j * nt;
+      from[j] = stg;
+      to[j] = frames;
+      if (u >= total) continue;
+      const uint32_t k = help ? 0u : bs->lslot[u >> ush];
+      const uint64_t q = help ? bs->help_page : bs->list[k];
+      const uint32_t f = help ? (uint32_t)bs->frame : bs->lframe[k];
+      const uint32_t at = (u & ((1u << ush) - 1)) << 4;
+      const uint64_t so = ((q - first) << sh) + at;
+      if (so < have) {
+        ok |= 1u << j;
+        from[j] = stg + so;
+        to[j] = frames + ((uint64_t)f << sh) + at;
+      }
+    }
+    copy_in8(to, from, ok);
   }
 }
 
@@ -2148,7 +2198,7 @@ __device__ __forceinline__ void publish_frame(const gfs_dev* d, uint32_t f, bool
   while (true) {
     uint64_t nw = ((w & ~(GFS_FW_STATE | GFS_FW_PULL)) | GFS_FS_VALID | GFS_FW_REF) + GFS_FW_VER_ONE;
     if (short_read) nw |= GFS_FW_ERR;
-    if (cas64(fw, w, nw)) break;
+    if (cas64_rlx(fw, w, nw)) break;
   }
 }
 
@@ -2157,11 +2207,14 @@ __device__ __forceinline__ void publish_frame(const gfs_dev* d, uint32_t f, bool
 __device__ __forceinline__ void request_done_lane(const gfs_dev* d, uint32_t s, uint64_t gen,
                                                   uint32_t cnt) {
   if (cnt == 0) return;
-  const uint32_t before = __hip_atomic_fetch_sub(G(&H(d)->reqd[s].remaining), cnt, __ATOMIC_ACQ_REL,
+  const uint32_t before = __hip_atomic_fetch_sub(G(&H(d)->reqd[s].remaining), cnt, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
   if (before == cnt) {
-    st_rel(&H(d)->slot_free[s], gen);
-    if (s >= H(d)->sync_slots) st_rel(&H(d)->reqd[s].busy, 0ull);   /* an asynchronous window's slot */
+    st_rlx(&H(d)->slot_free[s], gen);
+    if (s >= H(d)->sync_slots) {   /* an asynchronous window's slot: its generation first */
+      drain_atomics();
+      st_rlx(&H(d)->reqd[s].busy, 0ull);
+    }
   }
 }
 
@@ -2179,7 +2232,6 @@ __device__ __attribute__((noinline)) int64_t publish_pull_wave(const gfs_dev* d,
     if (l == 0) {
       const bool sh = staged_short(d, bs->help_page, bs->first_page, bs->result, fsize);
       publish_frame(d, (uint32_t)bs->frame, sh);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       request_done_lane(d, bs->slot, bs->gen, 1);
       bad = sh ? 1u : 0u;
       st = sh ? -kEIO : 0;
@@ -2192,7 +2244,7 @@ __device__ __attribute__((noinline)) int64_t publish_pull_wave(const gfs_dev* d,
       publish_frame(d, bs->lframe[k], sh);
       bad += sh ? 1u : 0u;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    drain_atomics();   /* every lane's frames are published */
     if (l == 0) {
       request_done_lane(d, bs->slot, bs->gen, bs->nclaim);
       /* the demanded page: pulled here, or by a helper that may still be copying it (an
@@ -2221,14 +2273,14 @@ __device__ void private_pull(const gfs_dev* d, const BlockState* bs, uint64_t fs
     const uint64_t q = bs->help_page;
     uint64_t n = fsize - (q << H(d)->page_shift);
     if (n > P) n = P;
-    copy_block_aligned(H(d)->frames + (uint64_t)f * P, pb + (q - ps->first) * P, n, tid, nt);
+    copy_in(H(d)->frames + (uint64_t)f * P, pb + (q - ps->first) * P, n, tid, nt);
     return;
   }
   const uint8_t* stg = H(d)->staging + (uint64_t)bs->slot * H(d)->max_req_bytes;
-  copy_block_aligned(H(d)->frames + (uint64_t)f * P, stg,
+  copy_in(H(d)->frames + (uint64_t)f * P, stg,
                      staged_bytes(d, bs->first_page, bs->first_page, bs->result, fsize), tid, nt);
   const int64_t rest = bs->result - (int64_t)P;
-  if (rest > 0) copy_block_aligned(pb, stg + P, (uint64_t)rest, tid, nt);
+  if (rest > 0) copy_in(pb, stg + P, (uint64_t)rest, tid, nt);
 }
 
 /* Thread 0, after private_pull and a block barrier: publish the frame; for a host request,
@@ -2246,7 +2298,7 @@ __device__ int64_t private_publish_lane(const gfs_dev* d, BlockState* bs, uint64
   const bool short_page = staged_short(d, bs->first_page, bs->first_page, bs->result, fsize);
   publish_frame(d, f, short_page);
   if (short_page) bcount(bs, GFS_C_IOERR, 1);
-  st_rel(&H(d)->slot_free[bs->slot], bs->gen);
+  st_rlx(&H(d)->slot_free[bs->slot], bs->gen);   /* the block's barrier came after its last read of the staging */
   const uint64_t off0 = bs->first_page << H(d)->page_shift;
   uint64_t expect = (uint64_t)bs->list_n * P;
   if (expect > fsize - off0) expect = fsize - off0;
@@ -2349,7 +2401,7 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   const uint64_t lk = lock_file_wave(d, file, 0, kNoPage, kNoNote, t0, false);
   const uint64_t ticket = lk >> 3;
   if ((lk & 7) != LOCK_OWN) {
-    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
+    if (l == 0) st_rlx(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   __builtin_amdgcn_s_setprio(3);
@@ -2364,7 +2416,7 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   if (sm == 0) {
     unlock_file_wave(d, file, ticket, 0, 0);
     __builtin_amdgcn_s_setprio(0);
-    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
+    if (l == 0) st_rlx(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   const int j = __ffsll((unsigned long long)sm) - 1;
@@ -2401,7 +2453,7 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   if (wnc == 0 || held || free_cl == 0 || cwe <= ws) {
     unlock_file_wave(d, file, ticket, 0, 0);
     __builtin_amdgcn_s_setprio(0);
-    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
+    if (l == 0) st_rlx(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   const uint32_t cj = (uint32_t)__builtin_ctzll(free_cl);
@@ -2411,7 +2463,7 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   __builtin_amdgcn_s_setprio(0);
   uint32_t failed = 0;
   const uint32_t n = reserve_from_wave(d, file, ws, (uint32_t)(cwe - ws), clip, bs, failed);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  drain_atomics();
   if (l == 0) st_rlx(claim, 0ull);
   wave_sync_lds();
   uint32_t keep = n;
@@ -2428,9 +2480,9 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   /* no demanded page: every page is prefetched; the window's first page is the new marker */
   const uint32_t got = keep ? alloc_wave(d, file, ~0ull, bs, keep, bid, ws) : 0;
   for (uint32_t i = got + l; i < n; i += 64)
-    if (bs->lslot[i] != 0xffffffffu) st_rel(H(d)->pt + bs->lslot[i], 0ull);
+    if (bs->lslot[i] != 0xffffffffu) st_rlx(H(d)->pt + bs->lslot[i], 0ull);
   if (got == 0) {
-    if (l == 0) st_rel(&H(d)->reqd[s].busy, 0ull);
+    if (l == 0) st_rlx(&H(d)->reqd[s].busy, 0ull);
     return;
   }
   if (got < n && l == 0) trace_ev(d, 1, GFS_EV_NOFRAME, bid, file, bs->list[got], GFS_NO_FRAME, 0, 0);
@@ -2440,21 +2492,14 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
   if (off0 + len > fsize) len = fsize - off0;
   /* the slot is this window's alone: its staging is free once its last request was counted
      off (that cleared busy), and its next generation is one past the last completed */
-  acquire_agent();
   const uint64_t gen = ld_rlx(&H(d)->slot_free[s]) + 1;
   const uint64_t tk = (gen - 1) * H(d)->rpc_slots + s;   /* for the trace only */
   if (l == 0)   /* frames count themselves off the request as they are published */
     __hip_atomic_store(G(&H(d)->reqd[s].remaining), got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t fill = (1ull << 63) | ((uint64_t)(s + 1) << 40) | (gen & ((1ull << 40) - 1));
-  for (uint32_t k = l; k < got; k += 64) st_rel(&H(d)->ffill[bs->lframe[k]], fill);
+  for (uint32_t k = l; k < got; k += 64) st_rlx(&H(d)->ffill[bs->lframe[k]], fill);
   if (l == 0) {
-    gfs_rpc_slot* rs = &H(d)->ring[s];
-    rs->file_id = file;
-    rs->npages = got;
-    rs->offset = off0;
-    rs->length = len;
-    rs->ticket = tk;
-    __hip_atomic_store(G(&rs->req_seq), gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    post_request_lane(&H(d)->ring[s], file, got, off0, len, tk, gen);   /* after the count and the fill words */
     trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)ws, GFS_NO_FRAME, got, tk);
     bcount(bs, GFS_C_REQUESTS, 1);
     bcount(bs, GFS_C_REQ_BYTES, len);
@@ -2486,20 +2531,18 @@ __device__ __attribute__((noinline)) int64_t async_finish_block(const gfs_dev* d
        blocks that joined its frames pulled and published every one of them, and the slot went
        to a later request (nothing is left to claim: no frame's fill word names this one) */
     uint64_t ds;
-    while ((int64_t)((ds = __hip_atomic_load(G(&rs->done_seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) -
-                     bs->a_gen) < 0) {
+    while ((int64_t)((ds = ld_host(&rs->done_seq)) - bs->a_gen) < 0) {
       if (expired(d, t0)) {
         st = -kETIMEDOUT;
         break;
       }
       nap(nn);
     }
-    acquire_system();   /* the staged bytes, written by the host before done_seq */
     bcount(bs, GFS_T_HOST, wall_clock64() - th0);
     if (st) bcount(bs, GFS_C_TIMEOUTS, 1);
     if (st == 0 && ds != bs->a_gen) st = 1;   /* done, and nothing left to pull */
     bs->a_status = st;
-    bs->result = rs->result;
+    bs->result = (int64_t)ld_host(&rs->result);
     bs->slot = bs->a_slot;
     bs->gen = bs->a_gen;
     bs->first_page = bs->a_first;
@@ -2514,8 +2557,8 @@ __device__ __attribute__((noinline)) int64_t async_finish_block(const gfs_dev* d
     if (tid < 64)
       claim_pulls_wave(d, bs, (1ull << 63) | ((uint64_t)(bs->a_slot + 1) << 40) | (bs->a_gen & ((1ull << 40) - 1)));
     __syncthreads();
-    block_pull(d, bs, fsize);
-    __threadfence();
+    block_pull(d, bs);
+    drain_atomics();   /* every wave's frame bytes are in memory before the frames are published */
     __syncthreads();
     if (tid < 64) (void)publish_pull_wave(d, bs, fsize, t0);
   }
@@ -2744,7 +2787,7 @@ __device__ __attribute__((noinline)) int64_t gread_page(const gfs_dev* d, BlockS
     if (bs->pull >= 3) {
       const uint64_t tp0 = wall_clock64();
       private_pull(d, bs, fsize);
-      __threadfence();
+      drain_atomics();   /* every wave's frame bytes are in memory before the frames are published */
       __syncthreads();
       if (tid == 0) {
         const int64_t st = private_publish_lane(d, bs, fsize);
@@ -2760,8 +2803,8 @@ __device__ __attribute__((noinline)) int64_t gread_page(const gfs_dev* d, BlockS
           claim_pulls_wave(d, bs, ((uint64_t)(bs->slot + 1) << 40) | (bs->gen & ((1ull << 40) - 1)));
         __syncthreads();
       }
-      block_pull(d, bs, fsize);
-      __threadfence();
+      block_pull(d, bs);
+      drain_atomics();   /* every wave's frame bytes are in memory before the frames are published */
       __syncthreads();
       if (tid < 64) {
         const int64_t st = publish_pull_wave(d, bs, fsize, wall_clock64());
