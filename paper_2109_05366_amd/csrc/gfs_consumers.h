@@ -60,30 +60,56 @@ __device__ __forceinline__ void histogram_clear(uint32_t* hist, uint32_t tid, ui
   for (uint32_t i = tid; i < kHistWords; i += nt) hist[i] = 0;
 }
 
-__device__ __forceinline__ void histogram_part(const uint8_t* buf, uint64_t n, uint32_t tid,
-                                               uint32_t nt, uint32_t* hist) {
+template <bool kSum>
+__device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, uint32_t tid, uint32_t nt,
+                                               uint32_t* hist) {
   const uint64_t n16 = n >> 4;
   const gfsd::gv4u* v = (const gfsd::gv4u*)buf;
   uint32_t* const mine = hist + (tid & (kHistColumns - 1));
+  uint64_t s = 0;
   const auto count = [&](uint32_t w) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) atomicAdd(&mine[((w >> (8 * b)) & 0xff) * kHistColumns], 1u);
   };
+  const auto unit = [&](const gfsd::v4u& x) {
+    if (kSum) s += (uint64_t)x.x + x.y + x.z + x.w;
+    count(x.x);
+    count(x.y);
+    count(x.z);
+    count(x.w);
+  };
   for (uint64_t i = tid; i < n16; i += 8ull * nt) {
     gfsd::v4u x[8];
+    if (kSum && i + 7ull * nt < n16) {   // a full round, without a test a load
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = v[i + (uint64_t)k * nt];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) unit(x[k]);
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < 8; ++k)
       if (i + (uint64_t)k * nt < n16) x[k] = v[i + (uint64_t)k * nt];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-      if (i + (uint64_t)k * nt < n16) {
-        count(x[k].x);
-        count(x[k].y);
-        count(x[k].z);
-        count(x[k].w);
-      }
+      if (i + (uint64_t)k * nt < n16) unit(x[k]);
   }
-  for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) atomicAdd(&mine[buf[j] * kHistColumns], 1u);
+  for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) {
+    atomicAdd(&mine[buf[j] * kHistColumns], 1u);
+    if (kSum) s += (uint64_t)buf[j] << (8 * (j & 3));
+  }
+  return s;
+}
+__device__ __forceinline__ void histogram_part(const uint8_t* buf, uint64_t n, uint32_t tid, uint32_t nt,
+                                               uint32_t* hist) {
+  (void)count_part<false>(buf, n, tid, nt, hist);
+}
+// checksum_part and histogram_part in one pass over the buffer, which for a large unit no longer
+// lies in the XCD's L2. Out of line: its 32 data registers are not the caller's, which keeps values
+// across gread. 64 files of 345 MiB: 307 us (two passes), 258 (one), 252 (out of line).
+__device__ __attribute__((noinline)) uint64_t checksum_histogram_part(const uint8_t* buf, uint64_t n, uint32_t tid,
+                                                                      uint32_t nt, uint32_t* hist) {
+  return count_part<true>(buf, n, tid, nt, hist);
 }
 
 // The count of byte value v over all copies (after a barrier); each lane starts at a copy of its own.

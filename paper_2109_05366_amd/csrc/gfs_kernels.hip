@@ -14,6 +14,7 @@ extern "C" int gfs_internal_zero(void* p, size_t bytes, hipStream_t s);
 namespace {
 
 using gfs_consumers::block_sum_u64;
+using gfs_consumers::checksum_histogram_part;
 using gfs_consumers::checksum_part;
 using gfs_consumers::histogram_clear;
 using gfs_consumers::histogram_count;
@@ -223,8 +224,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
       break;
     }
     total += r;
-    part += checksum_part(mybuf, (uint64_t)r, tid, nt);
-    histogram_part(mybuf, (uint64_t)r, tid, nt, lhist);
+    part += checksum_histogram_part(mybuf, (uint64_t)r, tid, nt, lhist);
     dirty = true;
     __syncthreads();
   }

@@ -130,3 +130,30 @@ def test_two_files_that_share_a_row_of_lock_notes(tmp_path, cuda):
             st = cache.stats()
             assert st["timeouts"] == 0 and st["io_errors"] == 0
             cache.reset()
+
+
+@pytest.mark.parametrize("threads", [64, 256])
+def test_batch_consumer_at_the_edges_of_its_rounds(threads, tmp_path, cuda):
+    """A batch launch's checksum and histogram over files whose last unit ends inside a 16-byte
+    piece, a word, and a round of eight pieces a thread."""
+    page, unit, rnd = 4 << 10, 64 << 10, 8 * 16 * threads
+    sizes = [1, 3, 15, 16, 17, rnd - 1, rnd, rnd + 16, rnd + 7, unit - 5, unit, unit + rnd + 2, 3 * unit + 19]
+    cfg = runner.make_config(page, 1024 * page, ra_cap_bytes=16 * page, timeout_s=20)
+    print(f"[gpu] batch consumer threads={threads}", flush=True)
+    with gfs.PageCache(cfg) as cache:
+        ids, datas = [], []
+        for i, size in enumerate(sizes):
+            data = np.random.RandomState(size).randint(0, 256, size, dtype=np.uint8)
+            p = str(tmp_path / f"b{i}.bin")
+            data.tofile(p)
+            ids.append(cache.open(p))
+            datas.append(data)
+        r = runner.BatchReader(ids, sizes, unit, 2, grid=5, threads=threads)
+        for _ in range(2):
+            r.launch(cache)
+            res = r.result()
+            words = [np.pad(d, (0, -len(d) % 4)).view("<u4") for d in datas]
+            # a file's units start on word boundaries, so their sums add up to the file's
+            np.testing.assert_array_equal(res.csum, [w.sum(dtype=np.uint64) for w in words])
+            np.testing.assert_array_equal(res.hist, [np.bincount(d, minlength=256) for d in datas])
+            assert int(res.status.sum()) == sum(sizes)
