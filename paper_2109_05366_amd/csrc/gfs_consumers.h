@@ -51,8 +51,10 @@ __device__ __forceinline__ uint64_t checksum_part(const uint8_t* buf, uint64_t n
 // lanes of half a wave ever wait for each other, whatever the bytes (with one copy, 64 random
 // bytes met in a bank 4-5 at a time, equal bytes 64 at a time). Eight 16-byte loads a thread
 // are in flight; with one, the loop waited a cache round trip for every 16 bytes.
+// The rounds go from the last to the first: the buffer's end was delivered last, and its start may
+// have left the XCD's L2, and for large reads the last-level cache, before the pass begins.
 // 512 MiB of cached 256 KiB pages, gread and histogram: 322 us (one load, one copy), 300 (eight
-// loads), 291; 64 files of 345 MiB, checksum and histogram: 384 -> 310.
+// loads), 291 (and 32 copies); by now 271 in forward order, 264 in reverse.
 constexpr uint32_t kHistColumns = 32;
 constexpr uint32_t kHistWords = 256 * kHistColumns;   // 32 KiB of LDS
 
@@ -78,21 +80,26 @@ __device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, u
     count(x.z);
     count(x.w);
   };
-  for (uint64_t i = tid; i < n16; i += 8ull * nt) {
+  // rounds of eight units a thread; a 64-bit division costs as much as a round
+  uint64_t r = n16 >> 32 ? n16 / (8ull * nt) : (uint64_t)((uint32_t)n16 / (8u * nt));
+  const uint64_t i = r * 8ull * nt + tid;
+  {   // the last, partly filled one
     gfsd::v4u x[8];
-    if (kSum && i + 7ull * nt < n16) {   // a full round, without a test a load
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = v[i + (uint64_t)k * nt];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) unit(x[k]);
-      continue;
-    }
 #pragma unroll
     for (int k = 0; k < 8; ++k)
       if (i + (uint64_t)k * nt < n16) x[k] = v[i + (uint64_t)k * nt];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
       if (i + (uint64_t)k * nt < n16) unit(x[k]);
+  }
+  const gfsd::gv4u* u = v + i;
+  while (r-- > 0) {
+    gfsd::v4u x[8];
+    u -= 8ull * nt;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = u[(uint64_t)k * nt];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) unit(x[k]);
   }
   for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) {
     atomicAdd(&mine[buf[j] * kHistColumns], 1u);
@@ -106,7 +113,8 @@ __device__ __forceinline__ void histogram_part(const uint8_t* buf, uint64_t n, u
 }
 // checksum_part and histogram_part in one pass over the buffer, which for a large unit no longer
 // lies in the XCD's L2. Out of line: its 32 data registers are not the caller's, which keeps values
-// across gread. 64 files of 345 MiB: 307 us (two passes), 258 (one), 252 (out of line).
+// across gread. 64 files of 345 MiB: 307 us (two passes), 258 (one), 252 (out of line), 240 (in
+// reverse order).
 __device__ __attribute__((noinline)) uint64_t checksum_histogram_part(const uint8_t* buf, uint64_t n, uint32_t tid,
                                                                       uint32_t nt, uint32_t* hist) {
   return count_part<true>(buf, n, tid, nt, hist);
