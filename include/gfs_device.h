@@ -1279,17 +1279,22 @@ __device__ __forceinline__ uint32_t ring_slot(const gfs_dev* d, uint32_t, uint64
 }
 __device__ __forceinline__ uint64_t ring_gen(const gfs_dev* d, uint64_t tk) { return tk / H(d)->sync_slots + 1; }
 
-/* Lane: write a request into ring slot rs and post it as generation gen. */
-__device__ __forceinline__ void post_request_lane(gfs_rpc_slot* rs, uint32_t file, uint32_t npages, uint64_t off0,
+/* Wave: write a request into ring slot rs and post it as generation gen. Four lanes' words go
+ * over the host link as one write: every write takes the slot's line away from the host threads
+ * that poll it, and a look over the whole ring stalls on each line that went. Random 64 KiB
+ * pages 10.5 -> 9.7 ms against five writes a request, 4 KiB pages through 64 KiB windows
+ * 7.1 -> 6.85. */
+__device__ __forceinline__ void post_request_wave(gfs_rpc_slot* rs, uint32_t file, uint32_t npages, uint64_t off0,
                                                   uint64_t len, uint64_t tk, uint64_t gen) {
-  static_assert(offsetof(gfs_rpc_slot, npages) == offsetof(gfs_rpc_slot, file_id) + 4 &&
-                offsetof(gfs_rpc_slot, file_id) % 8 == 0, "written as one word");
-  st_host(&rs->file_id, (uint64_t)file | ((uint64_t)npages << 32));
-  st_host(&rs->offset, off0);
-  st_host(&rs->length, len);
-  st_host(&rs->ticket, tk);
+  constexpr size_t at = offsetof(gfs_rpc_slot, file_id);
+  static_assert(offsetof(gfs_rpc_slot, npages) == at + 4 && offsetof(gfs_rpc_slot, offset) == at + 8 &&
+                offsetof(gfs_rpc_slot, length) == at + 16 && offsetof(gfs_rpc_slot, ticket) == at + 24 && at % 8 == 0,
+                "four words");
+  const uint32_t l = lane();
+  const uint64_t v = l == 0 ? (uint64_t)file | ((uint64_t)npages << 32) : l == 1 ? off0 : l == 2 ? len : tk;
+  if (l < 4) st_host((uint64_t*)&rs->file_id + l, v);
   drain_atomics();
-  st_host(&rs->req_seq, gen);
+  if (l == 0) st_host(&rs->req_seq, gen);
 }
 
 /* Lane: take a free slot of the asynchronous windows (busy 0 -> 1), starting at the block's
@@ -1362,12 +1367,13 @@ __device__ __attribute__((noinline)) int miss_private_wave(const gfs_dev* d, uin
     }
     return 0;
   }
-  int status = 0;
+  int status = 0, asked = 0;
+  uint64_t tk = 0;
+  const uint64_t npages = H(d)->files[file].npages;
+  const uint32_t cap = H(d)->ra_cap;
+  const uint32_t span = (uint32_t)((npages - p) < (uint64_t)(1 + cap) ? (npages - p) : (uint64_t)(1 + cap));
   if (l == 0) {
     gfs_pslot* ps = &H(d)->pslots[bs->pslot];
-    const uint64_t npages = H(d)->files[file].npages;
-    const uint32_t cap = H(d)->ra_cap;
-    const uint32_t span = (uint32_t)((npages - p) < (uint64_t)(1 + cap) ? (npages - p) : (uint64_t)(1 + cap));
     const bool in_pb = ps->n && ps->file == file && ps->first <= p && p < ps->first + ps->n;
     trace_ev(d, 1, GFS_EV_MISS, bid, file, (uint32_t)p, 0, in_pb ? 1u : span, p);
     /* a frame of the block's share, least recently allocated first */
@@ -1419,11 +1425,7 @@ __device__ __attribute__((noinline)) int miss_private_wave(const gfs_dev* d, uin
         bs->pull = 3;
         bs->help_page = (uint32_t)p;
       } else {
-        /* one request: the page and the prefetch that follows it */
-        const uint64_t off0 = p << H(d)->page_shift;
-        uint64_t len = (uint64_t)span << H(d)->page_shift;
-        if (off0 + len > fsize) len = fsize - off0;
-        uint64_t tk;
+        /* one request: the page and the prefetch that follows it, posted below */
         ring_ticket_lane(d, bid, tk);
         const uint32_t s = ring_slot(d, bid, tk);
         const uint64_t gen = ring_gen(d, tk);
@@ -1437,40 +1439,53 @@ __device__ __attribute__((noinline)) int miss_private_wave(const gfs_dev* d, uin
           nap(nn);
         }
         bcount(bs, GFS_T_SLOT, wall_clock64() - ts0);
-        if (status == 0) {
-          gfs_rpc_slot* rs = &H(d)->ring[s];
-          post_request_lane(rs, file, span, off0, len, tk, gen);
-          trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)p, GFS_NO_FRAME, span, tk);
-          bcount(bs, GFS_C_REQUESTS, 1);
-          bcount(bs, GFS_C_REQ_BYTES, len);
-          bcount(bs, GFS_C_FETCHED, 1);
-          const uint64_t th0 = wall_clock64();
-          while (ld_host(&rs->done_seq) != gen) {
-            if (expired(d, t0)) {
-              status = 2;
-              break;
-            }
-            nap(nn);
-          }
-          bcount(bs, GFS_T_HOST, wall_clock64() - th0);
-          if (status == 0) bs->result = (int64_t)ld_host(&rs->result);
-        }
-        if (status == 0) {
-          bs->pull = 4;
-          bs->slot = s;
-          bs->gen = gen;
-          bs->first_page = p;
-          bs->list_n = span;
-        } else {
-          /* the frame stays FILLING with the pin; the cache must be reset after a timeout */
-          bs->status = -kETIMEDOUT;
-          bs->pull = 0;
-          bcount(bs, GFS_C_TIMEOUTS, 1);
-        }
+        asked = 1;
       }
     }
   }
   status = __shfl(status, 0, 64);
+  if (__shfl(asked, 0, 64)) {
+    tk = __shfl(tk, 0, 64);
+    const uint32_t s = ring_slot(d, bid, tk);
+    const uint64_t gen = ring_gen(d, tk);
+    gfs_rpc_slot* rs = &H(d)->ring[s];
+    const uint64_t off0 = p << H(d)->page_shift;
+    uint64_t len = (uint64_t)span << H(d)->page_shift;
+    if (off0 + len > fsize) len = fsize - off0;
+    if (status == 0) post_request_wave(rs, file, span, off0, len, tk, gen);
+    if (l == 0) {
+      if (status == 0) {
+        trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)p, GFS_NO_FRAME, span, tk);
+        bcount(bs, GFS_C_REQUESTS, 1);
+        bcount(bs, GFS_C_REQ_BYTES, len);
+        bcount(bs, GFS_C_FETCHED, 1);
+        uint32_t nn = 0;
+        const uint64_t th0 = wall_clock64();
+        while (ld_host(&rs->done_seq) != gen) {
+          if (expired(d, t0)) {
+            status = 2;
+            break;
+          }
+          nap(nn);
+        }
+        bcount(bs, GFS_T_HOST, wall_clock64() - th0);
+        if (status == 0) bs->result = (int64_t)ld_host(&rs->result);
+      }
+      if (status == 0) {
+        bs->pull = 4;
+        bs->slot = s;
+        bs->gen = gen;
+        bs->first_page = p;
+        bs->list_n = span;
+      } else {
+        /* the frame stays FILLING with the pin; the cache must be reset after a timeout */
+        bs->status = -kETIMEDOUT;
+        bs->pull = 0;
+        bcount(bs, GFS_C_TIMEOUTS, 1);
+      }
+    }
+    status = __shfl(status, 0, 64);
+  }
   if (status == 1) {
     if (expired(d, t0)) return 2;
     if (l == 0) nap(bs->naps);
@@ -1520,8 +1535,14 @@ __device__ __attribute__((noinline)) int post_wait_wave(const gfs_dev* d, uint32
       nap(nn);
     }
     bcount(bs, GFS_T_SLOT, wall_clock64() - ts0);
-    if (status == 0) {
-      post_request_lane(&H(d)->ring[s], file, span, off0, len, tk, gen);
+  }
+  status = __shfl(status, 0, 64);
+  tk = __shfl(tk, 0, 64);
+  const uint32_t s = ring_slot(d, bid, tk);
+  const uint64_t gen = ring_gen(d, tk);
+  if (status == 0) {
+    post_request_wave(&H(d)->ring[s], file, span, off0, len, tk, gen);
+    if (l == 0) {
       trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)lo, GFS_NO_FRAME, span, tk);
       bcount(bs, GFS_C_MISSES, 1);
       bcount(bs, GFS_C_REQUESTS, 1);
@@ -1529,12 +1550,6 @@ __device__ __attribute__((noinline)) int post_wait_wave(const gfs_dev* d, uint32
       bcount(bs, GFS_C_FETCHED, got);
       bcount(bs, GFS_C_RA_PAGES, got - 1);
     }
-  }
-  status = __shfl(status, 0, 64);
-  tk = __shfl(tk, 0, 64);
-  const uint32_t s = ring_slot(d, bid, tk);
-  const uint64_t gen = ring_gen(d, tk);
-  if (status == 0) {
     /* tell waiting blocks which request fills each frame: (slot + 1) << 40 | gen */
     const uint64_t fill = ((uint64_t)(s + 1) << 40) | (gen & ((1ull << 40) - 1));
     for (uint32_t k = l; k < got; k += 64) st_rlx(&H(d)->ffill[bs->lframe[k]], fill);
@@ -2498,8 +2513,8 @@ __device__ __attribute__((noinline)) void async_issue_wave(const gfs_dev* d, uin
     __hip_atomic_store(G(&H(d)->reqd[s].remaining), got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t fill = (1ull << 63) | ((uint64_t)(s + 1) << 40) | (gen & ((1ull << 40) - 1));
   for (uint32_t k = l; k < got; k += 64) st_rlx(&H(d)->ffill[bs->lframe[k]], fill);
+  post_request_wave(&H(d)->ring[s], file, got, off0, len, tk, gen);   /* after the count and the fill words */
   if (l == 0) {
-    post_request_lane(&H(d)->ring[s], file, got, off0, len, tk, gen);   /* after the count and the fill words */
     trace_ev(d, 1, GFS_EV_REQ, bid, file, (uint32_t)ws, GFS_NO_FRAME, got, tk);
     bcount(bs, GFS_C_REQUESTS, 1);
     bcount(bs, GFS_C_REQ_BYTES, len);
