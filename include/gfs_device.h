@@ -516,8 +516,9 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
  * state it holds, exactly as if each had held the lock in turn, claims their windows, writes
  * state and claims back once, and leaves each its outcome in its slot ("decided n, window" or
  * "covered n"). 256 MiB through 4 KiB pages and 64 KiB windows, 4096 decisions: 22.2 ms when each
- * decision held the lock (4.8 us of it, 5.7 with the hand-off), 11.4 now (2.2 us of it), where
- * the ring slots are the bound. */
+ * decision held the lock (4.8 us of it, 5.7 with the hand-off), 11.4 with seven decided for (2.2 us
+ * of it), 6.4 by now (fifteen, and no cache maintenance: 1.4 us), where the ring slots are the
+ * bound. */
 
 enum { LOCK_OWN = 0, LOCK_LEFT = 1, LOCK_TIMEOUT = 2, LOCK_COVERED = 3, LOCK_DECIDED = 4 };
 
@@ -532,10 +533,10 @@ __device__ __forceinline__ uint64_t lock_taken(uint64_t n) { return (1ull << 62)
 /* decided: the claimed window [page - below, page + above) in claim slot `claim`; marked: the page
    after the demanded one is its stream's marker */
 __device__ __forceinline__ uint64_t lock_decided(uint64_t n, uint32_t below, uint32_t above, uint32_t claim, bool marked) {
-  const uint32_t w = below | (above << 10) | (claim << 21) | (marked ? 1u << 25 : 0u);
+  const uint32_t w = below | (above << 10) | (claim << 21) | (marked ? 1u << 26 : 0u);
   return (1ull << 62) | ((uint64_t)w << 32) | lock_covered(n);
 }
-static_assert(GFS_MAX_WINDOW_PAGES <= 1024 && GFS_CLAIMS <= 16, "a window's extent and claim slot fit lock_decided");
+static_assert(GFS_MAX_WINDOW_PAGES <= 1024 && GFS_CLAIMS <= 32, "a window's extent and claim slot fit lock_decided");
 /* A miss as its waiter notes it: pages of the read from the missed one on, cached history behind
  * it, the block (for the trace); all ones if they do not fit, which no holder decides on. The top
  * bits say whose note it is, of the files that share the row and the tickets that share the slot:
@@ -1750,8 +1751,8 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     const uint32_t w = (uint32_t)(lr >> 3);
     cws = p - (w & 0x3ffu);
     cwe = p + ((w >> 10) & 0x7ffu);
-    claim = &clp[(w >> 21) & 15u];
-    if ((w >> 25) & 1u) mark = p + 1;
+    claim = &clp[(w >> 21) & 31u];
+    if ((w >> 26) & 1u) mark = p + 1;
   } else {
     const uint64_t ticket = lr >> 3;
     /* every block waiting on this file's lock waits for this wave: let it issue first, and

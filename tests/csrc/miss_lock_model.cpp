@@ -157,7 +157,7 @@ int miss(uint64_t p, uint32_t want, Claim* win, uint32_t* cj) {
         if (v >> 62) {
           const uint32_t w = (uint32_t)(v >> 32);
           *win = {true, p - (w & 0x3ff), p + (w >> 10 & 0x7ff)};
-          *cj = w >> 21 & 15;
+          *cj = w >> 21 & 31;
           g_for_others.fetch_add(1, RLX);
           return WINDOW;
         }
