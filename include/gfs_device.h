@@ -157,7 +157,6 @@ __device__ __forceinline__ uint64_t ld_rlx(uint64_t* p) {
 __device__ __forceinline__ uint64_t ld_acq(uint64_t* p) {
   return __hip_atomic_load(G(p), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void acquire_agent() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 __device__ __forceinline__ void acquire_system() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, ""); }
 /* Ordering without cache maintenance. An agent-scope release writes the XCD's L2 back and an
  * acquire empties it, for the sake of plain (cached) accesses, and every block of the XCD pays:

@@ -121,7 +121,7 @@ __device__ __forceinline__ void st_sys_rlx(uint64_t* p, uint64_t v) {
 __device__ void complete_entry(SrvEntry* e, SrvDone* dn, uint64_t t_first) {
   const int64_t err = (int64_t)gfsd::ld_acq((uint64_t*)&e->err);
   st_sys_rlx(&dn->csum, gfsd::ld_acq(&e->csum));
-  st_sys_rlx((uint64_t*)&dn->result, (uint64_t)(err ? err : (int64_t)e->size));
+  st_sys_rlx((uint64_t*)&dn->result, (uint64_t)(err ? err : (int64_t)gfsd::ld_rlx(&e->size)));
   st_sys_rlx(&dn->t_first, t_first);
   st_sys_rlx(&dn->t_done, wall_clock64());
   st_sys_rel(&dn->flag, 1);
@@ -151,7 +151,7 @@ __device__ bool poll_host(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSu
       uint64_t size = 0, nch = 0;
       if (k < tail) {
         size = ld_sys_rlx(&subs[k].size);
-        tab[k].file = ld_sys_rlx32(&subs[k].file);
+        gfsd::st_rlx32(&tab[k].file, ld_sys_rlx32(&subs[k].file));
         nch = (size + chunk - 1) / chunk;
       }
       uint64_t sum = nch;   /* over this lane and those below it */
@@ -160,14 +160,14 @@ __device__ bool poll_host(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSu
         if ((int)l >= off) sum += o;
       }
       if (k < tail) {
-        tab[k].size = size;
-        tab[k].start = units + sum - nch;
-        tab[k].nchunks = nch;
+        gfsd::st_rlx(&tab[k].size, size);
+        gfsd::st_rlx(&tab[k].start, units + sum - nch);
+        gfsd::st_rlx(&tab[k].nchunks, nch);
         if (size == 0) complete_entry(&tab[k], &done[k], now);
       }
       units += __shfl(sum, 63, 64);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   /* every lane's entries, before units */
+    gfsd::drain_atomics();   /* every lane's entries are performed before units is written */
     if (l == 0) {
       gfsd::st_rlx(&ctl->ingested, tail);
       gfsd::st_rlx(&ctl->units, units);
@@ -195,8 +195,9 @@ __device__ bool poll_host(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSu
 }
 
 /* Wave 0: take the next unit and wait until its request is in the table, or decide to exit.
-   The words a waiting block reads are read relaxed: an agent-scope acquire would invalidate
-   its XCD's L2 each time; the table is read after one acquire fence, once the unit is there.
+   The control words and the table are written and read by device-scope atomics only: a look
+   takes in 64 entries, of which the poller may be writing the later ones, and a plain load would
+   leave their lines in the XCD's L2 as they were then, for the blocks that look next.
    hint: an entry at or before the one that holds the unit (a block's units only grow, so its
    last one's), from which 64 entries are looked at in one round. */
 __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub* subs, SrvHost* host,
@@ -229,16 +230,16 @@ __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub
     }
     idle_nap(naps, t - units < 64);
   }
-  gfsd::acquire_agent();   /* the entries, written before units */
+  gfsd::drain_atomics();   /* the entries are read after units */
   for (uint64_t base = hint; base < cap; base += 64) {
     const uint64_t i = base + l;
     uint64_t start = 0, nch = 0, sz = 0;
     uint32_t f = 0;
     if (i < cap) {
-      start = tab[i].start;
-      nch = tab[i].nchunks;
-      sz = tab[i].size;
-      f = tab[i].file;
+      start = gfsd::ld_rlx(&tab[i].start);
+      nch = gfsd::ld_rlx(&tab[i].nchunks);
+      sz = gfsd::ld_rlx(&tab[i].size);
+      f = gfsd::ld_rlx32(&tab[i].file);
     }
     const uint64_t m = __ballot(start <= t && t - start < nch);
     if (m) {
@@ -332,7 +333,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
       const uint64_t now = wall_clock64();
       gfsd::st_rlx(&ctl->progress, now);
       const uint64_t prev = __hip_atomic_fetch_add(&e->done, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-      if (prev + 1 == e->nchunks) complete_entry(e, &done[i], gfsd::ld_acq(&e->t_first));
+      if (prev + 1 == gfsd::ld_rlx(&e->nchunks)) complete_entry(e, &done[i], gfsd::ld_acq(&e->t_first));
     }
     __syncthreads();
   }
