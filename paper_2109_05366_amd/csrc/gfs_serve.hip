@@ -60,7 +60,7 @@ struct SrvCtrl {
   uint64_t ingested;    uint64_t pad1[15];   /* entries filled in (read and written by the poller only) */
   uint64_t poller;      uint64_t pad2[15];   /* 1 while a block polls the host */
   /* the line that waiting blocks read */
-  uint64_t units;                            /* units of the entries filled in (release) */
+  uint64_t units;                            /* units of the entries filled in, written after them */
   uint64_t final_n;                          /* 0 until the host has closed; then units + 1 */
   uint64_t abort;       uint64_t pad3[13];   /* 1: stop taking work */
   uint64_t progress;    uint64_t pad4[31];   /* wall_clock64 of the last chunk or submission seen */
@@ -631,6 +631,7 @@ struct gfs_serve_area {
   uint32_t* queue = nullptr;
   uint32_t* inflight = nullptr;
   ServeBuffers kept;         /* gfs_serve_run's, freed with the context */
+  std::mutex kept_mu;        /* held by the run that uses them */
 };
 
 extern "C" void gfs_internal_serve_teardown(gfs_serve_area* a) {
@@ -698,7 +699,10 @@ extern "C" int gfs_serve_run(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32
   gfs_serve_area* a = gfs_internal_ctx_serve_area(ctx);
   int dev = -1;
   if (!a || hipGetDevice(&dev) != hipSuccess) return -EIO;
-  ServeBuffers& B = a->kept;
+  /* a second run of the context at the same time gets buffers of its own */
+  std::unique_lock<std::mutex> held(a->kept_mu, std::try_to_lock);
+  ServeBuffers own;
+  ServeBuffers& B = held.owns_lock() ? a->kept : own;
   rc = B.reserve(dev, z.tab + z.ctl + z.st + z.bufs, z.sub + z.hc + z.dn);
   if (rc) return rc;
   std::vector<uint64_t> size(n), resv(n);

@@ -58,3 +58,36 @@ def test_bursts_around_a_wave(files, cuda, chunk, grid):
             _run(cache, ids, rng.randint(0, len(SIZES), n), want, chunk, grid)
         _run(cache, ids, np.zeros(70, dtype=np.int64), want, chunk, grid)   # nothing but empty files
         assert cache.stats()["timeouts"] == 0
+
+
+def test_two_runs_of_one_context_at_once(files, cuda):
+    """Each run has buffers of its own, whichever of them the context keeps."""
+    import threading
+    torch = cuda
+    paths, want = files
+    cfg = runner.make_config(PAGE, 16 << 20, ra_cap_bytes=1 << 20, rpc_slots=16, timeout_s=20)
+    asked = [np.random.RandomState(s).randint(0, len(SIZES), 40) for s in (1, 2)]
+    got, failed = [None, None], []
+    with gfs.PageCache(cfg) as cache:
+        ids = [cache.open(p) for p in paths]
+
+        def work(i):
+            try:
+                torch.cuda.set_device(0)
+                with torch.cuda.stream(torch.cuda.Stream()):
+                    for rep in range(4):
+                        print(f"[gpu] run {i} of two, rep={rep}", flush=True)
+                        got[i], _ = runner.serve(cache, [ids[f] for f in asked[i]], [0] * len(asked[i]), 16 << 20,
+                                                 chunk_bytes=16 << 10, grid=8, idle_timeout_s=20.0)
+                        np.testing.assert_array_equal(got[i]["csum"], want[asked[i]])
+                        np.testing.assert_array_equal(got[i]["result"], np.array(SIZES, dtype=np.int64)[asked[i]])
+            except Exception as e:   # noqa: BLE001 - reported below
+                failed.append(repr(e))
+
+        t = [threading.Thread(target=work, args=(i,)) for i in (0, 1)]
+        for x in t:
+            x.start()
+        for x in t:
+            x.join()
+        assert not failed, failed
+        assert cache.stats()["timeouts"] == 0
