@@ -41,7 +41,7 @@ extern "C" {
 #define GFS_MAX_RECENT 64u           /* detector: recent misses remembered per file (one per lane) */
 
 /* Threads per block of the library's workload kernels. gread is inlined into its caller;
- * at 256 threads the compiler keeps the whole miss path in registers (about 220 VGPRs, no
+ * at 256 threads the compiler keeps a cached page's path in registers (248-256 VGPRs, no
  * scratch), where a 1024-thread bound would cap it at 128 and spill to scratch memory. */
 #define GFS_MAX_BLOCK_THREADS 256u
 

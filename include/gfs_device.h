@@ -15,8 +15,7 @@
  *       Same, from the id gfs_open returned.
  *   int64_t gread (const gfs_dev* d, int fd, uint64_t offset, uint64_t size, void* dst);
  *       Copy file bytes [offset, min(offset+size, file size)) to dst (device memory of
- *       at least that many bytes; 16-byte alignment of dst and offset takes the vector
- *       path). Returns the byte count (short only at EOF, 0 at or past it) or -EBADF,
+ *       at least that many bytes, at any alignment). Returns the byte count (short only at EOF, 0 at or past it) or -EBADF,
  *       -EINVAL, -EIO (host read failed), -ENOSPC (the page's table buckets stayed full of
  *       other misses' reservations until the wait limit), -ETIMEDOUT (a wait exceeded the
  *       configured timeout; the cache must then be reset).
@@ -32,7 +31,7 @@
  * frames, publishes them, and copies its own page out. Blocks that find a page whose
  * frame is reserved or still being filled wait for it instead of fetching it again.
  *
- * Calling kernels: gread is inlined into its caller and its miss path needs about 220
+ * Calling kernels: gread is inlined into its caller and its miss path needs about 250
  * VGPRs; give the kernel __launch_bounds__(GFS_MAX_BLOCK_THREADS) or less, or the compiler
  * caps registers lower and spills every call's state to scratch memory.
  */
@@ -131,9 +130,9 @@ __device__ __forceinline__ void wave_sync_lds() {
 
 /* ------------------------------------------------------------------ the device handle
  * Written by the host before any kernel and never changed while one runs, so its fields are
- * read as constants: through the scalar cache, which no acquire empties, and kept in scalar
- * registers across fences and barriers. As ordinary memory each field was a vector load that
- * every acquire sent back to memory: about five dependent round trips a page on the hit path. */
+ * read as constants: through the scalar cache, and kept in scalar registers across waits and
+ * barriers. As ordinary memory each field was a vector load after every one of them: about five
+ * dependent round trips a page on the hit path. */
 typedef const __attribute__((address_space(4))) gfs_dev hdev;
 __device__ __forceinline__ hdev* H(const gfs_dev* d) { return (hdev*)d; }
 /* A function that is not inlined gets the handle's address in vector registers; it is the same
@@ -168,8 +167,8 @@ __device__ __forceinline__ void acquire_system() { __builtin_amdgcn_fence(__ATOM
  * outstanding memory operations (with a block barrier for those of other waves), and for a
  * reader that it issues a load only once it has seen the value the load depends on. The
  * workgroup fences keep the compiler from moving memory operations across the wait.
- * Without the releases and acquires: 256 MiB through 4 KiB pages 11.7 -> 7.2 ms (pull 95 -> 29 us,
- * allocation 36 -> 9, run 7.0 -> 3.5 a miss), random 64 KiB pages 13.8 -> 10.3. */
+ * Without the releases and acquires: 256 MiB through 4 KiB pages 11.7 -> 7.0 ms (pull 95 -> 29 us,
+ * allocation 36 -> 9, run 7.0 -> 3.5 a miss), random 64 KiB pages 13.9 -> 10.3. */
 __device__ __forceinline__ void drain_atomics() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0x0F70);   /* vmcnt(0): every load, store and atomic done */
@@ -1042,9 +1041,9 @@ __device__ __attribute__((noinline)) void copy_in(uint8_t* dst, const uint8_t* s
  * not follow each other's writes. Its bytes are read with device-scope loads (sc1), which do
  * not take a line another XCD has replaced, so a pin needs no acquire. With one per
  * hit, emptying the XCD's L2 each time, 256 MiB of cached 4 KiB pages in 128 KiB reads took
- * 253 us instead of 165, 4080-byte records 332 instead of 273. The loads go out after the pin's result was seen (and a block barrier for
- * the other waves), and the bytes reached memory before the frame was published (the fill's
- * release). They are nontemporal as well: page bytes pass once.
+ * 253 us instead of 165, 4080-byte records 332 instead of 273. The loads go out after the pin's
+ * result was seen (and a block barrier for the other waves), and the bytes reached memory before
+ * the frame was published. They are nontemporal as well: page bytes pass once.
  * N loads of 16 bytes at any alignment, issued together and waited for in the same statement;
  * every address must be readable. */
 template <int N>
@@ -1711,7 +1710,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   const uint32_t hist_pre = ra_history_wave(d, file, p, req);
   const RaParams rp = ra_params(d);
   /* what the critical section needs from the device and file records, read now: after the
-     grant's acquire, each would be a load from memory on the path every waiter waits on */
+     grant, each would be a load on the path every waiter waits on */
   gfs_file_dev* const fe = &H(d)->files[file];
   uint64_t* const clp = H(d)->claims[file].e;
   uint64_t* const lq = lock_queue(d, file);
@@ -2233,7 +2232,7 @@ __device__ __forceinline__ void request_done_lane(const gfs_dev* d, uint32_t s, 
   }
 }
 
-/* Wave 0, after the block's pull, a fence by every thread and a barrier: publish the frames
+/* Wave 0, after the block's pull, a wait by every wave and a barrier: publish the frames
  * this block pulled and count them off. Returns the status of this block's page: for its
  * own request the demanded page (list[0]), which a helper may be pulling, so it may wait.
  * On an error the block's pin on its page has been dropped. */

@@ -167,7 +167,7 @@ typedef struct gfs_file_claims {
 /* request ring slot in pinned host memory: the device writes the first cache line,
  * the host the second */
 typedef struct gfs_rpc_slot {
-  uint64_t req_seq;       /* generation, published last (system-scope release) */
+  uint64_t req_seq;       /* generation, written last */
   uint32_t file_id;
   uint32_t npages;        /* pages in the span */
   uint64_t offset;        /* file byte offset of the first page */
