@@ -2981,9 +2981,11 @@ __device__ int gclose(const gfs_dev* d, int fd) {
   return 0;
 }
 
-__device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd, uint64_t offset,
-                                                        uint64_t size, void* dst) {
-  using namespace gfsd;
+namespace gfsd {
+/* gread of `size` bytes by a block that is reading `ahead` (at least size) from offset on, in pieces:
+   the detector sees the whole read. */
+__device__ __attribute__((always_inline)) int64_t gread_piece(const gfs_dev* d, int fd, uint64_t offset, uint64_t size,
+                                                              uint64_t ahead, void* dst) {
   BlockState* bs = block_state();
   if (fd < 0 || (uint32_t)fd >= H(d)->max_files) return -kEBADF;
   uint64_t fsize;
@@ -3001,7 +3003,8 @@ __device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd
   const uint32_t sh = H(d)->page_shift;
   const uint64_t plast = (end - 1) >> sh;
   const bool grouped = H(d)->trace_level == 0;
-  if (tid == 0) bs->read_last = plast;   /* read by wave 0's miss path, after this store */
+  /* read by wave 0's miss path, after this store */
+  if (tid == 0) bs->read_last = ((ahead > fsize - offset ? fsize : offset + ahead) - 1) >> sh;
   for (uint64_t base = offset >> sh; base <= plast; base += 64) {
     const uint32_t n = plast - base < 64 ? (uint32_t)(plast - base) + 1 : 64u;
     uint64_t todo = n == 64 ? ~0ull : (1ull << n) - 1;
@@ -3020,6 +3023,25 @@ __device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd
   }
   if (tid == 0) bcount(bs, GFS_C_DELIVERED, end - offset);
   return (int64_t)(end - offset);
+}
+/* Bytes of the next piece, at offset, of a read with `left` bytes to go, for a block that consumes
+ * each piece before it reads the next: the consumer then finds it in the last-level cache, which 512
+ * blocks' units of a megabyte are too large for. Cuts lie at multiples of 256 KiB, or of a larger
+ * page, so that no page is looked up twice and a piece's look-up is a few per cent of its copy. A
+ * read that starts off a 16-byte boundary is read whole, as its pieces would not start on one in
+ * the buffer. 64 files of 345 MiB through units of 1 MiB: 240 us whole, 229 (cuts at 128 KiB 233, at
+ * 64 KiB 262); a burst of 64 requests for 313 MiB: 353 -> 343. */
+__device__ __forceinline__ uint64_t piece_bytes(const gfs_dev* d, uint64_t offset, uint64_t left) {
+  const uint32_t sh = H(d)->page_shift;
+  const uint64_t b = 1ull << (sh > 18u ? sh : 18u);
+  const uint64_t n = b - (offset & (b - 1));
+  return (offset & 15u) || n > left ? left : n;
+}
+}  // namespace gfsd
+
+__device__ __attribute__((always_inline)) int64_t gread(const gfs_dev* d, int fd, uint64_t offset,
+                                                        uint64_t size, void* dst) {
+  return gfsd::gread_piece(d, fd, offset, size, size, dst);
 }
 
 #endif /* GFS_DEVICE_H */

@@ -290,6 +290,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
     const uint32_t file = s_file;
     __syncthreads();
     int64_t r = 0;
+    uint64_t part = 0;
     if (file != cur_file) {
       if (fd >= 0) gclose(d, fd);
       fd = gopen_id(d, (int)file, GFS_O_RDONLY);
@@ -300,25 +301,27 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
     const uint64_t len = std::min<uint64_t>(chunk, size - off);
     if (r == 0) {
       // the request's first page on its own, so that its delivery time is the time to
-      // first page; then the rest of the chunk
-      const uint64_t first = k == 0 ? std::min<uint64_t>(len, d->page_size) : len;
-      uint64_t at = 0, piece = first;
-      do {
-        const int64_t got = gread(d, fd, off + at, piece, mybuf + at);
+      // first page; then the rest of the chunk, in pieces
+      for (uint64_t at = 0; at < len;) {
+        const bool head = k == 0 && at == 0;
+        const uint64_t n = head ? std::min<uint64_t>(len, d->page_size) : gfsd::piece_bytes(d, off + at, len - at);
+        uint8_t* const to = mybuf + at;
+        const int64_t got = gfsd::gread_piece(d, fd, off + at, n, head ? n : len - at, to);
         if (got < 0) {
           r = got;
           break;
         }
         r += got;
-        if (k == 0 && at == 0 && got == (int64_t)first && tid == 0) {
+        if (head && got == (int64_t)n && tid == 0) {
           uint64_t zero = 0;
           gfsd::cas64(&tab[i].t_first, zero, wall_clock64());
         }
-        at += piece;
-        piece = len - at;
-      } while (r == (int64_t)at && piece);
+        part += checksum_part(to, (uint64_t)got, tid, nt);
+        at += n;
+        if (got < (int64_t)n) break;
+        __syncthreads();
+      }
     }
-    const uint64_t part = r > 0 ? checksum_part(mybuf, (uint64_t)r, tid, nt) : 0;
     const uint64_t s = block_sum_u64(part, red, tid, nt);
     if (tid == 0) {
       SrvEntry* e = &tab[i];

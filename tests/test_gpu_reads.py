@@ -157,3 +157,33 @@ def test_batch_consumer_at_the_edges_of_its_rounds(threads, tmp_path, cuda):
             np.testing.assert_array_equal(res.csum, [w.sum(dtype=np.uint64) for w in words])
             np.testing.assert_array_equal(res.hist, [np.bincount(d, minlength=256) for d in datas])
             assert int(res.status.sum()) == sum(sizes)
+
+
+@pytest.mark.parametrize("page,unit", [(4 << 10, (300 << 10) + 16), (512 << 10, (1 << 20) + 48), (64 << 10, 256 << 10)])
+def test_batch_units_read_in_pieces(page, unit, tmp_path, cuda):
+    """Units that start before, on and after the places a unit is cut at, and units that start off
+    a 16-byte boundary, cold and cached: sums over each unit's own words, and the buffer's bytes."""
+    size = 3 * unit + 100003
+    path, data = _file(tmp_path, size, page + unit)
+    cut = max(page, 256 << 10)
+    starts = [0, 16, cut - 16, cut, cut + 16, unit, 5, cut - 7, cut + 1, size - 40, size - unit - 3]
+    cfg = runner.make_config(page, max(64 * page, 16 << 20), ra_cap_bytes=max(page, 256 << 10), timeout_s=20)
+    with gfs.PageCache(cfg) as cache:
+        fid = cache.open(path)
+        units = np.zeros(len(starts), dtype=gfs.UNIT_DTYPE)
+        for i, o in enumerate(starts):
+            units[i]["file"], units[i]["offset"] = fid, o
+            units[i]["size"] = min(unit, size - o)
+        r = runner.BatchReader(None, None, unit, 0, grid=3, units=units, nout=1)
+        got = [data[o:o + int(u["size"])] for o, u in zip(starts, units)]
+        for rep in range(2):
+            print(f"[gpu] pieces page={page} unit={unit} rep={rep}", flush=True)
+            r.launch(cache)
+            res = r.result()
+            assert int(res.csum[0]) == sum(int(np.pad(g, (0, -len(g) % 4)).view("<u4").sum(dtype=np.uint64)) for g in got)
+            np.testing.assert_array_equal(res.hist[0], sum(np.bincount(g, minlength=256) for g in got))
+            assert int(res.status.sum()) == sum(len(g) for g in got)
+        one = runner.BatchReader(None, None, unit, 0, grid=1, units=units[3:4], nout=1)
+        one.launch(cache)
+        one.result()
+        np.testing.assert_array_equal(one.buf.cpu().numpy()[:len(got[3])], got[3])
