@@ -218,18 +218,19 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
       cur_file = un.file;
       cur_out = un.out;
     }
-    for (uint64_t at = 0; at < un.size && err == 0;) {
+    for (uint64_t at = 0; at < un.size;) {
       const uint64_t n = gfsd::piece_bytes(d, un.offset + at, un.size - at);
       uint8_t* const to = mybuf + at;
       const int64_t r = gfsd::gread_piece(d, fd, un.offset + at, n, un.size - at, to);
       if (r < 0) {
         err = r;
-      } else {
-        total += r;
-        part += checksum_histogram_part(to, (uint64_t)r, tid, nt, lhist);
-        dirty = true;
+        break;
       }
+      total += r;
+      part += checksum_histogram_part(to, (uint64_t)r, tid, nt, lhist);
+      dirty = true;
       __syncthreads();
+      if ((uint64_t)r < n) break;   // the file ends in this piece, however far the unit goes on
       at += n;
     }
     if (err) break;

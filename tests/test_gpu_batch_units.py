@@ -1,0 +1,54 @@
+"""Units of a batch launch are each one gread of a file: a unit reaching past the file's end, by
+any size, delivers what the file has and ends there."""
+import numpy as np
+import pytest
+
+from paper_2109_05366_amd import gfs, runner
+
+pytestmark = pytest.mark.gpu
+
+PAGE = 64 << 10
+
+
+@pytest.fixture(scope="module")
+def cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gfs.lib()
+    return torch
+
+
+def _file(path, size, seed):
+    data = np.random.RandomState(seed).randint(0, 256, size, dtype=np.uint8)
+    data.tofile(path)
+    return data
+
+
+def _units(rows):
+    units = np.zeros(len(rows), dtype=gfs.UNIT_DTYPE)
+    for i, (f, out, offset, size) in enumerate(rows):
+        units[i]["file"], units[i]["out"], units[i]["offset"], units[i]["size"] = f, out, offset, size
+    return units
+
+
+def _sum(data):
+    return int(np.pad(data, (0, -len(data) % 4)).view("<u4").sum(dtype=np.uint64))
+
+
+@pytest.mark.parametrize("beyond", [1, 300 << 10, 1 << 40, (1 << 64) - 1])
+def test_units_past_the_end_of_the_file(beyond, tmp_path, cuda):
+    size = (700 << 10) + 13
+    data = _file(str(tmp_path / "f.bin"), size, 5)
+    with gfs.PageCache(runner.make_config(PAGE, 64 * PAGE, ra_cap_bytes=4 * PAGE, timeout_s=20)) as cache:
+        starts = [0, 16, 5, 512 << 10, size - 40, size - 1, size, size + 7, size + (1 << 30)]
+        ids = [cache.open(str(tmp_path / "f.bin")) for _ in starts]   # an output row belongs to one file id
+        rows = [(ids[i], i, o, min(max(size - o, 0) + beyond, (1 << 64) - 1)) for i, o in enumerate(starts)]
+        r = runner.BatchReader(None, None, 1 << 20, 0, grid=4, units=_units(rows), nout=len(rows))
+        for rep in range(2):
+            print(f"[gpu] units past the end by {beyond}, rep={rep}", flush=True)
+            r.launch(cache)
+            res = r.result()
+            assert [int(c) for c in res.csum] == [_sum(data[o:]) for o in starts]
+            np.testing.assert_array_equal(res.hist, [np.bincount(data[o:], minlength=256) for o in starts])
+            assert int(res.status.sum()) == sum(len(data[o:]) for o in starts)
