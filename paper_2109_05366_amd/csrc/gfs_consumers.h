@@ -62,7 +62,7 @@ __device__ __forceinline__ void histogram_clear(uint32_t* hist, uint32_t tid, ui
   for (uint32_t i = tid; i < kHistWords; i += nt) hist[i] = 0;
 }
 
-template <bool kSum>
+template <bool kSum, uint32_t kOne = 1u>
 __device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, uint32_t tid, uint32_t nt,
                                                uint32_t* hist) {
   const uint64_t n16 = n >> 4;
@@ -71,7 +71,7 @@ __device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, u
   uint64_t s = 0;
   const auto count = [&](uint32_t w) {
 #pragma unroll
-    for (int b = 0; b < 4; ++b) atomicAdd(&mine[((w >> (8 * b)) & 0xff) * kHistColumns], 1u);
+    for (int b = 0; b < 4; ++b) atomicAdd(&mine[((w >> (8 * b)) & 0xff) * kHistColumns], kOne);
   };
   const auto unit = [&](const gfsd::v4u& x) {
     if (kSum) s += (uint64_t)x.x + x.y + x.z + x.w;
@@ -102,7 +102,7 @@ __device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, u
     for (int k = 0; k < 8; ++k) unit(x[k]);
   }
   for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) {
-    atomicAdd(&mine[buf[j] * kHistColumns], 1u);
+    atomicAdd(&mine[buf[j] * kHistColumns], kOne);
     if (kSum) s += (uint64_t)buf[j] << (8 * (j & 3));
   }
   return s;
@@ -118,6 +118,11 @@ __device__ __forceinline__ void histogram_part(const uint8_t* buf, uint64_t n, u
 __device__ __attribute__((noinline)) uint64_t checksum_histogram_part(const uint8_t* buf, uint64_t n, uint32_t tid,
                                                                       uint32_t nt, uint32_t* hist) {
   return count_part<true>(buf, n, tid, nt, hist);
+}
+// Takes a buffer's bytes out of the histogram again; returns the sum to take off.
+__device__ __attribute__((noinline)) uint64_t checksum_histogram_undo(const uint8_t* buf, uint64_t n, uint32_t tid,
+                                                                      uint32_t nt, uint32_t* hist) {
+  return count_part<true, ~0u>(buf, n, tid, nt, hist);
 }
 
 // The count of byte value v over all copies (after a barrier); each lane starts at a copy of its own.

@@ -15,6 +15,7 @@ namespace {
 
 using gfs_consumers::block_sum_u64;
 using gfs_consumers::checksum_histogram_part;
+using gfs_consumers::checksum_histogram_undo;
 using gfs_consumers::checksum_part;
 using gfs_consumers::histogram_clear;
 using gfs_consumers::histogram_count;
@@ -223,6 +224,9 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
       uint8_t* const to = mybuf + at;
       const int64_t r = gfsd::gread_piece(d, fd, un.offset + at, n, un.size - at, to);
       if (r < 0) {
+        // a unit that fails adds nothing: its earlier pieces are still in the buffer
+        part -= checksum_histogram_undo(mybuf, at, tid, nt, lhist);
+        if (tid == 0) gfsd::bcount(gfsd::block_state(), GFS_C_DELIVERED, 0 - at);
         err = r;
         break;
       }

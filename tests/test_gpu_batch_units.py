@@ -1,5 +1,8 @@
 """Units of a batch launch are each one gread of a file: a unit reaching past the file's end, by
-any size, delivers what the file has and ends there."""
+any size, delivers what the file has and ends there, and a unit whose read fails adds nothing to
+its file's checksum and histogram, nor to the bytes delivered."""
+import os
+
 import numpy as np
 import pytest
 
@@ -52,3 +55,27 @@ def test_units_past_the_end_of_the_file(beyond, tmp_path, cuda):
             assert [int(c) for c in res.csum] == [_sum(data[o:]) for o in starts]
             np.testing.assert_array_equal(res.hist, [np.bincount(data[o:], minlength=256) for o in starts])
             assert int(res.status.sum()) == sum(len(data[o:]) for o in starts)
+
+
+@pytest.mark.parametrize("threads", [64, 256])
+@pytest.mark.parametrize("cut", [100, (600 << 10) + 100])
+def test_a_unit_that_fails_adds_nothing(cut, threads, tmp_path, cuda):
+    """The second file is cut on disk once it is registered, inside its first or a later piece: the
+    first file's unit is delivered, the second's fails whole."""
+    size = (1 << 20) - 48
+    good = _file(str(tmp_path / "good.bin"), size, 1)
+    _file(str(tmp_path / "cut.bin"), size, 2)
+    with gfs.PageCache(runner.make_config(PAGE, 64 * PAGE, ra_cap_bytes=2 * PAGE, timeout_s=20)) as cache:
+        ids = [cache.open(str(tmp_path / n)) for n in ("good.bin", "cut.bin")]
+        os.truncate(str(tmp_path / "cut.bin"), cut)
+        r = runner.BatchReader(None, None, 1 << 20, 0, grid=1, threads=threads, nout=2,
+                               units=_units([(ids[0], 0, 0, size), (ids[1], 1, 0, size)]))
+        print(f"[gpu] a unit that fails, cut={cut} threads={threads}", flush=True)
+        r.launch(cache)
+        res = r.result()
+        st = cache.stats()
+    assert int(res.status[0]) == -5 and st["timeouts"] == 0
+    assert [int(c) for c in res.csum] == [_sum(good), 0]
+    np.testing.assert_array_equal(res.hist[0], np.bincount(good, minlength=256))
+    assert not res.hist[1].any()
+    assert st["delivered_bytes"] == size
