@@ -309,6 +309,10 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
         const int64_t got = gfsd::gread_piece(d, fd, off + at, n, head ? n : len - at, to);
         if (got < 0) {
           r = got;
+          // what failed counts as one read: of its bytes none are delivered (the request's first
+          // page is a read of its own)
+          const uint64_t first = k == 0 ? std::min<uint64_t>(len, d->page_size) : 0;
+          if (tid == 0 && at > first) gfsd::bcount(gfsd::block_state(), GFS_C_DELIVERED, first - at);
           break;
         }
         r += got;

@@ -1,6 +1,7 @@
 """Units of a batch launch are each one gread of a file: a unit reaching past the file's end, by
 any size, delivers what the file has and ends there, and a unit whose read fails adds nothing to
-its file's checksum and histogram, nor to the bytes delivered."""
+its file's checksum and histogram, nor to the bytes delivered. A served chunk's first page is a
+gread of its own, and the rest of the chunk another."""
 import os
 
 import numpy as np
@@ -79,3 +80,16 @@ def test_a_unit_that_fails_adds_nothing(cut, threads, tmp_path, cuda):
     np.testing.assert_array_equal(res.hist[0], np.bincount(good, minlength=256))
     assert not res.hist[1].any()
     assert st["delivered_bytes"] == size
+
+
+def test_a_served_chunk_that_fails_counts_its_first_page_alone(tmp_path, cuda):
+    size = (1 << 20) - 48
+    _file(str(tmp_path / "cut.bin"), size, 2)
+    with gfs.PageCache(runner.make_config(PAGE, 64 * PAGE, ra_cap_bytes=2 * PAGE, timeout_s=20)) as cache:
+        fid = cache.open(str(tmp_path / "cut.bin"))
+        os.truncate(str(tmp_path / "cut.bin"), (600 << 10) + 100)
+        print("[gpu] a served chunk that fails", flush=True)
+        recs, _ = runner.serve(cache, [fid], [0], 64 * PAGE, grid=2, idle_timeout_s=20.0)
+        st = cache.stats()
+    assert int(recs["result"][0]) == -5 and int(recs["csum"][0]) == 0 and int(recs["first_ns"][0]) > 0
+    assert st["delivered_bytes"] == PAGE and st["timeouts"] == 0
