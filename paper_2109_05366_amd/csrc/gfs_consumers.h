@@ -46,20 +46,26 @@ __device__ __forceinline__ uint64_t checksum_part(const uint8_t* buf, uint64_t n
   return s;
 }
 
-// Byte histogram. The block counts into kHistColumns copies of the 256 counters, lane l into copy
-// l mod kHistColumns, laid out so that a lane's counters all lie in its own LDS bank: no two
-// lanes of half a wave ever wait for each other, whatever the bytes (with one copy, 64 random
-// bytes met in a bank 4-5 at a time, equal bytes 64 at a time). Eight 16-byte loads a thread
+// Byte histogram. The block counts into several copies (columns) of the 256 counters, lane l into
+// copy l mod the columns, laid out so that with 32 of them a lane's counters all lie in its own LDS
+// bank: no two lanes of half a wave ever wait for each other, whatever the bytes (with one copy, 64
+// random bytes met in a bank 4-5 at a time, equal bytes 64 at a time). Eight 16-byte loads a thread
 // are in flight; with one, the loop waited a cache round trip for every 16 bytes.
 // The rounds go from the last to the first: the buffer's end was delivered last, and its start may
 // have left the XCD's L2, and for large reads the last-level cache, before the pass begins.
 // 512 MiB of cached 256 KiB pages, gread and histogram: 322 us (one load, one copy), 300 (eight
 // loads), 291 (and 32 copies); by now 271 in forward order, 264 in reverse.
-constexpr uint32_t kHistColumns = 32;
-constexpr uint32_t kHistWords = 256 * kHistColumns;   // 32 KiB of LDS
+//
+// Blocks of one and two waves take 4 and 16 columns: a compute unit's registers hold 8 and 4 such
+// blocks, which leave 20 and 40 KiB of its LDS to each, 13-14 of them for gread's state. With 32
+// columns (32 KiB) only 3 blocks were resident.
+__host__ __device__ __forceinline__ constexpr uint32_t hist_column_bits(uint32_t nt) {
+  return nt <= 64 ? 2u : nt <= 128 ? 4u : 5u;
+}
+__host__ __device__ __forceinline__ constexpr uint32_t hist_bytes(uint32_t nt) { return 1024u << hist_column_bits(nt); }
 
 __device__ __forceinline__ void histogram_clear(uint32_t* hist, uint32_t tid, uint32_t nt) {
-  for (uint32_t i = tid; i < kHistWords; i += nt) hist[i] = 0;
+  for (uint32_t i = tid; i < 256u << hist_column_bits(nt); i += nt) hist[i] = 0;
 }
 
 template <bool kSum, uint32_t kOne = 1u>
@@ -67,11 +73,12 @@ __device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, u
                                                uint32_t* hist) {
   const uint64_t n16 = n >> 4;
   const gfsd::gv4u* v = (const gfsd::gv4u*)buf;
-  uint32_t* const mine = hist + (tid & (kHistColumns - 1));
+  const uint32_t cb = hist_column_bits(nt);
+  uint32_t* const mine = hist + (tid & ((1u << cb) - 1));
   uint64_t s = 0;
   const auto count = [&](uint32_t w) {
 #pragma unroll
-    for (int b = 0; b < 4; ++b) atomicAdd(&mine[((w >> (8 * b)) & 0xff) * kHistColumns], kOne);
+    for (int b = 0; b < 4; ++b) atomicAdd(&mine[((w >> (8 * b)) & 0xff) << cb], kOne);
   };
   const auto unit = [&](const gfsd::v4u& x) {
     if (kSum) s += (uint64_t)x.x + x.y + x.z + x.w;
@@ -102,7 +109,7 @@ __device__ __forceinline__ uint64_t count_part(const uint8_t* buf, uint64_t n, u
     for (int k = 0; k < 8; ++k) unit(x[k]);
   }
   for (uint64_t j = (n16 << 4) + tid; j < n; j += nt) {
-    atomicAdd(&mine[buf[j] * kHistColumns], kOne);
+    atomicAdd(&mine[(uint32_t)buf[j] << cb], kOne);
     if (kSum) s += (uint64_t)buf[j] << (8 * (j & 3));
   }
   return s;
@@ -126,9 +133,10 @@ __device__ __attribute__((noinline)) uint64_t checksum_histogram_undo(const uint
 }
 
 // The count of byte value v over all copies (after a barrier); each lane starts at a copy of its own.
-__device__ __forceinline__ uint32_t histogram_count(const uint32_t* hist, uint32_t v) {
+__device__ __forceinline__ uint32_t histogram_count(const uint32_t* hist, uint32_t v, uint32_t nt) {
+  const uint32_t cb = hist_column_bits(nt);
   uint32_t s = 0;
-  for (uint32_t c = 0; c < kHistColumns; ++c) s += hist[v * kHistColumns + ((c + v) & (kHistColumns - 1))];
+  for (uint32_t c = 0; c < 1u << cb; ++c) s += hist[(v << cb) + ((c + v) & ((1u << cb) - 1))];
   return s;
 }
 

@@ -17,11 +17,15 @@ using gfs_consumers::block_sum_u64;
 using gfs_consumers::checksum_histogram_part;
 using gfs_consumers::checksum_histogram_undo;
 using gfs_consumers::checksum_part;
+using gfs_consumers::hist_bytes;
+using gfs_consumers::hist_column_bits;
 using gfs_consumers::histogram_clear;
 using gfs_consumers::histogram_count;
 using gfs_consumers::histogram_part;
-using gfs_consumers::kHistColumns;
-using gfs_consumers::kHistWords;
+
+// LDS of the list reader beside its fixed part: the counters, for the consumer that counts. The
+// reads alone and the checksum hold none, so that they lose no resident blocks to it.
+uint32_t list_lds(int consumer, uint32_t threads) { return consumer == 1 ? hist_bytes(threads) : 0u; }
 
 __global__ void zero_kernel(uint64_t* p, uint64_t n8) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -52,7 +56,7 @@ __global__ void purge_file_kernel(const gfs_dev* d, uint32_t nframes, uint64_t p
 __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) list_reader_kernel(const gfs_dev* d, int file_id, const uint64_t* offsets,
                                    uint32_t reads, uint64_t read_size, int consumer,
                                    uint8_t* buf, void* out, int64_t* status, uint64_t* turn) {
-  __shared__ uint32_t hist[kHistWords];
+  extern __shared__ uint32_t hist[];   // list_lds
   __shared__ uint64_t red[16];
   __shared__ int gate_err;
   __shared__ uint64_t offs[64];   /* the block's next read offsets, fetched 64 at a time */
@@ -122,7 +126,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) list_reader_kernel(c
     }
   } else if (consumer == 1) {
     __syncthreads();
-    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = histogram_count(hist, i);
+    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = histogram_count(hist, i, nt);
   }
   if (tid == 0) status[b] = err ? err : total;
 }
@@ -135,7 +139,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
                                                                               const uint64_t* offsets, uint32_t reads,
                                                                               uint64_t read_size, int consumer,
                                                                               void* out, int64_t* status) {
-  extern __shared__ uint32_t hist[];   // kHistWords if the consumer is the histogram
+  extern __shared__ uint32_t hist[];   // list_lds
   __shared__ uint64_t red[16];
   const uint32_t b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   if (consumer == 1) histogram_clear(hist, tid, nt);
@@ -159,7 +163,8 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
         csum += word;
       }
     } else {
-      for (uint64_t j = tid; j < n; j += nt) atomicAdd(&hist[p[j] * kHistColumns + (tid & (kHistColumns - 1))], 1u);
+      const uint32_t cb = hist_column_bits(nt);
+      for (uint64_t j = tid; j < n; j += nt) atomicAdd(&hist[((uint32_t)p[j] << cb) + (tid & ((1u << cb) - 1))], 1u);
     }
   }
   __syncthreads();
@@ -167,7 +172,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
     const uint64_t s = block_sum_u64(csum, red, tid, nt);
     if (tid == 0) ((uint64_t*)out)[b] = s;
   } else {
-    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = histogram_count(hist, i);
+    for (uint32_t i = tid; i < 256; i += nt) ((uint32_t*)out)[(uint64_t)b * 256 + i] = histogram_count(hist, i, nt);
   }
   if (tid == 0) status[b] = total;
 }
@@ -178,7 +183,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) buffer_reader_kernel
 __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(const gfs_dev* d, const gfs_unit* units, uint64_t nunits,
                                     uint64_t* counter, uint8_t* buf, uint64_t unit_bytes,
                                     uint64_t* csum, uint32_t* hist, int64_t* status) {
-  __shared__ uint32_t lhist[kHistWords];
+  extern __shared__ uint32_t lhist[];   // hist_bytes
   __shared__ uint64_t red[16];
   __shared__ uint64_t s_unit;
   const uint32_t tid = threadIdx.x, nt = blockDim.x;
@@ -202,7 +207,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
         if (tid == 0) __hip_atomic_fetch_add(&csum[cur_out], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         for (uint32_t i = tid; i < 256; i += nt) {
-          const uint32_t c = histogram_count(lhist, i);
+          const uint32_t c = histogram_count(lhist, i, nt);
           if (c) atomicAdd(&hist[(uint64_t)cur_out * 256 + i], c);
         }
         __syncthreads();
@@ -244,7 +249,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
     if (tid == 0) __hip_atomic_fetch_add(&csum[cur_out], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     for (uint32_t i = tid; i < 256; i += nt) {
-      const uint32_t c = histogram_count(lhist, i);
+      const uint32_t c = histogram_count(lhist, i, nt);
       if (c) atomicAdd(&hist[(uint64_t)cur_out * 256 + i], c);
     }
   }
@@ -264,7 +269,7 @@ extern "C" int gfs_launch_batch(gfs_ctx* ctx, const gfs_unit* units, uint64_t nu
   hipStream_t s = (hipStream_t)hip_stream;
   const int rc = gfs_internal_zero(counter, 8, s);
   if (rc) return rc;
-  hipLaunchKernelGGL(batch_reader_kernel, dim3(grid), dim3(threads), 0, s, gfs_device_handle(ctx), units,
+  hipLaunchKernelGGL(batch_reader_kernel, dim3(grid), dim3(threads), hist_bytes(threads), s, gfs_device_handle(ctx), units,
                      nunits, counter, (uint8_t*)buf, unit_bytes, csum, hist, status);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
@@ -277,9 +282,8 @@ extern "C" int gfs_launch_buffer_reader(const void* data_dev, uint64_t data_size
   if (threads == 0 || threads % 64 || threads > GFS_MAX_BLOCK_THREADS) return -EINVAL;
   if (read_size == 0 || (consumer != 0 && consumer != 1)) return -EINVAL;
   if (((uintptr_t)out) & 15) return -EINVAL;
-  const uint32_t lds = consumer == 1 ? kHistWords * sizeof(uint32_t) : 0;
-  hipLaunchKernelGGL(buffer_reader_kernel, dim3(blocks), dim3(threads), lds, (hipStream_t)hip_stream,
-                     (const uint8_t*)data_dev, data_size, offsets, reads, read_size, consumer, out, status);
+  hipLaunchKernelGGL(buffer_reader_kernel, dim3(blocks), dim3(threads), list_lds(consumer, threads),
+                     (hipStream_t)hip_stream, (const uint8_t*)data_dev, data_size, offsets, reads, read_size, consumer, out, status);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
 
@@ -287,7 +291,7 @@ extern "C" int gfs_batch_grid(uint32_t threads, uint32_t* grid) {
   if (!grid || threads == 0 || threads % 64 || threads > GFS_MAX_BLOCK_THREADS) return -EINVAL;
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return -EIO;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_reader_kernel, (int)threads, 0) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_reader_kernel, (int)threads, hist_bytes(threads)) != hipSuccess)
     return -EIO;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -EIO;
   *grid = (uint32_t)(per_cu > 0 ? per_cu : 1) * (uint32_t)cus;
@@ -341,13 +345,14 @@ extern "C" int gfs_launch_list_reader(gfs_ctx* ctx, int file_id, const uint64_t*
     // the serialising gate waits on other blocks: every block must be resident at once
     int dev = 0, per_cu = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, list_reader_kernel, (int)threads, 0) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, list_reader_kernel, (int)threads,
+                                                     list_lds(consumer, threads)) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return -EIO;
     if ((uint64_t)blocks > (uint64_t)per_cu * (uint64_t)cus) return -EINVAL;
   }
   const gfs_dev* d = gfs_device_handle(ctx);
-  hipLaunchKernelGGL(list_reader_kernel, dim3(blocks), dim3(threads), 0, (hipStream_t)hip_stream, d,
-                     file_id, offsets, reads, read_size, consumer, (uint8_t*)buf, out, status, turn);
+  hipLaunchKernelGGL(list_reader_kernel, dim3(blocks), dim3(threads), list_lds(consumer, threads),
+                     (hipStream_t)hip_stream, d, file_id, offsets, reads, read_size, consumer, (uint8_t*)buf, out, status, turn);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
