@@ -31,6 +31,9 @@ def hipcc() -> str:
 # a user kernel of the device API that the tests call (gopen by path, error returns)
 PROBE_SRC = os.path.join(ROOT, "tests", "csrc", "gfs_api_probe.hip")
 PROBE_LIB = os.path.join(ROOT, "tests", "libgfs_api_probe.so")
+# the serving loop's hand-out on a table of the tests' own making
+SERVE_PROBE_SRC = os.path.join(ROOT, "tests", "csrc", "gfs_serve_probe.hip")
+SERVE_PROBE_LIB = os.path.join(ROOT, "tests", "libgfs_serve_probe.so")
 
 
 def _hipcc_shared(sources, out, verbose: bool) -> str:
@@ -52,11 +55,12 @@ def _hipcc_shared(sources, out, verbose: bool) -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source into libgfs.so, and the tests' device-API probe into
-    tests/libgfs_api_probe.so (always recompiles); returns the library path."""
+    """Compile every source into libgfs.so, and the tests' device probes into
+    tests/libgfs_*_probe.so (always recompiles); returns the library path."""
     _hipcc_shared([os.path.join(CSRC, s) for s in SOURCES], LIB, verbose)
-    if os.path.exists(PROBE_SRC):
-        _hipcc_shared([PROBE_SRC], PROBE_LIB, verbose)
+    for src, out in ((PROBE_SRC, PROBE_LIB), (SERVE_PROBE_SRC, SERVE_PROBE_LIB)):
+        if os.path.exists(src):
+            _hipcc_shared([src], out, verbose)
     return LIB
 
 

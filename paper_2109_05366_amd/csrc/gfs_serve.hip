@@ -251,7 +251,10 @@ __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub
       return kWork;
     }
   }
-  return kExit;   /* not reached: units counts the chunks of entries in the table */
+  /* not reached, as units counts the chunks of entries in the table; if it were, nobody would finish
+     this unit: stop every block at once, so that the host sees the kernel end */
+  if (l == 0) gfsd::st_rlx(&ctl->abort, 1);
+  return kExit;
 }
 
 __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const gfs_dev* d, SrvEntry* tab, uint32_t cap, SrvCtrl* ctl, const SrvSub* subs,
