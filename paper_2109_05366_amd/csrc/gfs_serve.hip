@@ -63,7 +63,8 @@ struct SrvCtrl {
   uint64_t units;                            /* units of the entries filled in, written after them */
   uint64_t final_n;                          /* 0 until the host has closed; then units + 1 */
   uint64_t abort;       uint64_t pad3[13];   /* 1: stop taking work */
-  uint64_t progress;    uint64_t pad4[31];   /* wall_clock64 of the last chunk or submission seen */
+  uint64_t progress;                         /* wall_clock64 of the last chunk or submission seen */
+  uint64_t finished;    uint64_t pad4[30];   /* units finished */
 };
 static_assert(sizeof(SrvCtrl) == 768, "a part of the scratch limit callers are told");
 
@@ -199,19 +200,22 @@ __device__ bool poll_host(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSu
    takes in 64 entries, of which the poller may be writing the later ones, and a plain load would
    leave their lines in the XCD's L2 as they were then, for the blocks that look next.
    hint: an entry at or before the one that holds the unit (a block's units only grow, so its
-   last one's), from which 64 entries are looked at in one round. */
+   last one's), from which 64 entries are looked at in one round. open: units submitted and not
+   finished, this one among them. */
 __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub* subs, SrvHost* host,
                          SrvDone* done, uint64_t chunk, uint64_t idle_ticks, uint64_t& hint, uint64_t* ok,
-                         uint32_t* file, uint64_t* size) {
+                         uint32_t* file, uint64_t* size, uint64_t* open) {
   const uint32_t l = gfsd::lane();
   uint64_t t = 0;
   if (l == 0) t = gfsd::fadd64(&ctl->taken, 1);
   t = __shfl(t, 0, 64);
   uint32_t naps = 0;
+  uint64_t units;
   while (true) {
     uint64_t v = 0;
     if (l < 3) v = gfsd::ld_rlx(l == 0 ? &ctl->units : l == 1 ? &ctl->final_n : &ctl->abort);
-    const uint64_t units = __shfl(v, 0, 64), fin = __shfl(v, 1, 64);
+    units = __shfl(v, 0, 64);
+    const uint64_t fin = __shfl(v, 1, 64);
     if (__shfl(v, 2, 64)) return kExit;
     if (t < units) break;
     if (fin && t >= fin - 1) return kExit;
@@ -231,6 +235,8 @@ __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub
     idle_nap(naps, t - units < 64);
   }
   gfsd::drain_atomics();   /* the entries are read after units */
+  const uint64_t finished = gfsd::ld_rlx(&ctl->finished);
+  *open = finished < units ? units - finished : 1;   /* finished is the younger of the two */
   for (uint64_t base = hint; base < cap; base += 64) {
     const uint64_t i = base + l;
     uint64_t start = 0, nch = 0, sz = 0;
@@ -263,7 +269,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
   __shared__ uint64_t red[16];
   __shared__ uint64_t s_i, s_k, s_size;
   __shared__ uint32_t s_file;
-  __shared__ int s_cmd;
+  __shared__ int s_cmd, s_cut;
   const uint32_t tid = threadIdx.x, nt = blockDim.x;
   uint8_t* mybuf = buf + (uint64_t)blockIdx.x * chunk;
   if (blockIdx.x == 0 && tid == 0) {
@@ -276,21 +282,23 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
   uint64_t hint = 0;   /* wave 0: the entry of the block's last unit */
   while (true) {
     if (tid < 64) {
-      uint64_t k = 0, size = 0;
+      uint64_t k = 0, size = 0, open = 0;
       uint32_t file = 0;
-      const int cmd = pick_unit(ctl, tab, cap, subs, host, done, chunk, idle_ticks, hint, &k, &file, &size);
+      const int cmd = pick_unit(ctl, tab, cap, subs, host, done, chunk, idle_ticks, hint, &k, &file, &size, &open);
       if (tid == 0) {
         s_cmd = cmd;
         s_i = hint;
         s_k = k;
         s_file = file;
         s_size = size;
+        s_cut = gfsd::cut_reads(open < gridDim.x ? open : gridDim.x, chunk) ? 1 : 0;
       }
     }
     __syncthreads();
     if (s_cmd == kExit) break;
     const uint64_t i = s_i, k = s_k, size = s_size;
     const uint32_t file = s_file;
+    const bool cut = s_cut != 0;
     __syncthreads();
     int64_t r = 0;
     uint64_t part = 0;
@@ -307,7 +315,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
       // first page; then the rest of the chunk, in pieces
       for (uint64_t at = 0; at < len;) {
         const bool head = k == 0 && at == 0;
-        const uint64_t n = head ? std::min<uint64_t>(len, d->page_size) : gfsd::piece_bytes(d, off + at, len - at);
+        const uint64_t n = head ? std::min<uint64_t>(len, d->page_size) : gfsd::piece_bytes(d, off + at, len - at, cut);
         uint8_t* const to = mybuf + at;
         const int64_t got = gfsd::gread_piece(d, fd, off + at, n, head ? n : len - at, to);
         if (got < 0) {
@@ -342,6 +350,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
       }
       const uint64_t now = wall_clock64();
       gfsd::st_rlx(&ctl->progress, now);
+      gfsd::fadd64(&ctl->finished, 1);
       const uint64_t prev = __hip_atomic_fetch_add(&e->done, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
       if (prev + 1 == gfsd::ld_rlx(&e->nchunks)) complete_entry(e, &done[i], gfsd::ld_acq(&e->t_first));
     }

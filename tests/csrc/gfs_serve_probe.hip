@@ -8,11 +8,11 @@ namespace {
 
 // out[0] what pick_unit returned, out[1] the abort word after it
 __global__ void lost_unit_kernel(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, int64_t* out) {
-  uint64_t hint = 0, k = 0, size = 0;
+  uint64_t hint = 0, k = 0, size = 0, open = 0;
   uint32_t file = 0;
   if (gfsd::lane() == 0) gfsd::st_rlx(&ctl->units, 1);
   gfsd::drain_atomics();
-  const int cmd = pick_unit(ctl, tab, cap, nullptr, nullptr, nullptr, 4096, 1, hint, &k, &file, &size);
+  const int cmd = pick_unit(ctl, tab, cap, nullptr, nullptr, nullptr, 4096, 1, hint, &k, &file, &size, &open);
   gfsd::drain_atomics();
   if (gfsd::lane() == 0) {
     out[0] = cmd;
@@ -30,3 +30,5 @@ extern "C" int gfs_test_serve_lost_unit(void* state, uint32_t cap, int64_t* out,
                      (SrvEntry*)((uint8_t*)state + sizeof(SrvCtrl)), cap, out);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
+// whether `blocks` blocks that consume reads of `bytes` cut them (host only)
+extern "C" int gfs_test_cut_reads(uint64_t blocks, uint64_t bytes) { return gfsd::cut_reads(blocks, bytes) ? 1 : 0; }

@@ -93,3 +93,49 @@ def test_a_served_chunk_that_fails_counts_its_first_page_alone(tmp_path, cuda):
         st = cache.stats()
     assert int(recs["result"][0]) == -5 and int(recs["csum"][0]) == 0 and int(recs["first_ns"][0]) > 0
     assert st["delivered_bytes"] == PAGE and st["timeouts"] == 0
+
+
+@pytest.mark.parametrize("threads", [64, 256])
+def test_units_read_in_pieces(threads, tmp_path, cuda):
+    """More blocks at work, on larger buffers, than are read whole (see test_cut_reads.py): units on,
+    before and after the places a unit is cut at, units past the end of the file, one that fails in
+    its last piece."""
+    size, unit, blocks = (3 << 20) + 1003, 1 << 20, 300
+    data = _file(str(tmp_path / "f.bin"), size, 7)
+    _file(str(tmp_path / "cut.bin"), size, 8)
+    with gfs.PageCache(runner.make_config(PAGE, 256 * PAGE, ra_cap_bytes=4 * PAGE, timeout_s=20)) as cache:
+        fid, bad = cache.open(str(tmp_path / "f.bin")), cache.open(str(tmp_path / "cut.bin"))
+        os.truncate(str(tmp_path / "cut.bin"), (900 << 10) + 100)
+        cut = 256 << 10
+        starts = [0, 16, cut - 16, cut, cut + 16, unit, 5, cut - 7, size - 40, size - unit - 3, size, size + 9]
+        good = [(fid, 0, o, unit if i % 3 else (1 << 64) - 1 - i) for i, o in enumerate(starts) if i % 3 or size - o <= unit]
+        good += [(fid, 0, 16 * i, 64 + i) for i in range(blocks - 1 - len(good))]
+        got = [data[o:min(size, o + n)] for _, _, o, n in good]
+        for rep, rows in enumerate((good, good, good + [(bad, 1, 0, unit)])):
+            print(f"[gpu] pieces threads={threads} rep={rep}", flush=True)
+            r = runner.BatchReader(None, None, unit, 0, grid=blocks, threads=threads, units=_units(rows), nout=2)
+            r.launch(cache)
+            res = r.result()
+            assert [int(c) for c in res.csum] == [sum(_sum(g) for g in got), 0]
+            np.testing.assert_array_equal(res.hist, [sum(np.bincount(g, minlength=256) for g in got), np.zeros(256, int)])
+            assert sorted(res.status)[0] == (-5 if rep == 2 else 0)
+            if rep < 2:
+                assert int(res.status.sum()) == sum(len(g) for g in got)
+        assert cache.stats()["delivered_bytes"] == 3 * sum(len(g) for g in got)
+
+
+def test_served_chunks_read_in_pieces(tmp_path, cuda):
+    """A burst of more than 256 chunks of 1 MiB in flight, cached and not, one of whose files fails."""
+    size = (8 << 20) + 24
+    datas = [_file(str(tmp_path / f"f{i}.bin"), size, i) for i in range(2)]
+    _file(str(tmp_path / "cut.bin"), size, 9)
+    with gfs.PageCache(runner.make_config(PAGE, 512 * PAGE, ra_cap_bytes=4 * PAGE, timeout_s=20)) as cache:
+        ids = [cache.open(str(tmp_path / n)) for n in ("f0.bin", "f1.bin", "cut.bin")]
+        os.truncate(str(tmp_path / "cut.bin"), (600 << 10) + 100)
+        asked = np.array([i % 2 for i in range(40)] + [2])
+        for rep in range(2):
+            print(f"[gpu] served pieces rep={rep}", flush=True)
+            recs, _ = runner.serve(cache, [ids[i] for i in asked], [0] * len(asked), 1 << 30, grid=512, idle_timeout_s=20.0)
+            np.testing.assert_array_equal(recs["csum"], np.array([_sum(d) for d in datas] + [0], dtype=np.uint64)[asked])
+            np.testing.assert_array_equal(recs["result"], np.array([size, size, -5])[asked])
+        assert cache.stats()["timeouts"] == 0
