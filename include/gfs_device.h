@@ -3024,29 +3024,34 @@ __device__ __attribute__((always_inline)) int64_t gread_piece(const gfs_dev* d, 
   if (tid == 0) bcount(bs, GFS_C_DELIVERED, end - offset);
   return (int64_t)(end - offset);
 }
-/* Whether blocks that each consume a read of `bytes` after it are better off reading and consuming
- * it in pieces: with more than 256 of them (one a compute unit) at work on more than the last-level
- * cache holds (256 MiB), a consumer finds a piece there but not a whole read. With fewer blocks a
- * piece's look-up is time nothing else fills, and with fewer bytes there is nothing to gain. Batch
- * units over 1.5 GiB of cached 64 KiB pages, us whole and cut, 256 threads: 512 blocks x 1 MiB
- * 868 and 750, 384 x 1 MiB 810 and 797, 256 x 1 MiB 844 and 845, 128 x 1 MiB 1378 and 1485,
- * 192 x 4 MiB 1097 and 1113, 64 x 4 MiB 2487 and 2789, 512 x 512 KiB 700 and 700; 128 threads:
- * 1024 x 384 KiB 882 and 793. Serving, cached, 512 blocks, chunks of 1 MiB: 20 requests of 16 MiB
- * 316 and 306, one 168 and 182. */
-__host__ __device__ __forceinline__ constexpr bool cut_reads(uint64_t blocks, uint64_t bytes) {
-  return blocks > 256 && blocks * bytes > (256ull << 20);
+/* The pieces (log2 of their bytes; kWhole: none) in which blocks that each consume a read of `bytes`
+ * after it are better off reading and consuming it. With more than 256 of them (one a compute unit)
+ * at work on more than the last-level cache holds (256 MiB), a consumer finds a piece there but not a
+ * whole read. With fewer blocks a piece's look-up is time nothing else fills, and with fewer bytes
+ * there is little to gain. 512 pieces of 256 KiB take half of that cache; more blocks, which are
+ * small ones, take pieces of 64 KiB, whose look-ups hide behind the other blocks of the unit, and
+ * from 192 MiB on.
+ * Batch units over 1.5 GiB of cached 64 KiB pages, us whole, cut at 256 KiB and at 64 KiB; 256
+ * threads: 512 blocks x 1 MiB 868, 750, -, 384 x 1 MiB 810, 797, -, 256 x 1 MiB 844, 845, -,
+ * 128 x 1 MiB 1378, 1485, -, 64 x 4 MiB 2487, 2789, -, 512 x 512 KiB 700, 700, -; 128 threads:
+ * 1024 x 1 MiB 1007, 892, 835, 768 x 1 MiB 955, 804, 764, 512 x 1 MiB 939, 839, 912, 1024 x 256 KiB
+ * 744, -, 708, 1024 x 128 KiB 714, -, 694; 64 threads: 2048 x 1 MiB 1212, 982, 865, 1024 x 256 KiB
+ * 847, -, 817, 768 x 256 KiB 929, -, 951, 512 x 1 MiB 1238, 1211, 1332. Serving, cached, 512 blocks,
+ * chunks of 1 MiB: 20 requests of 16 MiB 316, 306, -, one 168, 182, -. */
+constexpr uint32_t kWhole = 63;
+__host__ __device__ __forceinline__ constexpr uint32_t cut_reads(uint64_t blocks, uint64_t bytes) {
+  return blocks <= 256 || blocks * bytes <= ((blocks <= 512 ? 256ull : 192ull) << 20) ? kWhole : blocks <= 512 ? 18u : 16u;
 }
 /* Bytes of the next piece, at offset, of a read with `left` bytes to go, for a block that consumes
- * each piece before it reads the next (cut: cut_reads' answer; otherwise the whole read). Cuts lie at
- * multiples of 256 KiB, or of a larger page, so that no page is looked up twice and a piece's
- * look-up is a few per cent of its copy. A read that starts off a 16-byte boundary is read whole, as
- * its pieces would not start on one in the buffer. 64 files of 345 MiB through units of 1 MiB: 240 us
- * whole, 229 (cuts at 128 KiB 233, at 64 KiB 262); a burst of 64 requests for 313 MiB: 353 -> 343. */
-__device__ __forceinline__ uint64_t piece_bytes(const gfs_dev* d, uint64_t offset, uint64_t left, bool cut) {
+ * each piece before it reads the next (cut: cut_reads' answer). Cuts lie at multiples of the piece, or
+ * of a larger page, so that no page is looked up twice and a piece's look-up is a few per cent of its
+ * copy. A read that starts off a 16-byte boundary is read whole, as its pieces would not start on
+ * one in the buffer. */
+__device__ __forceinline__ uint64_t piece_bytes(const gfs_dev* d, uint64_t offset, uint64_t left, uint32_t cut) {
   const uint32_t sh = H(d)->page_shift;
-  const uint64_t b = 1ull << (sh > 18u ? sh : 18u);
+  const uint64_t b = 1ull << (sh > cut ? sh : cut);
   const uint64_t n = b - (offset & (b - 1));
-  return !cut || (offset & 15u) || n > left ? left : n;
+  return (offset & 15u) || n > left ? left : n;
 }
 }  // namespace gfsd
 

@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) batch_reader_kernel(
   uint64_t part = 0;
   int64_t err = 0, total = 0;
   bool dirty = false;
-  const bool cut = gfsd::cut_reads(nunits < gridDim.x ? nunits : gridDim.x, unit_bytes);
+  const uint32_t cut = gfsd::cut_reads(nunits < gridDim.x ? nunits : gridDim.x, unit_bytes);
   while (true) {
     if (tid == 0) s_unit = __hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();

@@ -268,8 +268,8 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
                              int64_t* status) {
   __shared__ uint64_t red[16];
   __shared__ uint64_t s_i, s_k, s_size;
-  __shared__ uint32_t s_file;
-  __shared__ int s_cmd, s_cut;
+  __shared__ uint32_t s_file, s_cut;
+  __shared__ int s_cmd;
   const uint32_t tid = threadIdx.x, nt = blockDim.x;
   uint8_t* mybuf = buf + (uint64_t)blockIdx.x * chunk;
   if (blockIdx.x == 0 && tid == 0) {
@@ -291,14 +291,14 @@ __global__ void __launch_bounds__(GFS_MAX_BLOCK_THREADS, 2) serve_kernel(const g
         s_k = k;
         s_file = file;
         s_size = size;
-        s_cut = gfsd::cut_reads(open < gridDim.x ? open : gridDim.x, chunk) ? 1 : 0;
+        s_cut = gfsd::cut_reads(open < gridDim.x ? open : gridDim.x, chunk);
       }
     }
     __syncthreads();
     if (s_cmd == kExit) break;
     const uint64_t i = s_i, k = s_k, size = s_size;
     const uint32_t file = s_file;
-    const bool cut = s_cut != 0;
+    const uint32_t cut = s_cut;
     __syncthreads();
     int64_t r = 0;
     uint64_t part = 0;

@@ -30,5 +30,8 @@ extern "C" int gfs_test_serve_lost_unit(void* state, uint32_t cap, int64_t* out,
                      (SrvEntry*)((uint8_t*)state + sizeof(SrvCtrl)), cap, out);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
-// whether `blocks` blocks that consume reads of `bytes` cut them (host only)
-extern "C" int gfs_test_cut_reads(uint64_t blocks, uint64_t bytes) { return gfsd::cut_reads(blocks, bytes) ? 1 : 0; }
+// log2 of the pieces in which `blocks` blocks that consume reads of `bytes` take them, 0: whole (host only)
+extern "C" uint32_t gfs_test_cut_reads(uint64_t blocks, uint64_t bytes) {
+  const uint32_t c = gfsd::cut_reads(blocks, bytes);
+  return c == gfsd::kWhole ? 0 : c;
+}

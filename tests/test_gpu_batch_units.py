@@ -95,18 +95,17 @@ def test_a_served_chunk_that_fails_counts_its_first_page_alone(tmp_path, cuda):
     assert st["delivered_bytes"] == PAGE and st["timeouts"] == 0
 
 
-@pytest.mark.parametrize("threads", [64, 256])
-def test_units_read_in_pieces(threads, tmp_path, cuda):
+@pytest.mark.parametrize("threads,blocks,cut", [(64, 300, 256 << 10), (256, 300, 256 << 10), (64, 600, 64 << 10)])
+def test_units_read_in_pieces(threads, blocks, cut, tmp_path, cuda):
     """More blocks at work, on larger buffers, than are read whole (see test_cut_reads.py): units on,
     before and after the places a unit is cut at, units past the end of the file, one that fails in
     its last piece."""
-    size, unit, blocks = (3 << 20) + 1003, 1 << 20, 300
+    size, unit = (3 << 20) + 1003, 1 << 20
     data = _file(str(tmp_path / "f.bin"), size, 7)
     _file(str(tmp_path / "cut.bin"), size, 8)
     with gfs.PageCache(runner.make_config(PAGE, 256 * PAGE, ra_cap_bytes=4 * PAGE, timeout_s=20)) as cache:
         fid, bad = cache.open(str(tmp_path / "f.bin")), cache.open(str(tmp_path / "cut.bin"))
         os.truncate(str(tmp_path / "cut.bin"), (900 << 10) + 100)
-        cut = 256 << 10
         starts = [0, 16, cut - 16, cut, cut + 16, unit, 5, cut - 7, size - 40, size - unit - 3, size, size + 9]
         good = [(fid, 0, o, unit if i % 3 else (1 << 64) - 1 - i) for i, o in enumerate(starts) if i % 3 or size - o <= unit]
         good += [(fid, 0, 16 * i, 64 + i) for i in range(blocks - 1 - len(good))]
