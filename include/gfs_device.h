@@ -43,6 +43,7 @@
 
 #include "gfs.h"
 #include "gfs_layout.h"
+#include "gfs_lock.h"
 
 namespace gfsd {
 
@@ -520,42 +521,13 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
 
 enum { LOCK_OWN = 0, LOCK_LEFT = 1, LOCK_TIMEOUT = 2, LOCK_COVERED = 3, LOCK_DECIDED = 4 };
 
-constexpr uint32_t kNoPage = 0x7fffffffu;   /* announced by a waiter that must hold the lock itself */
-__device__ __forceinline__ uint64_t lock_granted(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 1u); }
-__device__ __forceinline__ uint64_t lock_left(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 2u); }
-__device__ __forceinline__ uint64_t lock_covered(uint64_t n) { return (uint64_t)(((uint32_t)n << 2) | 3u); }
-__device__ __forceinline__ uint64_t lock_waiting(uint64_t n, uint64_t page) {
-  return (1ull << 63) | (page << 32) | (uint64_t)((uint32_t)n << 2);
-}
-__device__ __forceinline__ uint64_t lock_taken(uint64_t n) { return (1ull << 62) | (uint64_t)((uint32_t)n << 2); }
-/* decided: the claimed window [page - below, page + above) in claim slot `claim`; marked: the page
-   after the demanded one is its stream's marker */
-__device__ __forceinline__ uint64_t lock_decided(uint64_t n, uint32_t below, uint32_t above, uint32_t claim, bool marked) {
-  const uint32_t w = below | (above << 10) | (claim << 21) | (marked ? 1u << 26 : 0u);
-  return (1ull << 62) | ((uint64_t)w << 32) | lock_covered(n);
-}
-static_assert(GFS_MAX_WINDOW_PAGES <= 1024 && GFS_CLAIMS <= 32, "a window's extent and claim slot fit lock_decided");
-/* A miss as its waiter notes it: pages of the read from the missed one on, cached history behind
- * it, the block (for the trace); all ones if they do not fit, which no holder decides on. The top
- * bits say whose note it is, of the files that share the row and the tickets that share the slot:
- * a holder that finds another one's there grants that waiter the lock instead. (The slot's next
- * ticket of the same file comes only once this one is gone.) */
-constexpr uint64_t kNoNote = ~0ull;
-__device__ __forceinline__ uint64_t lock_note(uint32_t req, uint32_t hist, uint32_t bid) {
-  if ((req >> 20) | (hist >> 12) | (bid >> 22)) return kNoNote;
-  return (uint64_t)req | ((uint64_t)hist << 20) | ((uint64_t)bid << 32);
-}
-__device__ __forceinline__ uint64_t lock_note_tag(uint32_t file, uint64_t n) {
-  return (uint64_t)(file / GFS_LOCK_NOTE_ROWS) | ((n / GFS_LOCK_SLOTS & 63u) << 4);
-}
-static_assert(GFS_MAX_FILES / GFS_LOCK_NOTE_ROWS <= 16, "a note's file fits its tag");
 /* a ticket's slot; lq: the file's slots */
-__device__ __forceinline__ uint64_t* lock_slot(uint64_t* lq, uint64_t n) { return lq + (n & (GFS_LOCK_SLOTS - 1)); }
+__device__ __forceinline__ uint64_t* lock_slot(uint64_t* lq, uint64_t n) { return lq + lock_slot_index(n); }
 __device__ __forceinline__ uint64_t* lock_queue(const gfs_dev* d, uint32_t file) {
   return H(d)->lockq + (uint64_t)file * GFS_LOCK_SLOTS;
 }
 __device__ __forceinline__ uint64_t* lock_note_at(const gfs_dev* d, uint32_t file, uint64_t n) {
-  return H(d)->lockn + (uint64_t)(file % GFS_LOCK_NOTE_ROWS) * GFS_LOCK_SLOTS + (n & (GFS_LOCK_SLOTS - 1));
+  return H(d)->lockn + lock_note_index(file, n);
 }
 
 /* Lane 0: leave the queue if ticket t has no grant or outcome yet; true if it left, false if its
@@ -593,7 +565,7 @@ __device__ __attribute__((noinline)) uint64_t lock_file_wave(const gfs_dev* d, u
       uint64_t v = ld_rlx(sl);
       if (v != lock_granted(t)) {
         if (note == kNoNote) page = kNoPage;
-        else st_rlx(lock_note_at(d, file, t), note | (lock_note_tag(file, t) << 54));
+        else st_rlx(lock_note_at(d, file, t), lock_note_tagged(note, file, t));
         drain_atomics();   /* the note is there before the slot says so */
         while (v != lock_granted(t)) {
           if (cas64_rlx(sl, v, lock_waiting(t, page))) break;
@@ -739,9 +711,9 @@ __device__ __forceinline__ RaState ra_load_lane(gfs_file_dev* fe, uint32_t nrec,
 /* The values of a round of loads are used only from here on, after the caller's wait: without
    this the compiler put work on the first of them between the loads, and so a wait for a round
    trip before the last ones were issued. */
-__device__ __forceinline__ void ra_loaded(RaState& st, uint64_t& a, uint64_t& b, uint64_t& c) {
+__device__ __forceinline__ void ra_loaded(RaState& st, uint64_t& a, uint64_t& b) {
   asm volatile("" : "+v"(st.advice), "+v"(st.clk), "+v"(st.rn), "+v"(st.r), "+v"(st.s_next), "+v"(st.s_size),
-               "+v"(st.s_last), "+v"(st.s_valid), "+v"(st.s_marker), "+v"(a), "+v"(b), "+v"(c));
+               "+v"(st.s_last), "+v"(st.s_valid), "+v"(st.s_marker), "+v"(a), "+v"(b));
 }
 
 /* Which rule decided a window (GFS_RA_RULE_*, recorded in the trace with the detector's inputs). */
@@ -1756,24 +1728,22 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
     /* every block waiting on this file's lock waits for this wave: let it issue first, and
        keep the statistics until the lock is passed on */
     __builtin_amdgcn_s_setprio(3);
-    /* one round: the detector state, the file's window claims, and the queue slots and notes
+    /* one round: the detector state, the file's window claims, and the queue slots
        behind this ticket (a waiter that arrives or leaves after this read is handled by the
        compare-and-swaps and the grant's exchange) */
     RaState ras = ra_load_lane(fe, rp.nrec, rp.nstreams);
     uint64_t cl = ld_rlx(&clp[l & (GFS_CLAIMS - 1)]);
     const uint64_t nl = ticket + 1 + l;
     uint64_t qv = ld_rlx(lock_slot(lq, nl));
-    uint64_t qn = ld_rlx(lock_note_at(d, file, nl));
     drain_atomics();   /* the table probes below go out after the claims were read */
-    ra_loaded(ras, cl, qv, qn);
+    ra_loaded(ras, cl, qv);
     bool cl_on = l < GFS_CLAIMS && (cl & 1ull);
     uint64_t cl_lo = cl >> 32, cl_hi = (cl >> 32) + ((cl & 0xffffffffull) >> 1);
     uint64_t free_cl = __ballot(l < GFS_CLAIMS && !cl_on);
     /* the waiters right behind that can be decided for: announced, with a page, and as many as
        there are free claims left beside this block's own */
     const bool gone = qv == lock_left(nl) || (uint32_t)qv == (uint32_t)lock_covered(nl);
-    const bool waits = (qv >> 63) && (uint32_t)qv == ((uint32_t)nl << 2) &&
-                       (uint32_t)(qv >> 32) != (0x80000000u | kNoPage) && (qn >> 54) == lock_note_tag(file, nl);
+    const bool waits = (qv >> 63) && (uint32_t)qv == ((uint32_t)nl << 2) && (uint32_t)(qv >> 32) != (0x80000000u | kNoPage);
     const uint64_t stop = __ballot(!gone && !waits);
     uint32_t end = stop ? (uint32_t)__builtin_ctzll(stop) : 64u;   /* slots looked at: [0, end) */
     const uint32_t nfree = (uint32_t)__popcll(free_cl);
@@ -1787,15 +1757,18 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
         cand &= (1ull << end) - 1;
       }
     }
-    /* take them, and probe the table for all the pages, in one round: items 0 (this block) and
-       1.. (the candidates in order), two a half wave each */
+    /* take them, read their notes, and probe the table for all the pages, in one round: items 0 (this
+       block) and 1.. (the candidates in order), two a half wave each. A waiter writes its note before
+       it announces, so a note read after the announcement was seen is that one, or one that another
+       file's waiter has written over it since */
+    const uint64_t qn = ld_rlx(lock_note_at(d, file, nl));
     uint64_t held = 0;
     bool took = false;
     if ((cand >> l) & 1) {
       uint64_t v = qv;
       took = cas64_rlx(lock_slot(lq, nl), v, lock_taken(nl));
     }
-    const uint32_t nitems = 1 + (uint32_t)__popcll(cand);
+    uint32_t nitems = 1 + (uint32_t)__popcll(cand);
     {
       uint64_t e[GFS_LOCK_BATCH / 2], k[GFS_LOCK_BATCH / 2];
       uint64_t m = cand;
@@ -1825,6 +1798,17 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
         held |= ((uint32_t)m2 ? 1ull : 0ull) << (2 * u) | ((m2 >> 32) ? 2ull : 0ull) << (2 * u);
       }
     }
+    const uint64_t lost = __ballot(took && !lock_note_is(qn, file, nl));
+    if (lost) {
+      /* the first whose note is gone gets the lock instead: it and the taken ones behind it wait
+         again, before the lock is passed on */
+      end = (uint32_t)__builtin_ctzll(lost);
+      if (took && l >= end) st_rlx(lock_slot(lq, nl), qv);
+      drain_atomics();
+      took = took && l < end;
+      cand &= (1ull << end) - 1;
+      nitems = 1 + (uint32_t)__popcll(cand);
+    }
     const uint64_t taken = __ballot(took);
     /* decide in ticket order */
     const uint64_t td0 = wall_clock64();
@@ -1843,11 +1827,10 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
         m &= m - 1;
         if (((taken >> at) & 1) == 0) continue;   /* it left */
         ip = (uint32_t)__builtin_amdgcn_readlane((int)(qv >> 32), (int)at) & 0x7fffffffu;
-        const uint32_t n0 = (uint32_t)__builtin_amdgcn_readlane((int)qn, (int)at);
-        const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane((int)(qn >> 32), (int)at);
-        ireq = n0 & 0xfffffu;
-        ihist = n0 >> 20;
-        ibid = n1 & 0x3fffffu;
+        const LockNote nt = lock_note_read(lane64(qn, (int)at));
+        ireq = nt.req;
+        ihist = nt.hist;
+        ibid = nt.bid;
       }
       const bool covered = __ballot(cl_on && cl_lo <= ip && ip < cl_hi) != 0;
       const bool present = ((held >> it) & 1) != 0;
