@@ -1692,7 +1692,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
   const bool tracing = H(d)->trace_level >= 1;
   const bool async_on = H(d)->ra_async != 0;
   const uint64_t tl0 = wall_clock64();
-  const uint64_t lr = lock_file_wave(d, file, key, p, lock_note(req, hist_pre, bid), t0);
+  const uint64_t lr = lock_file_wave(d, file, key, p, lock_note(req, hist_pre, rp.cap, bid), t0);
   const int lk = (int)(lr & 7);
   const uint64_t tl1 = wall_clock64();
   if (lk != LOCK_OWN && l == 0) {
@@ -1822,6 +1822,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
       uint32_t at = 0;
       uint64_t ip = p;
       uint32_t ireq = req, ihist = hist_pre, ibid = bid;
+      RaParams irp = rp;
       if (it) {
         at = (uint32_t)__builtin_ctzll(m);
         m &= m - 1;
@@ -1831,6 +1832,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
         ireq = nt.req;
         ihist = nt.hist;
         ibid = nt.bid;
+        irp.cap = nt.cap;   /* of the waiter's launch, which may not be this block's */
       }
       const bool covered = __ballot(cl_on && cl_lo <= ip && ip < cl_hi) != 0;
       const bool present = ((held >> it) & 1) != 0;
@@ -1840,7 +1842,7 @@ __device__ __attribute__((noinline)) int miss_shared_wave(const gfs_dev* d, uint
         uint64_t ws;
         uint32_t wn, near, hist, rule;
         int rslot;
-        ra_decide_wave(ip, ireq, ihist, rp, ras, dirty, ws, wn, near, hist, rule, rslot);
+        ra_decide_wave(ip, ireq, ihist, irp, ras, dirty, ws, wn, near, hist, rule, rslot);
         if (ws + wn > npages) wn = (uint32_t)(npages - ws);
         /* asynchronous readahead: the page after the demanded one is the stream's marker */
         const bool marked = async_on && rslot >= 0 && ip + 1 < ws + wn;

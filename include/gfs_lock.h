@@ -31,18 +31,25 @@ constexpr uint64_t lock_decided(uint64_t n, uint32_t below, uint32_t above, uint
 static_assert(GFS_MAX_WINDOW_PAGES <= 1024 && GFS_CLAIMS <= 32, "a window's extent and claim slot fit lock_decided");
 
 /* ---- a miss as its waiter notes it: pages of the read from the missed one on, cached history behind
- * it, the block (for the trace); kNoNote if they do not fit, which no holder decides on. */
+ * it, the largest window its launch allows, the block (for the trace); kNoNote if they do not fit,
+ * which no holder decides on. A read longer than any window is noted as 2047 pages: the decision
+ * does not tell them apart. */
 struct LockNote {
-  uint32_t req, hist, bid;
+  uint32_t req, hist, cap, bid;
 };
 constexpr uint64_t kNoNote = ~0ull;
-constexpr uint64_t lock_note(uint32_t req, uint32_t hist, uint32_t bid) {
-  return (req >> 20) | (hist >> 12) | (bid >> 22) ? kNoNote
-                                                  : (uint64_t)req | ((uint64_t)hist << 20) | ((uint64_t)bid << 32);
+constexpr uint32_t kNoteReq = 2047;
+constexpr uint64_t lock_note(uint32_t req, uint32_t hist, uint32_t cap, uint32_t bid) {
+  return (hist >> 11) | ((cap - 1) >> 10) | (bid >> 22)
+             ? kNoNote
+             : (uint64_t)(req < kNoteReq ? req : kNoteReq) | ((uint64_t)hist << 11) | ((uint64_t)(cap - 1) << 22) |
+                   ((uint64_t)bid << 32);
 }
 constexpr LockNote lock_note_read(uint64_t v) {
-  return LockNote{(uint32_t)v & 0xfffffu, (uint32_t)v >> 20, (uint32_t)(v >> 32) & 0x3fffffu};
+  return LockNote{(uint32_t)v & kNoteReq, (uint32_t)(v >> 11) & 2047u, ((uint32_t)(v >> 22) & 1023u) + 1,
+                  (uint32_t)(v >> 32) & 0x3fffffu};
 }
+static_assert(GFS_MAX_WINDOW_PAGES <= 1024, "the cap, a history of up to one page more, and kNoteReq above both");
 
 /* Whose note it is, in the top ten bits: of the files that share the row, of the tickets that share
  * the place; never 0, which is what cleared memory holds. A holder that finds another's note there

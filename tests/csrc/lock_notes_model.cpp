@@ -5,7 +5,7 @@
 // tickets and clears their slots but not their notes.
 //
 // Threads stand in for blocks (the same number for every file). Each takes tickets of one file, writes its note (read length, cached
-// history, block: different each time), announces its page, and is granted the
+// history, largest window, block: different each time), announces its page, and is granted the
 // lock, or finds an outcome. A holder looks at the slots behind its ticket, then reads the notes of
 // those that wait, takes them, and decides for each from its note up to the first whose note is
 // another's; that one and the taken ones behind it wait again before the lock is passed on. With
@@ -104,8 +104,8 @@ void block(File* fp, uint32_t me, int misses, uint64_t seed) {
   File& f = *fp;
   std::mt19937_64 r(seed * 1000003 + me);
   for (int k = 0; k < misses && !late(); ++k) {
-    const uint32_t req = 1 + (uint32_t)(r() % 4000), hist = (uint32_t)(r() % 1026);
-    const uint64_t mine = lock_note(req, hist, me);
+    const uint32_t req = 1 + (uint32_t)(r() % 4000), hist = (uint32_t)(r() % 1026), cap = 1 + (uint32_t)(r() % 1024);
+    const uint64_t mine = lock_note(req, hist, cap, me);
     // files go on together, so that their tickets meet in the row
     while (!late()) {
       uint64_t least = ~0ull;
@@ -133,7 +133,7 @@ void block(File* fp, uint32_t me, int misses, uint64_t seed) {
     }
     g_for_others.fetch_add(1, RLX);
     const LockNote n = f.used[lock_slot_index(t)];
-    if (n.req != req || n.hist != hist || n.bid != me)
+    if (n.req != (req < kNoteReq ? req : kNoteReq) || n.hist != hist || n.cap != cap || n.bid != me)
       fail("decided on another miss", t, n.bid);
   }
 }
@@ -150,12 +150,13 @@ int main(int argc, char** argv) {
   else if (mode == "note-first") g_slot_first = false;
   else if (mode == "pass-over") g_pass_over = true;
   else if (mode != "notes") return 2;
-  for (uint32_t req : {1u, 0xfffffu})
-    for (uint32_t hist : {0u, 1025u}) {
-      const LockNote n = lock_note_read(lock_note_tagged(lock_note(req, hist, 0x3fffffu), GFS_MAX_FILES - 1, ~0ull));
-      if (n.req != req || n.hist != hist || n.bid != 0x3fffffu) fail("encoding", req, hist);
-    }
-  if (lock_note(1, 0, 0x400000u) != kNoNote || lock_note(1 << 20, 0, 0) != kNoNote) fail("a note that does not fit");
+  for (uint32_t req : {1u, 2046u, 2047u, 2048u, ~0u})
+    for (uint32_t hist : {0u, 1025u})
+      for (uint32_t cap : {1u, 1024u}) {
+        const LockNote n = lock_note_read(lock_note_tagged(lock_note(req, hist, cap, 0x3fffffu), GFS_MAX_FILES - 1, ~0ull));
+        if (n.req != (req < 2047 ? req : 2047) || n.hist != hist || n.cap != cap || n.bid != 0x3fffffu) fail("encoding", req, cap);
+      }
+  if (lock_note(1, 0, 1, 0x400000u) != kNoNote || lock_note(1, 2048, 1, 0) != kNoNote) fail("a note that does not fit");
   if (lock_note_is(0, 0, 0)) fail("cleared memory is a note");
   const char* dl = getenv("LNM_DEADLINE_S");
   g_deadline = std::chrono::steady_clock::now() + std::chrono::seconds(dl ? atoi(dl) : 60);

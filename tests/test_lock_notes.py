@@ -1,7 +1,7 @@
 """The notes that waiters of the per-file miss lock leave for its holder, as a CPU thread model under
 ThreadSanitizer on the device's encodings (tests/csrc/lock_notes_model.cpp says what it checks):
-files that share a row of notes, files opened again; and planted mistakes that the checks must
-catch."""
+files that share a row of notes, files opened again, launches of different largest windows; and
+planted mistakes that the checks must catch."""
 import os
 import shutil
 import subprocess
