@@ -297,8 +297,8 @@ int gfs_trace_read(gfs_ctx* ctx, void* dst, size_t cap_bytes, size_t* n_bytes);
 
 /* Drop every cached page, readahead stream, counter and trace record (cold start: Sec. 6
  * flushes the page cache before every run; file reads then use O_DIRECT or come after
- * POSIX_FADV_DONTNEED). Registered files stay registered. Call when no kernel using the
- * context runs. -EINVAL, -EIO. */
+ * POSIX_FADV_DONTNEED), and give back the buffers that gfs_serve_run keeps with the context.
+ * Registered files stay registered. Call when no kernel using the context runs. -EINVAL, -EIO. */
 int gfs_reset_cache(gfs_ctx* ctx);
 
 /* Stop the host threads (Sec. 2.2), free the ring and staging, close files, free the
@@ -448,7 +448,7 @@ typedef struct gfs_serve_summary {
  * the kernel is seen running. The call's device and pinned buffers (a chunk buffer per block,
  * 64 B per request) are allocated by the first call and stay with the context for the next,
  * grown when a call needs more; after a call that failed or needed more than 1 GiB, and by
- * gfs_shutdown, they are freed. The kernel runs on hip_stream, which must not carry other work that
+ * gfs_reset_cache and gfs_shutdown, they are freed. The kernel runs on hip_stream, which must not carry other work that
  * waits on it. Errors: -EINVAL (bad arguments), -EBADF (a file not registered), -ENOMEM,
  * -EIO (HIP error), -ETIMEDOUT (the kernel stopped serving); per-request failures are
  * reported in out[i].result with the call returning 0. */

@@ -33,6 +33,7 @@ extern "C" int gfs_internal_resident_blocks(uint32_t threads, uint32_t* blocks);
 struct gfs_serve_area;
 extern "C" int gfs_internal_serve_setup(int device, gfs_serve_area** out);
 extern "C" void gfs_internal_serve_teardown(gfs_serve_area* a);
+extern "C" void gfs_internal_serve_release(gfs_serve_area* a);
 extern "C" int gfs_internal_purge_file(const gfs_dev* ddev, uint32_t nframes, uint64_t pt_entries, uint32_t file,
                                        hipStream_t s);
 
@@ -594,6 +595,7 @@ int gfs_trace_read(gfs_ctx* c, void* dst, size_t cap_bytes, size_t* n_bytes) {
 int gfs_reset_cache(gfs_ctx* c) {
   if (!c) return -EINVAL;
   gfs_hostio::stop_threads(&c->io);
+  gfs_internal_serve_release(c->serve);
   int rc = zero_dynamic(c);
   // clear readahead streams, locks and clocks of registered files
   for (int i = 0; !rc && i < (int)c->cfg.max_files; ++i) {

@@ -583,7 +583,8 @@ int serve_core(gfs_ctx* ctx, const gfs_serve_request* reqs, uint32_t n, const gf
 /* Buffers of gfs_serve_run. A context keeps its last run's, so that a program that serves in
    many short runs does not pay for the memory each time: 512 blocks x 1 MiB cost 0.5 ms a run
    to allocate and free while the driver still had cleared memory, and 9-15 ms once it had to
-   clear what earlier runs gave back. A run that needs more than kKeepBytes gives it back. */
+   clear what earlier runs gave back. A run that needs more than kKeepBytes gives it back, and so do
+   gfs_reset_cache and gfs_shutdown. */
 struct ServeBuffers {
   uint8_t* dev = nullptr;    /* table, control, block status; then one chunk buffer per block */
   uint8_t* pin = nullptr;    /* submissions, host control, completion records (pinned) */
@@ -663,6 +664,13 @@ extern "C" void gfs_internal_serve_teardown(gfs_serve_area* a) {
   delete[] a->queue;
   delete[] a->inflight;
   delete a;
+}
+
+/* Called by gfs_reset_cache: give gfs_serve_run's buffers back (no run is using them then). */
+extern "C" void gfs_internal_serve_release(gfs_serve_area* a) {
+  if (!a) return;
+  std::unique_lock<std::mutex> held(a->kept_mu, std::try_to_lock);
+  if (held.owns_lock()) a->kept.clear();
 }
 
 /* Called by gfs_init with `device` current: look up this device's scratch address (once per
