@@ -235,8 +235,7 @@ __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub
     idle_nap(naps, t - units < 64);
   }
   gfsd::drain_atomics();   /* the entries are read after units */
-  const uint64_t finished = gfsd::ld_rlx(&ctl->finished);
-  *open = finished < units ? units - finished : 1;   /* finished is the younger of the two */
+  const uint64_t finished = gfsd::ld_rlx(&ctl->finished);   /* waited for with the first entries */
   for (uint64_t base = hint; base < cap; base += 64) {
     const uint64_t i = base + l;
     uint64_t start = 0, nch = 0, sz = 0;
@@ -254,6 +253,7 @@ __device__ int pick_unit(SrvCtrl* ctl, SrvEntry* tab, uint32_t cap, const SrvSub
       *ok = t - __shfl(start, at, 64);
       *file = (uint32_t)__shfl((int)f, at, 64);
       *size = __shfl(sz, at, 64);
+      *open = finished < units ? units - finished : 1;   /* finished is the younger of the two */
       return kWork;
     }
   }
