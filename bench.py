@@ -37,7 +37,7 @@ def log(msg: str) -> None:
 
 # sources the list-reader kernel is compiled from: HBM traffic counted for one version of
 # them is reported only while they are unchanged
-KERNEL_SOURCES = ("include/gfs_device.h", "include/gfs_layout.h", "include/gfs.h",
+KERNEL_SOURCES = ("include/gfs_device.h", "include/gfs_layout.h", "include/gfs_lock.h", "include/gfs.h",
                   "paper_2109_05366_amd/csrc/gfs_kernels.hip", "paper_2109_05366_amd/csrc/gfs_consumers.h")
 TRAFFIC_SUMMARY = "profiles/list_reader_c2_hbm_traffic.md"
 HIT_TRAFFIC_SUMMARY = "profiles/list_reader_hit_hbm_traffic.md"

@@ -96,7 +96,8 @@ typedef struct gfs_config {
                                     multiple of 4 KiB, 64 KiB .. 64 MiB; each host thread holds
                                     one bounce buffer of this size for O_DIRECT reads */
   uint32_t max_files;            /* files registered at once (ids 0..max_files-1), 1..GFS_MAX_FILES;
-                                    sizes the per-file metadata (about 98 KiB per file) */
+                                    sizes the per-file metadata (about 98 KiB per file, and
+                                    32 KiB more for each of the first 64) */
   /* Readahead detector (Sec. 2.3: Linux also follows several readers that interleave on one
      file, by heuristics the paper does not spell out; these are the constants of this library's
      aggregate-reading rule). A
@@ -268,7 +269,9 @@ enum {
   GFS_EV_HIT = 1,    /* file,page,frame                                         */
   GFS_EV_JOIN = 2,   /* file,page,frame                                         */
   GFS_EV_MISS = 3,   /* file,page; a = window length (EOF-clamped), b = window start |
-                        req << 32, req = pages of the read from page on (readahead on);
+                        req << 32, req = pages of the read from page on (readahead on; at
+                        most 2047, more than any window, where another block decided for
+                        this one);
                         frame = near | h << 8 | rule << 24: the detector's inputs and choice --
                         near = the file's recent misses near page, h = cached pages right
                         behind page (counted only when no stream zone or the aggregate rule

@@ -3,9 +3,10 @@
  * Include from HIP code compiled for gfx950. The functions are block-collective
  * (Sec. 2.2: each threadblock issues a file call by invoking it from all of its
  * threads): every thread of the block must call them with the same arguments, and
- * every thread gets the same result. Blocks must have a multiple of 64 threads. A
- * kernel must obtain its descriptor with gopen/gopen_id before calling gread, and
- * should gclose it at the end: the block's statistics are flushed there.
+ * every thread gets the same result. Blocks must have a multiple of 64 threads. Every
+ * block must obtain its descriptor with gopen/gopen_id before calling gread, and
+ * should gclose it at the end: the block's statistics are flushed there. A block has files
+ * of one cache open at a time (its state in LDS is that cache's until gclose).
  *
  *   int     gopen (const gfs_dev* d, const char* path, int flags);
  *       Resolve a path registered with gfs_open (path: NUL-terminated, device-readable
@@ -512,7 +513,8 @@ __device__ int64_t wait_valid_lane(const gfs_dev* d, uint32_t f, uint64_t t0) {
  * registers. So the holder takes up to GFS_LOCK_BATCH - 1 waiters right behind it along: it
  * turns their slots from "waiting" to "taken" (a waiter can no longer leave then) while the
  * table probes for all their pages are in flight, decides for each in ticket order on the
- * state it holds, exactly as if each had held the lock in turn, claims their windows, writes
+ * state it holds and from what each noted of its miss and its launch, exactly as if each had held
+ * the lock in turn, claims their windows, writes
  * state and claims back once, and leaves each its outcome in its slot ("decided n, window" or
  * "covered n"). 256 MiB through 4 KiB pages and 64 KiB windows, 4096 decisions: 22.2 ms when each
  * decision held the lock (4.8 us of it, 5.7 with the hand-off), 11.4 with seven decided for (2.2 us
@@ -1253,8 +1255,8 @@ __device__ __forceinline__ uint64_t ring_gen(const gfs_dev* d, uint64_t tk) { re
 /* Wave: write a request into ring slot rs and post it as generation gen. Four lanes' words go
  * over the host link as one write: every write takes the slot's line away from the host threads
  * that poll it, and a look over the whole ring stalls on each line that went. Random 64 KiB
- * pages 10.5 -> 9.7 ms against five writes a request, 4 KiB pages through 64 KiB windows
- * 7.1 -> 6.85. */
+ * pages 10.0 -> 9.5 ms against five writes a request, 4 KiB pages through 64 KiB windows
+ * 7.15 -> 6.85. */
 __device__ __forceinline__ void post_request_wave(gfs_rpc_slot* rs, uint32_t file, uint32_t npages, uint64_t off0,
                                                   uint64_t len, uint64_t tk, uint64_t gen) {
   constexpr size_t at = offsetof(gfs_rpc_slot, file_id);

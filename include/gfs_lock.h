@@ -58,7 +58,9 @@ constexpr uint64_t lock_note_tag(uint32_t file, uint64_t n) {
   return 1ull | ((uint64_t)(file / GFS_LOCK_NOTE_ROWS) << 1) | ((n / GFS_LOCK_SLOTS & 31u) << 5);
 }
 static_assert(GFS_MAX_FILES / GFS_LOCK_NOTE_ROWS <= 16, "a note's file fits its tag");
-constexpr uint64_t lock_note_tagged(uint64_t note, uint32_t file, uint64_t n) { return note | (lock_note_tag(file, n) << 54); }
+constexpr uint64_t lock_note_tagged(uint64_t note, uint32_t file, uint64_t n) {
+  return note | (lock_note_tag(file, n) << 54);
+}
 constexpr bool lock_note_is(uint64_t v, uint32_t file, uint64_t n) { return (v >> 54) == lock_note_tag(file, n); }
 /* a ticket's place among its file's slots, and among the notes of all files */
 constexpr uint64_t lock_slot_index(uint64_t n) { return n & (GFS_LOCK_SLOTS - 1); }

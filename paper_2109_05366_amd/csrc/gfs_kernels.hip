@@ -270,8 +270,8 @@ extern "C" int gfs_launch_batch(gfs_ctx* ctx, const gfs_unit* units, uint64_t nu
   hipStream_t s = (hipStream_t)hip_stream;
   const int rc = gfs_internal_zero(counter, 8, s);
   if (rc) return rc;
-  hipLaunchKernelGGL(batch_reader_kernel, dim3(grid), dim3(threads), hist_bytes(threads), s, gfs_device_handle(ctx), units,
-                     nunits, counter, (uint8_t*)buf, unit_bytes, csum, hist, status);
+  hipLaunchKernelGGL(batch_reader_kernel, dim3(grid), dim3(threads), hist_bytes(threads), s, gfs_device_handle(ctx),
+                     units, nunits, counter, (uint8_t*)buf, unit_bytes, csum, hist, status);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
 
@@ -284,7 +284,8 @@ extern "C" int gfs_launch_buffer_reader(const void* data_dev, uint64_t data_size
   if (read_size == 0 || (consumer != 0 && consumer != 1)) return -EINVAL;
   if (((uintptr_t)out) & 15) return -EINVAL;
   hipLaunchKernelGGL(buffer_reader_kernel, dim3(blocks), dim3(threads), list_lds(consumer, threads),
-                     (hipStream_t)hip_stream, (const uint8_t*)data_dev, data_size, offsets, reads, read_size, consumer, out, status);
+                     (hipStream_t)hip_stream, (const uint8_t*)data_dev, data_size, offsets, reads, read_size, consumer,
+                     out, status);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
 
@@ -292,7 +293,8 @@ extern "C" int gfs_batch_grid(uint32_t threads, uint32_t* grid) {
   if (!grid || threads == 0 || threads % 64 || threads > GFS_MAX_BLOCK_THREADS) return -EINVAL;
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return -EIO;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_reader_kernel, (int)threads, hist_bytes(threads)) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_reader_kernel, (int)threads,
+                                                   hist_bytes(threads)) != hipSuccess)
     return -EIO;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -EIO;
   *grid = (uint32_t)(per_cu > 0 ? per_cu : 1) * (uint32_t)cus;
@@ -354,6 +356,7 @@ extern "C" int gfs_launch_list_reader(gfs_ctx* ctx, int file_id, const uint64_t*
   }
   const gfs_dev* d = gfs_device_handle(ctx);
   hipLaunchKernelGGL(list_reader_kernel, dim3(blocks), dim3(threads), list_lds(consumer, threads),
-                     (hipStream_t)hip_stream, d, file_id, offsets, reads, read_size, consumer, (uint8_t*)buf, out, status, turn);
+                     (hipStream_t)hip_stream, d, file_id, offsets, reads, read_size, consumer, (uint8_t*)buf, out,
+                     status, turn);
   return hipGetLastError() == hipSuccess ? 0 : -EIO;
 }
